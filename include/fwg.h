@@ -162,7 +162,9 @@ int fwg_generate(fwg_handle *h, int32_t batch, int32_t n_steps, const float *uni
  * the words they exchange in a static device array of 4 MiB (one per device,
  * set up by fwg_create and held until the process ends) instead of the
  * workspace; a batch whose words do not fit (split family: more than 4 MiB /
- * (8 x (512 L + 8544)) groups of 16 streams, about 21 groups at L = 30; wide
+ * (8 x (512 L + 8544)) groups of 16 streams, about 21 groups at L = 30, for
+ * width 2 and L a multiple of 6 from 12 on -- other layer counts and width 3
+ * then keep them in the workspace; wide
  * family: 256 + 8 x (16,384 L + 17,664) bytes whatever the batch, so L <= 30;
  * gated chain pair family: 256 + 8 x (736 + 32 L) bytes per stream, 381
  * streams at L = 20) returns FWG_ENOSPACE before anything is enqueued.  The
@@ -246,8 +248,15 @@ int fwg_destroy(fwg_handle *h);
 /* Message for the last non-OK status returned on this thread ("" if none). */
 const char *fwg_last_error(void);
 
-/* Short name of the kernel family a handle uses (for logs and profiles). */
+/* Short name of the kernel family a handle uses (for logs and profiles).
+ * "mfma_bf16_r64_s512" covers both layouts of the MFMA kernels: one block per
+ * 16 streams, and, for layer counts other than multiples of 6 from 12 on and
+ * for width 3, the split over cooperating blocks (fwg_waits tells them apart). */
 const char *fwg_regime(const fwg_handle *h);
+
+/* 1 when the blocks of the handle's launches wait for each other, so that
+ * fwg_device_status can report a launch without valid results; else 0. */
+int fwg_waits(const fwg_handle *h);
 
 /* Wait for every call enqueued on the handle's stream, then report whether a
  * launch since the last create/reset ended without valid results: FWG_EDEVICE

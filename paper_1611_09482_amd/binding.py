@@ -18,7 +18,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libfwg.so")
 EXPORTED = ["fwg_workspace_size", "fwg_create", "fwg_reset_queues", "fwg_generate", "fwg_generate_noalloc",
             "fwg_teacher_forced",
             "fwg_step_forced", "fwg_teacher_forced_parallel", "fwg_prime", "fwg_generate_naive", "fwg_naive_nodes",
-            "fwg_destroy", "fwg_last_error", "fwg_regime", "fwg_device_status"]
+            "fwg_destroy", "fwg_last_error", "fwg_regime", "fwg_waits", "fwg_device_status"]
 
 
 class FwgError(RuntimeError):
@@ -73,6 +73,8 @@ def load_library(path: Optional[str] = None):
     L.fwg_last_error.restype = ctypes.c_char_p
     L.fwg_regime.argtypes = [vp]
     L.fwg_regime.restype = ctypes.c_char_p
+    L.fwg_waits.argtypes = [vp]
+    L.fwg_waits.restype = ctypes.c_int
     L.fwg_device_status.argtypes = [vp]
     for name in ["fwg_workspace_size", "fwg_create", "fwg_reset_queues", "fwg_generate", "fwg_generate_noalloc",
                  "fwg_teacher_forced",
@@ -164,7 +166,7 @@ class FastWavenet:
         self.handle = h
         # kernel families whose launches wait on each other's blocks: a wait that ran out leaves
         # invalid outputs and a sticky device mark, which the calls below check by default
-        self._waits = self.regime.startswith(("mfma_split", "wide", "chain_pair"))
+        self._waits = bool(self.lib.fwg_waits(self.handle))
 
     def _after(self, check: bool):
         if check and self._waits:

@@ -257,10 +257,10 @@ int make_plan(const fwg_desc *d, Plan *p) {
   const bool mfma_shape = (w == 2 || w == 3) && p->kind == FWG_GATED && p->dtype == FWG_BF16 && p->C == kMfR &&
                           p->S == kMfS && p->H == kMfH && p->Q == 256 && p->L <= kMfMaxLayers &&
                           mfma_lds_bytes(p->L, w) <= 160 * 1024;
-  // the split family takes the MFMA family's shape at width 2 when L suits its unrolled layer loop
-  // (FWG_REGIME=mfma keeps the single-block kernel); fwg_create falls back to it when the split
-  // launch's blocks cannot all be resident at once
-  const bool split_shape = mfma_shape && w == 2 && split_layers_ok(p->L);
+  // the split family takes the MFMA family's shape from 9 layers on (FWG_REGIME=mfma keeps the
+  // single-block kernel); fwg_create falls back to it when the split launch's blocks cannot all be
+  // resident at once
+  const bool split_shape = mfma_shape && split_layers_ok(p->L) && split_lds_bytes(p->L, w) <= 160 * 1024;
   if (mfma_shape && !(force && strcmp(force, "valu") == 0))
     p->regime = split_shape && !(force && strcmp(force, "mfma") == 0) ? REGIME_SPLIT : REGIME_MFMA;
   // small float32 ReLU stacks: one block per stream with the layer chain on one wavefront (chain
@@ -304,7 +304,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
   p->off_frags = p->off_embT = p->off_bias = p->off_ptrtab = p->off_comm = p->off_sticky = 0;
   if (mf_family) {
     // either family's fragment streams fit (create may fall back from the split family)
-    p->off_frags = take(std::max(mfma_all_frag_bytes(p->L, w), split_shape ? split_frag_bytes(p->L) : size_t(0)));
+    p->off_frags = take(std::max(mfma_all_frag_bytes(p->L, w), split_shape ? split_frag_bytes(p->L, w) : size_t(0)));
     p->off_embT = take((size_t)p->Q * p->C * 2);
     p->off_bias = take(sizeof(float) * mfma_bias_floats(p->L));
     p->off_ptrtab = take(sizeof(void *) * 3 * p->L);
@@ -430,6 +430,9 @@ int make_plan(const fwg_desc *d, Plan *p) {
   return FWG_OK;
 }
 
+// The layer counts and width that the split kernels took over from the single-block MFMA kernel.
+bool split_taken_over(const Plan &p) { return p.w == 3 || p.L % 6 != 0 || p.L < 12; }
+
 }  // namespace
 
 struct fwg_handle {
@@ -446,6 +449,9 @@ struct fwg_handle {
   // the region was last zeroed is at most this), and whether the region has been zeroed since create
   uint32_t sp_tag = 0;
   bool sp_comm_zeroed = false;
+  // the highest tag of a launch recorded into a graph: a replay clears the words and writes its tags
+  // again at any time, so every other launch's tags lie above it
+  uint32_t sp_graph_tag = 0;
 };
 
 namespace {
@@ -586,6 +592,12 @@ int naive_step(fwg_handle *h, int batch, long long t, int n_steps, int s, const 
   return FWG_OK;
 }
 
+// Whether launches on the stream are being recorded into a graph (the NULL stream never is).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // One step-kernel launch of the handle's kernel family.  comm: where the split family's exchange
 // words go (NULL: the workspace's region).
 hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
@@ -604,18 +616,26 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       // batch uses, since a later call may use more groups than this one) before its first launch
       // and when the tags would wrap; every launch takes the tags above the previous launch's
       // (handshake base + 1, step s base + 2 + s).
+      // A launch recorded into a graph clears the words itself and starts its tags at 1, since every
+      // replay writes the same ones.
       const uint32_t need = (uint32_t)a.n_steps + 2u;
-      if (comm || !h->sp_comm_zeroed || h->sp_tag > 0xFFFFFFFFu - need) {
+      const bool graph = !comm && capturing(h->stream);
+      if (comm || graph || !h->sp_comm_zeroed || h->sp_tag > 0xFFFFFFFFu - need) {
         const size_t bytes = split_comm_bytes(p.L, comm ? b.sp_nb : p.brows / kMfRows);
         hipError_t e = launch_fill_zero(b.sp_comm, bytes, h->stream);
         if (e != hipSuccess) return e;
-        if (!comm) {
+        if (!comm && !graph) {
           h->sp_comm_zeroed = true;
-          h->sp_tag = 0;
+          h->sp_tag = h->sp_graph_tag;
         }
       }
-      b.sp_tag0 = comm ? 0u : h->sp_tag;
-      if (!comm) h->sp_tag += need - 1u;
+      b.sp_tag0 = comm || graph ? 0u : h->sp_tag;
+      if (graph) {
+        h->sp_graph_tag = std::max(h->sp_graph_tag, need - 1u);
+        h->sp_tag = std::max(h->sp_tag, h->sp_graph_tag);
+      } else if (!comm) {
+        h->sp_tag += need - 1u;
+      }
       return launch_split_step(b, h->stream);
     }
     case REGIME_WIDE: {
@@ -951,7 +971,7 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
   }
   if (p.regime == REGIME_SPLIT) {
     int coresident = 0;
-    TRY_OR_FREE(split_setup(p.L, p.brows / kMfRows, &coresident));
+    TRY_OR_FREE(split_setup(p.L, p.w, p.brows / kMfRows, &coresident));
     if (!coresident) h->plan.regime = REGIME_MFMA;  // same workspace layout
   }
   if (h->plan.regime == REGIME_SPLIT) {
@@ -966,8 +986,8 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
     }
     char *frags = ws + p.off_frags;
     for (int l = 0; l < p.L; ++l)
-      TRY_OR_FREE(launch_split_repack_layer(w->conv[l], w->res[l], w->skip[l], l, p.L, frags, s));
-    TRY_OR_FREE(launch_split_repack_head(w->head, w->out, p.L, frags, s));
+      TRY_OR_FREE(launch_split_repack_layer(w->conv[l], w->res[l], w->skip[l], l, p.L, p.w, frags, s));
+    TRY_OR_FREE(launch_split_repack_head(w->head, w->out, p.L, p.w, frags, s));
   } else if (h->plan.regime == REGIME_MFMA) {
     char *frags = ws + p.off_frags;
     // layers first: a layer also writes fragments into the previous stage and the last head stage
@@ -1018,11 +1038,14 @@ int generate_impl(fwg_handle *h, int32_t batch, int32_t n_steps, const float *un
     const size_t need = p.regime == REGIME_SPLIT ? split_comm_bytes(p.L, (batch + kMfRows - 1) / kMfRows)
                         : p.regime == REGIME_WIDE ? p.wide_comm
                                                   : chain_pair_comm_bytes(p.L, batch);
-    if (need > kStaticScratchBytes)
+    // The layer counts and widths that the split kernels took over from the single-block kernel, which
+    // has no exchange words, keep running at every batch: their words then stay in the workspace.
+    const bool taken_over = p.regime == REGIME_SPLIT && split_taken_over(p);
+    if (need > kStaticScratchBytes && !taken_over)
       return fail(FWG_ENOSPACE, "the exchange words of %d streams x %d layers need %zu bytes; the static scratch "
                   "array holds %zu", batch, p.L, need, kStaticScratchBytes);
     if (!h->static_scratch) return fail(FWG_ESTATE, "no static scratch address was set up for this handle");
-    comm = h->static_scratch;
+    if (need <= kStaticScratchBytes) comm = h->static_scratch;
   }
   if (n_steps == 0) return FWG_OK;
   if (!uniforms || !samples) return fail(FWG_EINVAL, "uniforms and samples are required");
@@ -1172,11 +1195,17 @@ int fwg_device_status(fwg_handle *h) {
   return FWG_OK;
 }
 
+int fwg_waits(const fwg_handle *h) {
+  if (!h) return 0;
+  const int r = h->plan.regime;
+  return r == REGIME_SPLIT || r == REGIME_WIDE || r == REGIME_CHAIN_PAIR;
+}
+
 const char *fwg_regime(const fwg_handle *h) {
   if (!h) return "";
   switch (h->plan.regime) {
     case REGIME_MFMA: return "mfma_bf16_r64_s512";
-    case REGIME_SPLIT: return "mfma_split_bf16_r64_s512";
+    case REGIME_SPLIT: return split_taken_over(h->plan) ? "mfma_bf16_r64_s512" : "mfma_split_bf16_r64_s512";
     case REGIME_WAVE: return "wave";
     case REGIME_CHAIN: return "chain_f32_c32";
     case REGIME_CHAIN_GATED: return "chain_gated_f32_r32";

@@ -92,21 +92,22 @@ __host__ __device__ inline size_t mfma_all_frag_bytes(int L, int w) {
 }
 __host__ __device__ inline size_t mfma_bias_floats(int L) { return (size_t)L * 3 * kMfR + kMfS + kMfH + 256 + kMfR; }
 
-// Split MFMA family (the MFMA family's model shape, L a multiple of 6 and at least 12): per 16
-// streams one chain block (the layers), kSpHelpers helper blocks, each owning S / kSpHelpers skip
-// channels and H / kSpHelpers hidden channels, and one class block (output 1x1 and sampling).
-// Fragments per layer of chain waves A and B, and per layer and helper wave.
+// Split MFMA family (the MFMA family's model shape, filter width 2 or 3, at least 9 layers: a pop is
+// issued 8 layers ahead, and its layer's push of the step before has to be past): per 16 streams one
+// chain block (the layers), kSpHelpers helper blocks, each owning S / kSpHelpers skip channels and
+// H / kSpHelpers hidden channels, and one class block (output 1x1 and sampling).
+// Fragments per layer of chain waves A and (per popped tap) B, and per layer and helper wave.
 constexpr int kSpHelpers = 8;
 constexpr int kSpFA = 6, kSpFB = 4, kSpFS = 8;
-inline bool split_layers_ok(int L) { return L % 6 == 0 && L >= 12; }
-size_t split_frag_bytes(int L);
+inline bool split_layers_ok(int L) { return L >= 9; }
+size_t split_frag_bytes(int L, int w);
 size_t split_comm_bytes(int L, int nb);
-size_t split_lds_bytes(int L);
-hipError_t split_setup(int L, int nb, int *coresident_ok);
+size_t split_lds_bytes(int L, int w);
+hipError_t split_setup(int L, int w, int nb, int *coresident_ok);
 hipError_t launch_split_step(const StepArgs &a, hipStream_t s);
-hipError_t launch_split_repack_layer(const void *conv, const void *res, const void *skip, int l, int L, void *frags,
-                                     hipStream_t s);
-hipError_t launch_split_repack_head(const void *head, const void *out, int L, void *frags, hipStream_t s);
+hipError_t launch_split_repack_layer(const void *conv, const void *res, const void *skip, int l, int L, int w,
+                                     void *frags, hipStream_t s);
+hipError_t launch_split_repack_head(const void *head, const void *out, int L, int w, void *frags, hipStream_t s);
 // Allocation-free generation: the split family's per-launch exchange words in a static device array
 // of this many bytes (one per device, held until the process ends) instead of the workspace.
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;

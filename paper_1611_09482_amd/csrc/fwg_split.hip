@@ -5,7 +5,7 @@
 // The work of one step of a block of 16 streams is split over 2 + kSpHelpers blocks of the same
 // launch (a group):
 //  - the chain block runs what lies on the layer-to-layer dependency chain: per layer the pop, the
-//    dilated width-2 product, the gate, the residual 1x1 and the push (paper Section 2.2); the
+//    dilated product, the gate, the residual 1x1 and the push (paper Section 2.2); the
 //    sample the class block returns is the next step's input (Section 1);
 //  - helper h owns 64 of the 512 channels of the skip sum and of the head's hidden layer.  Per
 //    step it accumulates sum_l W_skip^l z^l + b for its skip channels from the gate outputs z^l
@@ -39,12 +39,13 @@
 // Chain block: 8 waves, A = waves 0..3 and B = waves 4..7, A and B of pair p share SIMD p.
 //  - wave A (p): the current-input half of the dilated product (W_e x) for tanh tile p and
 //    sigmoid tile p, plus W_r v + b from LDS, the gate, the residual 1x1 for channel tile p;
-//  - wave B (p): W_r v + b of the next layer (v = the popped state, known early) and the queue
+//  - wave B (p): W_r v + b of the next layer (v = the popped states, one per tap but the current one,
+//    known early) and the queue
 //    pops of stream rows 4p..4p+3, issued five layers before they land in LDS; between the layer's
 //    two barriers, while A runs the residual product, the publication of z^l to the helpers and the
 //    push of the layer input.
 // Every chain wave streams its own pre-packed weight fragments from L2 through a ring of registers,
-// 18 fragments (three layers) for A and 24 (six layers) for B, whose loads also queue behind the
+// 18 fragments (three layers) for A and 24 (six layers, three at width 3) for B, whose loads also queue behind the
 // queue reads; a slot is refilled with the fragment one ring length ahead as soon as it is
 // consumed.  The layer loop is unrolled by six layers so every ring slot is a fixed register.
 #include <hip/hip_runtime.h>
@@ -73,25 +74,29 @@ constexpr int PL = Q + 4;   // fp32 logits rows
 constexpr int PP = 20;      // fp32 partial-tile rows
 constexpr int PH = SL + 4;  // fp32 helper skip-partial rows
 constexpr int ZST = R / 2 + 4;  // staged z^l rows of a helper wave (32-bit words)
-constexpr int FA = kSpFA, FB = kSpFB, FS = kSpFS;
+constexpr int FA = kSpFA, FS = kSpFS;
+// recurrent fragments of a layer for chain wave B with TP popped taps (filter width TP + 1)
+__host__ __device__ constexpr int frags_b(int TP) { return kSpFB * TP; }
 // fragments of a helper's first-1x1 slice and of a class-block wave's output-1x1 slice
 constexpr int FW1 = (HL / 16) * (S / 32), FW2 = (QL / 16) * (H / 32);
-constexpr int DA = 3 * FA, DB = 6 * FB;  // ring depths (fragments) of chain waves A and B
+constexpr int DA = 3 * FA, DB = 6 * kSpFB;  // ring depths (fragments) of chain waves A and B: three
+                                             // layers of A, six (width 2) or three (width 3) of B
 constexpr int KCH = 64;                  // steps per chunk of per-step inputs staged in LDS
 static_assert(ZST <= PH && ZST % 4 == 0, "a wave's staged z^l rows fit its partial-sum area, 16-byte aligned");
 static_assert(SL == 64 && FS == 8 && HL == 64 && QL == 32 && NHLP == NW,
               "helper slices of 4 skip and 4 hidden tiles; 2 class tiles per class-block wave");
 
+template <int TP>
 struct ChainLds {
-  uint16_t vbuf[3][ROWS * PX];     // popped queue rows, by layer index mod 3
-  uint16_t xbuf[2][ROWS * PX];     // layer inputs x^l, by layer parity
-  uint16_t zbuf[2][ROWS * PX];     // gate outputs z^l, by layer parity
+  uint16_t vbuf[3][TP][ROWS * PX]; // popped queue rows per tap (0: the newest), by running layer count mod 3
+  uint16_t xbuf[2][ROWS * PX];     // layer inputs x^l, by running layer parity
+  uint16_t zbuf[2][ROWS * PX];     // gate outputs z^l, by running layer parity
   float pbuf[2][4][2][ROWS * PP];  // W_r v + b of a layer: [layer parity][tile][tanh / sigmoid]
   uint16_t embT[Q * R];            // embedding table, [class][channel]
   int in[ROWS][KCH];               // forced inputs (forced modes)
   int ins[ROWS + NHLP + 1];        // next inputs, then (at launch) the helpers' and the class block's XCD ids
-  // followed by the per-layer tables: slot[L], dil[L], rbase[L], qoff[2][L] (32-bit), then the fp32
-  // bias block
+  // followed by the per-layer tables: slot[L], depth[L], rbase[L], qoff[TP][2][L] (32-bit), then the
+  // fp32 bias block
 };
 struct HelperLds {
   union {
@@ -110,22 +115,26 @@ struct ClassLds {
   int local;                // the group's mode from the launch handshake
 };
 
-__host__ __device__ constexpr size_t chain_fixed_bytes() { return (sizeof(ChainLds) + 15) & ~size_t(15); }
-__host__ __device__ inline size_t dyn_bias_offset(int L) { return ((size_t)L * 20 + 15) & ~size_t(15); }
+template <int TP> __host__ __device__ constexpr size_t chain_fixed_bytes() {
+  return (sizeof(ChainLds<TP>) + 15) & ~size_t(15);
+}
+template <int TP> __host__ __device__ inline size_t dyn_bias_offset(int L) {
+  return ((size_t)L * (12 + 8 * TP) + 15) & ~size_t(15);
+}
 
 // Fragment stream geometry (1 KB fragments): chain wave A p, chain wave B p, helper (h, wave w)
 // skip stream, then the helpers' head slices.
 __host__ __device__ inline int len_a(int L) { return FA * L; }
-__host__ __device__ inline int len_b(int L) { return FB * L; }
+__host__ __device__ inline int len_b(int L, int TP) { return frags_b(TP) * L; }
 __host__ __device__ inline int helper_layers(int L) { return (L + NW - 1) / NW; }
 __host__ __device__ inline size_t base_a(int L, int p) { return (size_t)p * len_a(L); }
-__host__ __device__ inline size_t base_b(int L, int p) { return 4 * (size_t)len_a(L) + (size_t)p * len_b(L); }
-__host__ __device__ inline size_t base_h(int L, int h, int w) {
-  return 4 * (size_t)len_a(L) + 4 * (size_t)len_b(L) + (size_t)(NW * h + w) * helper_layers(L) * FS;
+__host__ __device__ inline size_t base_b(int L, int TP, int p) { return 4 * (size_t)len_a(L) + (size_t)p * len_b(L, TP); }
+__host__ __device__ inline size_t base_h(int L, int TP, int h, int w) {
+  return 4 * (size_t)len_a(L) + 4 * (size_t)len_b(L, TP) + (size_t)(NW * h + w) * helper_layers(L) * FS;
 }
-__host__ __device__ inline size_t base_w1(int L, int h) { return base_h(L, NHLP, 0) + (size_t)h * FW1; }
-__host__ __device__ inline size_t base_w2(int L, int h) { return base_w1(L, NHLP) + (size_t)h * FW2; }
-__host__ __device__ inline size_t frag_count(int L) { return base_w2(L, NHLP); }
+__host__ __device__ inline size_t base_w1(int L, int TP, int h) { return base_h(L, TP, NHLP, 0) + (size_t)h * FW1; }
+__host__ __device__ inline size_t base_w2(int L, int TP, int h) { return base_w1(L, TP, NHLP) + (size_t)h * FW2; }
+__host__ __device__ inline size_t frag_count(int L, int TP) { return base_w2(L, TP, NHLP); }
 
 // Exchange buffers: abort word, then per group: z^l words [L][512]; relu(skip sum) and relu(hidden)
 // words [16 streams][256] each; the step's samples (forced modes: step-done marks) [16] in a
@@ -155,12 +164,16 @@ __device__ __forceinline__ uint32_t step_tag(const StepArgs &a, long long step) 
 // ---------------------------------------------------------------------------
 // Chain block
 
+template <int TP>
 struct Ctx {
   const StepArgs *a;
-  ChainLds *s;
-  int *slot, *dil;
+  ChainLds<TP> *s;
+  int *slot, *depth;
   uint32_t *rbase;  // byte offset of each layer's queue in the queue region
-  uint32_t *qoff;   // [2][L]: byte offset of the rows of the current slot (0) and the next step's (1)
+  uint32_t *qoff;   // [TP][2][L]: byte offset of the rows of the current slot (0) and the next step's
+                    // (1), the oldest tap's (the slot the step's push replaces) first; at width 3 then
+                    // the newer tap's, dilation slots further on
+  const uint32_t *pqoff;  // the offsets this lane pops from: lanes 32..63 take the second tap at width 3
   char *ring;       // queue region
   uint32_t rowb;    // byte offset of this lane's 16-byte chunk of a queue row (wave B)
   const float *conv_b, *res_b, *emb_b;
@@ -176,14 +189,15 @@ struct Ctx {
   int L, w, p, lane, n, q, b0, nrows, blk;
 };
 
-__device__ __forceinline__ u32x4 frag_at(const Ctx &c, int pos) {
+template <int TP>
+__device__ __forceinline__ u32x4 frag_at(const Ctx<TP> &c, int pos) {
   return *(const u32x4 *)(c.fw + (size_t)pos * 1024 + c.wvoff);
 }
 // Slot `f` of ring W has just been consumed: load the stream's next fragment into it (the ring is a
 // FIFO over the cyclic stream).  The scheduling barriers keep the load after the MFMA that still
 // reads the slot's old contents.
-template <int D>
-__device__ __forceinline__ void refill(Ctx &c, u32x4 (&W)[D], int f) {
+template <int TP, int D>
+__device__ __forceinline__ void refill(Ctx<TP> &c, u32x4 (&W)[D], int f) {
   __builtin_amdgcn_sched_barrier(0);
   if (c.nxt == c.fend) c.nxt = c.fw;
   W[f] = *(const u32x4 *)(c.nxt + c.wvoff);
@@ -192,63 +206,76 @@ __device__ __forceinline__ void refill(Ctx &c, u32x4 (&W)[D], int f) {
 }
 
 // Queue rows moved by wave B of pair p: stream rows 4p..4p+3, lane l handling row 4p + (l%32)/8
-// and 16-byte chunk l%8 (lanes 32..63 mirror lanes 0..31 on loads and skip the stores).  The lane
-// that pushes a row chunk is the lane that later pops it, so program order keeps every pop after
-// the push it must see.
+// and 16-byte chunk l%8.  At width 2 lanes 32..63 mirror lanes 0..31 on loads and skip the stores; at
+// width 3 they pop the newer tap's rows.  The wave that pushes a row is the wave that later pops it,
+// so program order keeps every pop after the push it must see.
 // Pop of layer l for the step `ahead` (0 or 1) steps after the one the offset table describes.
-__device__ __forceinline__ u32x4 pop_issue(const Ctx &c, int l, int ahead) {
-  return *(const u32x4 *)(c.ring + (c.qoff[ahead * c.L + l] + c.rowb));
+template <int TP>
+__device__ __forceinline__ u32x4 pop_issue(const Ctx<TP> &c, int l, int ahead) {
+  return *(const u32x4 *)(c.ring + (c.pqoff[ahead * c.L + l] + c.rowb));
 }
 // The same load from an offset read from the table earlier.
-__device__ __forceinline__ u32x4 pop_issue_at(const Ctx &c, uint32_t off) {
+template <int TP>
+__device__ __forceinline__ u32x4 pop_issue_at(const Ctx<TP> &c, uint32_t off) {
   return *(const u32x4 *)(c.ring + (off + c.rowb));
 }
-__device__ __forceinline__ void pop_land(const Ctx &c, int buf, u32x4 v) {
-  if (c.lane < 32) {
-    const int r = 4 * c.p + (c.lane >> 3);
-    *(u32x4 *)(c.s->vbuf[buf] + r * PX + 8 * (c.lane & 7)) = v;
+template <int TP>
+__device__ __forceinline__ void pop_land(const Ctx<TP> &c, int buf, u32x4 v) {
+  if (TP == 2 || c.lane < 32) {
+    const int r = 4 * c.p + ((c.lane & 31) >> 3);
+    *(u32x4 *)(c.s->vbuf[buf][TP == 2 && c.lane < 32 ? 1 : 0] + r * PX + 8 * (c.lane & 7)) = v;
   }
 }
 // Between the layer's barriers: z^l of stream rows 4p..4p+3 to the helpers (lane l covers row
 // 4p + l/16, channels 4(l%16)..+3, as two words of two bf16 each; word index = row * 32 +
 // channel / 2), and the push of layer l (its input x^l replaces the slot popped for this step).
 // All LDS reads are issued before either store, so the wave waits for LDS once.
-__device__ __forceinline__ void publish_and_push(const Ctx &c, int l, uint32_t tag) {
+template <int TP>
+__device__ __forceinline__ void publish_and_push(const Ctx<TP> &c, int l, int par, uint32_t tag) {
   const int rz = 4 * c.p + (c.lane >> 4), cp = 2 * (c.lane & 15);
   const int rx = 4 * c.p + ((c.lane & 31) >> 3);
-  const u32x2 zv = *(const u32x2 *)(c.s->zbuf[l & 1] + rz * PX + 2 * cp);
-  const u32x4 xv = *(const u32x4 *)(c.s->xbuf[l & 1] + rx * PX + 8 * (c.lane & 7));
+  const u32x2 zv = *(const u32x2 *)(c.s->zbuf[par] + rz * PX + 2 * cp);
+  const u32x4 xv = *(const u32x4 *)(c.s->xbuf[par] + rx * PX + 8 * (c.lane & 7));
   const uint32_t off = c.qoff[l];
   __builtin_amdgcn_sched_barrier(0);
   put_words2(c.zp + (size_t)l * ZWORDS + rz * (R / 2) + cp, zv.x, zv.y, tag, c.local);
   if (c.lane < 32) *(u32x4 *)(c.ring + (off + c.rowb)) = xv;
 }
 
-// W_r v + b of layer ln from the popped rows in vbuf[vb3] and ring slots f0..f0+3 (tanh tile p
-// k-steps 0,1, sigmoid tile p k-steps 0,1), into pbuf[par].
-template <int D>
-__device__ __forceinline__ void recurrent_half(const Ctx &c, int ln, int vb3, int par, const u32x4 (&W)[D], int f0) {
-  ChainLds &s = *c.s;
-  const uint16_t *vb = s.vbuf[vb3] + c.n * PX;
+// W_r v + b of layer ln from the popped rows in vbuf[vb3] and ring slots f0.. (per tap: tanh tile p
+// k-steps 0,1, sigmoid tile p k-steps 0,1; the newest tap first), into pbuf[par].
+template <int TP, int D>
+__device__ __forceinline__ void recurrent_half(const Ctx<TP> &c, int ln, int vb3, int par, const u32x4 (&W)[D], int f0) {
+  ChainLds<TP> &s = *c.s;
   const float *cb = c.conv_b + ln * 2 * R;
-  // the biases (C operands) first, so the two products interleave (the LDS reads land in order)
+  // the biases (C operands) first, so the products interleave (the LDS reads land in order)
   f32x4 pt = ldsf4(cb + 16 * c.p + 4 * c.q), pg = ldsf4(cb + R + 16 * c.p + 4 * c.q);
-  const u32x4 bv0 = lds16(vb + 8 * c.q), bv1 = lds16(vb + 32 + 8 * c.q);
-  // the four LDS reads in flight together (one wait), not one round trip per product
+  u32x4 bv[TP][2];
+#pragma unroll
+  for (int k = 0; k < TP; ++k) {
+    const uint16_t *vb = s.vbuf[vb3][k] + c.n * PX;
+    bv[k][0] = lds16(vb + 8 * c.q);
+    bv[k][1] = lds16(vb + 32 + 8 * c.q);
+  }
+  // all LDS reads in flight together (one wait), not one round trip per product
   __builtin_amdgcn_sched_barrier(0);
-  pt = mfma(W[f0 + 0], bv0, pt);
-  pg = mfma(W[f0 + 2], bv0, pg);
-  pt = mfma(W[f0 + 1], bv1, pt);
-  pg = mfma(W[f0 + 3], bv1, pg);
+#pragma unroll
+  for (int k = 0; k < TP; ++k)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      pt = mfma(W[f0 + 4 * k + ks], bv[k][ks], pt);
+      pg = mfma(W[f0 + 4 * k + 2 + ks], bv[k][ks], pg);
+    }
   stf4(s.pbuf[par][c.p][0] + c.n * PP + 4 * c.q, pt);
   stf4(s.pbuf[par][c.p][1] + c.n * PP + 4 * c.q, pg);
 }
 
 // Forced inputs of steps [s0, s0 + KCH) into LDS (forced modes; every thread): the input that
 // follows each step.
-__device__ __forceinline__ void stage_inputs(const Ctx &c, long long s0) {
+template <int TP>
+__device__ __forceinline__ void stage_inputs(const Ctx<TP> &c, long long s0) {
   const StepArgs &a = *c.a;
-  ChainLds &s = *c.s;
+  ChainLds<TP> &s = *c.s;
   static_assert((ROWS * KCH) % NT == 0, "the chunk divides evenly over the threads");
 #pragma unroll
   for (int e = 0; e < ROWS * KCH / NT; ++e) {
@@ -261,12 +288,12 @@ __device__ __forceinline__ void stage_inputs(const Ctx &c, long long s0) {
   }
 }
 
-// Layer l on wave A, ring slots PHS..PHS+5 (x-half of tanh/sigmoid tile p, residual tile p).
-template <int PHS>
-__device__ __forceinline__ void a_layer(Ctx &c, int l, u32x4 (&W)[DA], f32x4 &xres) {
-  ChainLds &s = *c.s;
+// Layer l on wave A, ring slots PHS..PHS+5 (x-half of tanh/sigmoid tile p, residual tile p); par: the
+// parity of the running layer count.
+template <int PHS, int TP>
+__device__ __forceinline__ void a_layer(Ctx<TP> &c, int l, int par, u32x4 (&W)[DA], f32x4 &xres) {
+  ChainLds<TP> &s = *c.s;
   const int n = c.n, q = c.q, p = c.p;
-  const int par = l & 1;
   // W_r v + b first: the LDS reads land in order, and with both C operands in before the layer input
   // the tanh and sigmoid products interleave instead of running as two dependent pairs
   f32x4 af = ldsf4(s.pbuf[par][p][0] + n * PP + 4 * q);
@@ -288,7 +315,7 @@ __device__ __forceinline__ void a_layer(Ctx &c, int l, u32x4 (&W)[DA], f32x4 &xr
     const int ch = 16 * p + 4 * q;
     const u32x2 raw = *(const u32x2 *)(e + ch);
     xres = f32x4{bf_lo(raw.x) + eb[ch], bf_hi(raw.x) + eb[ch + 1], bf_lo(raw.y) + eb[ch + 2], bf_hi(raw.y) + eb[ch + 3]};
-    lds8(s.xbuf[0] + n * PX + ch, pack4(xres));
+    lds8(s.xbuf[par] + n * PX + ch, pack4(xres));
   } else {
     const uint16_t *xb = s.xbuf[par] + n * PX;
     bx0 = lds16(xb + 8 * q);
@@ -318,30 +345,37 @@ __device__ __forceinline__ void a_layer(Ctx &c, int l, u32x4 (&W)[DA], f32x4 &xr
   __syncthreads();
 }
 
-// Layer l on wave B, ring slots PBS..PBS+3 (W_r of the next layer), pop registers rotated by
-// G6 = l mod 6 (L is a multiple of 6, so this is also the global layer index mod 6): the pop of
-// global layer index g sits in P[g mod 6] from its issue, five layers ahead of landing, until it
-// lands in vbuf[g mod 3] before the first barrier of layer g - 3, four block barriers before its
-// product.
-template <int PBS, int G6>
-__device__ __forceinline__ void b_layer(Ctx &c, int l, u32x4 (&W)[DB], u32x4 (&P)[6], uint32_t tag) {
+// Layer l on wave B, ring slots PBS.. (W_r of the next layer), pop registers rotated by G6, the
+// running layer count mod 6: the pop of running layer index g sits in P[g mod 6] from its issue, five
+// layers ahead of landing, until it lands in vbuf[g mod 3] before the first barrier of layer g - 3,
+// four block barriers before its product.  par, v3: the running layer count mod 2 and mod 3.
+template <int PBS, int G6, int TP>
+__device__ __forceinline__ void b_layer(Ctx<TP> &c, int l, int par, int v3, u32x4 (&W)[DB], u32x4 (&P)[6], uint32_t tag) {
   const int L = c.L;
   const int ln = l + 1 < L ? l + 1 : 0;
   // queue offset of the pop issued below, read with the product's LDS reads
   const int j = l + 8 < L ? l + 8 : l + 8 - L;
-  const uint32_t joff = c.qoff[(l + 8 < L ? 0 : L) + j];
-  recurrent_half(c, ln, (G6 + 1) % 3, (l + 1) & 1, W, PBS);
+  const uint32_t joff = c.pqoff[(l + 8 < L ? 0 : L) + j];
+  recurrent_half<TP>(c, ln, v3 == 2 ? 0 : v3 + 1, par ^ 1, W, PBS);
 #pragma unroll
-  for (int f = 0; f < FB; ++f) refill(c, W, PBS + f);
+  for (int f = 0; f < frags_b(TP); ++f) refill(c, W, PBS + f);
   // the pop of layer l + 3 into LDS (its buffer was last read before the previous layer's first
   // barrier) and the pop of layer l + 8 issued
-  pop_land(c, G6 % 3, P[(G6 + 3) % 6]);
+  pop_land(c, v3, P[(G6 + 3) % 6]);
   P[(G6 + 2) % 6] = pop_issue_at(c, joff);
   __syncthreads();
   // while wave A runs the residual product: the layer's gate output to the helpers and its input
   // into its queue
-  publish_and_push(c, l, tag);
+  publish_and_push(c, l, par, tag);
   __syncthreads();
+}
+
+// Queue slot of tap k when the oldest tap's is `slot` (width 3: the newer tap's row was pushed one
+// dilation, half the queue, later).
+__device__ __forceinline__ int tap_slot(int slot, int depth, int k) {
+  if (k == 0) return slot;
+  const int s = slot + depth / 2;
+  return s >= depth ? s - depth : s;
 }
 
 // End of step `step` on every chain wave: the slot advance, then the class block's word for each
@@ -349,8 +383,9 @@ __device__ __forceinline__ void b_layer(Ctx &c, int l, u32x4 (&W)[DB], u32x4 (&P
 // where the next input is the forced one).  Waiting for it in every mode also keeps the chain from
 // rewriting the z^l words before the helpers have read this step's.  One barrier (two when forced
 // inputs are staged).
-__device__ __forceinline__ void finish_step(Ctx &c, long long step) {
-  ChainLds &s = *c.s;
+template <int TP>
+__device__ __forceinline__ void finish_step(Ctx<TP> &c, long long step) {
+  ChainLds<TP> &s = *c.s;
   const StepArgs &a = *c.a;
   const int tid = threadIdx.x;
   if (a.mode != MODE_GENERATE && step % KCH == 0) {
@@ -359,11 +394,15 @@ __device__ __forceinline__ void finish_step(Ctx &c, long long step) {
   }
   // no wave reads the offset table between the last layer's push and the next step's first layer
   for (int l = tid; l < c.L; l += NT) {
-    const int nx = c.slot[l] + 1 == c.dil[l] ? 0 : c.slot[l] + 1;
-    const int nn = nx + 1 == c.dil[l] ? 0 : nx + 1;
+    const int nx = c.slot[l] + 1 == c.depth[l] ? 0 : c.slot[l] + 1;
+    const int nn = nx + 1 == c.depth[l] ? 0 : nx + 1;
     c.slot[l] = nx;
-    c.qoff[l] = c.qoff[c.L + l];
-    c.qoff[c.L + l] = c.rbase[l] + (uint32_t)nn * (uint32_t)(a.bmax * R * 2);
+#pragma unroll
+    for (int k = 0; k < TP; ++k) {
+      uint32_t *qo = c.qoff + 2 * k * c.L;
+      qo[l] = qo[c.L + l];
+      qo[c.L + l] = c.rbase[l] + (uint32_t)tap_slot(nn, c.depth[l], k) * (uint32_t)(a.bmax * R * 2);
+    }
   }
   if (tid < ROWS) {
     uint32_t v[1];
@@ -380,14 +419,34 @@ __device__ __forceinline__ void finish_step(Ctx &c, long long step) {
 // Launch handshake, second half (after the barrier that follows wave A's poll of the XCD ids):
 // whether the whole group shares this block's XCD, which decides the scope of every word the block
 // stores; thread 0 publishes it to the group.
-__device__ __forceinline__ void set_mode(Ctx &c) {
+template <int TP>
+__device__ __forceinline__ void set_mode(Ctx<TP> &c) {
   bool local = true;
   for (int h = 0; h < NHLP + 1; ++h) local = local && (uint32_t)c.s->ins[ROWS + h] == xcd_id();
   c.local = local;
   if (threadIdx.x == 0) put_word(comm_hs(c.a->sp_comm, c.L, c.blk) + HSLOT * (NHLP + 1), local ? 1u : 0u, c.mark, false);
 }
 
-__device__ __forceinline__ void a_role(Ctx &c) {
+// Any layer count from 9 on and both widths run on these kernels (before, layer counts other than
+// multiples of 6 and width 3 took the single-block kernel): 20 layers at 100 streams 30.5 -> 13.9 us
+// per step, 14 layers of width 3 at 256 streams 27.1 -> 13.1.
+// The layer loops run six layers at a time, with every ring slot a fixed register, and then the
+// REM layers that are left (L mod 6, and 7 for a remainder of 1: with a tail of one layer the compiler
+// folds the tail into the loop's first layer and spills); after such a step the rings stand REM layers further on, and
+// the registers are rotated back so that the next step starts at slot 0 again (moves, and a wait for
+// loads that the end of the step gives time to land anyway).  Buffers in LDS go by the running layer
+// count instead: its value mod 2 and mod 3 at layer 0 of the step.
+template <int N, int D>
+__device__ __forceinline__ void rotate_ring(u32x4 (&W)[D]) {
+  u32x4 t[D];
+#pragma unroll
+  for (int f = 0; f < D; ++f) t[f] = W[(f + N) % D];
+#pragma unroll
+  for (int f = 0; f < D; ++f) W[f] = t[f];
+}
+
+template <int TP, int REM>
+__device__ __forceinline__ void a_role(Ctx<TP> &c) {
   const int L = c.L;
   c.fw = (const char *)c.a->mf_frags + base_a(L, c.p) * 1024;
   c.fend = c.fw + (size_t)len_a(L) * 1024;
@@ -406,23 +465,39 @@ __device__ __forceinline__ void a_role(Ctx &c) {
   __syncthreads();  // the popped rows of layers 0..2 and the XCD ids are in LDS
   set_mode(c);
   __syncthreads();  // W_r v + b of layer 0 is in LDS
+  int par = 0;
   for (long long step = 0; step < c.a->n_steps; ++step) {
-    for (int l = 0; l < L; l += 6) {
-      a_layer<0>(c, l, W, xres);
-      a_layer<FA>(c, l + 1, W, xres);
-      a_layer<2 * FA>(c, l + 2, W, xres);
-      a_layer<0>(c, l + 3, W, xres);
-      a_layer<FA>(c, l + 4, W, xres);
-      a_layer<2 * FA>(c, l + 5, W, xres);
+    int l = 0;
+    for (; l + REM < L; l += 6) {
+      a_layer<0>(c, l, par, W, xres);
+      a_layer<FA>(c, l + 1, par ^ 1, W, xres);
+      a_layer<2 * FA>(c, l + 2, par, W, xres);
+      a_layer<0>(c, l + 3, par ^ 1, W, xres);
+      a_layer<FA>(c, l + 4, par, W, xres);
+      a_layer<2 * FA>(c, l + 5, par ^ 1, W, xres);
+    }
+    if constexpr (REM > 0) a_layer<0>(c, l, par, W, xres);
+    if constexpr (REM > 1) a_layer<FA>(c, l + 1, par ^ 1, W, xres);
+    if constexpr (REM > 2) a_layer<2 * FA>(c, l + 2, par, W, xres);
+    if constexpr (REM > 3) a_layer<0>(c, l + 3, par ^ 1, W, xres);
+    if constexpr (REM > 4) a_layer<FA>(c, l + 4, par, W, xres);
+    if constexpr (REM > 5) {
+      a_layer<2 * FA>(c, l + 5, par ^ 1, W, xres);
+      a_layer<0>(c, l + 6, par, W, xres);
     }
     finish_step(c, step);
+    if constexpr (REM % 3 != 0) rotate_ring<(REM % 3) * FA>(W);
+    if constexpr (REM % 2 != 0) par ^= 1;
   }
 }
 
-__device__ __forceinline__ void b_role(Ctx &c) {
+template <int TP, int REM>
+__device__ __forceinline__ void b_role(Ctx<TP> &c) {
+  constexpr int FB = frags_b(TP);
+  constexpr int NB = DB / FB;  // layers the weight ring holds
   const int L = c.L;
-  c.fw = (const char *)c.a->mf_frags + base_b(L, c.p) * 1024;
-  c.fend = c.fw + (size_t)len_b(L) * 1024;
+  c.fw = (const char *)c.a->mf_frags + base_b(L, TP, c.p) * 1024;
+  c.fend = c.fw + (size_t)len_b(L, TP) * 1024;
   u32x4 W[DB], P[6];
   // layers 0..2 of step 0 land now and layers 3..7 are issued; layer 0's W_r v + b comes from its
   // stream stage L - 1 (all of these loads in flight together)
@@ -436,40 +511,58 @@ __device__ __forceinline__ void b_role(Ctx &c) {
   pop_land(c, 2, v2);
   __syncthreads();  // the popped rows of layers 0..2 and the XCD ids are in LDS
   set_mode(c);
-  recurrent_half(c, 0, 0, 0, W, 0);
+  recurrent_half<TP>(c, 0, 0, 0, W, 0);
 #pragma unroll
   for (int f = 0; f < DB; ++f) W[f] = frag_at(c, f);
   c.nxt = c.fw + DB * 1024;
   __syncthreads();
+  int par = 0, v3 = 0;  // the running layer count mod 2 and mod 3 at layer 0 of the step
   for (long long step = 0; step < c.a->n_steps; ++step) {
     const uint32_t tag = step_tag(*c.a, step);
-    for (int l = 0; l < L; l += 6) {
-      b_layer<0, 0>(c, l, W, P, tag);
-      b_layer<FB, 1>(c, l + 1, W, P, tag);
-      b_layer<2 * FB, 2>(c, l + 2, W, P, tag);
-      b_layer<3 * FB, 3>(c, l + 3, W, P, tag);
-      b_layer<4 * FB, 4>(c, l + 4, W, P, tag);
-      b_layer<5 * FB, 5>(c, l + 5, W, P, tag);
+    const int v4 = v3 == 2 ? 0 : v3 + 1, v5 = v4 == 2 ? 0 : v4 + 1;
+    int l = 0;
+    for (; l + REM < L; l += 6) {
+      b_layer<0, 0>(c, l, par, v3, W, P, tag);
+      b_layer<(1 % NB) * FB, 1>(c, l + 1, par ^ 1, v4, W, P, tag);
+      b_layer<(2 % NB) * FB, 2>(c, l + 2, par, v5, W, P, tag);
+      b_layer<(3 % NB) * FB, 3>(c, l + 3, par ^ 1, v3, W, P, tag);
+      b_layer<(4 % NB) * FB, 4>(c, l + 4, par, v4, W, P, tag);
+      b_layer<(5 % NB) * FB, 5>(c, l + 5, par ^ 1, v5, W, P, tag);
+    }
+    if constexpr (REM > 0) b_layer<0, 0>(c, l, par, v3, W, P, tag);
+    if constexpr (REM > 1) b_layer<(1 % NB) * FB, 1>(c, l + 1, par ^ 1, v4, W, P, tag);
+    if constexpr (REM > 2) b_layer<(2 % NB) * FB, 2>(c, l + 2, par, v5, W, P, tag);
+    if constexpr (REM > 3) b_layer<(3 % NB) * FB, 3>(c, l + 3, par ^ 1, v3, W, P, tag);
+    if constexpr (REM > 4) b_layer<(4 % NB) * FB, 4>(c, l + 4, par, v4, W, P, tag);
+    if constexpr (REM > 5) {
+      b_layer<(5 % NB) * FB, 5>(c, l + 5, par ^ 1, v5, W, P, tag);
+      b_layer<0, 0>(c, l + 6, par, v3, W, P, tag);
     }
     finish_step(c, step);
+    if constexpr (REM % NB != 0) rotate_ring<(REM % NB) * FB>(W);
+    if constexpr (REM != 0) rotate_ring<REM % 6>(P);
+    if constexpr (REM % 2 != 0) par ^= 1;
+    if constexpr (REM % 3 == 1) v3 = v4;
+    if constexpr (REM % 3 == 2) v3 = v5;
   }
 }
 
+template <int TP, int REM>
 __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, int blk) {
-  ChainLds &s = *(ChainLds *)lds_raw;
+  ChainLds<TP> &s = *(ChainLds<TP> *)lds_raw;
   const int tid = threadIdx.x, L = a.L;
-  char *dyn = lds_raw + chain_fixed_bytes();
+  char *dyn = lds_raw + chain_fixed_bytes<TP>();
   int *slot = (int *)dyn;
-  int *dil = slot + L;
-  uint32_t *rbase = (uint32_t *)(dil + L);
+  int *depth = slot + L;
+  uint32_t *rbase = (uint32_t *)(depth + L);
   uint32_t *qoff = rbase + L;
-  float *bias = (float *)(dyn + dyn_bias_offset(L));  // conv_b [L][2R], res_b [L][R], emb_b [R]
+  float *bias = (float *)(dyn + dyn_bias_offset<TP>(L));  // conv_b [L][2R], res_b [L][R], emb_b [R]
 
-  Ctx c;
+  Ctx<TP> c;
   c.a = &a;
   c.s = &s;
   c.slot = slot;
-  c.dil = dil;
+  c.depth = depth;
   c.rbase = rbase;
   c.qoff = qoff;
   c.ring = (char *)a.ring;
@@ -486,6 +579,7 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
   c.b0 = blk * ROWS;
   c.nrows = min(ROWS, a.batch - c.b0);
   c.wvoff = 16 * c.lane;
+  c.pqoff = qoff + (TP == 2 && c.lane >= 32 ? 2 * L : 0);
   c.rowb = (uint32_t)(((c.b0 + 4 * c.p + ((c.lane & 31) >> 3)) * R + 8 * (c.lane & 7)) * 2);
   c.zp = comm_z(a.sp_comm, L, blk);
   c.smp = comm_smp(a.sp_comm, L, blk);
@@ -513,11 +607,11 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
     for (int k = 0; k < NB4; ++k)
       if (tid + k * NT < nb4) bv[k] = bsrc[tid + k * NT];
     const float eb = tid < R ? a.mf_bias[L * 3 * R + S + H + Q + tid] : 0.f;
-    long long roff = 0;  // the layer's queue offset and dilation (first batch of layers)
-    int ldil = 1;
+    long long roff = 0;  // the layer's queue offset and depth (first batch of layers)
+    int ldep = 1;
     if (tid < L) {
       roff = a.layers[tid].ring_off;
-      ldil = a.layers[tid].dil;
+      ldep = a.layers[tid].depth;
     }
     int in0 = 0;
     if (tid < c.nrows) in0 = a.mode == MODE_TEACHER ? a.inputs[(long long)(c.b0 + tid) * a.n_steps] : a.last[c.b0 + tid];
@@ -532,14 +626,17 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
     for (int l = tid; l < L; l += NT) {
       if (l >= NT) {  // more than NT layers
         roff = a.layers[l].ring_off;
-        ldil = a.layers[l].dil;
+        ldep = a.layers[l].depth;
       }
-      const int s0 = (int)(a.t0 % (long long)ldil), s1 = s0 + 1 == ldil ? 0 : s0 + 1;
+      const int s0 = (int)(a.t0 % (long long)ldep), s1 = s0 + 1 == ldep ? 0 : s0 + 1;
       rbase[l] = (uint32_t)(roff * 2);
-      dil[l] = ldil;
+      depth[l] = ldep;
       slot[l] = s0;
-      qoff[l] = rbase[l] + (uint32_t)s0 * slot_bytes;
-      qoff[L + l] = rbase[l] + (uint32_t)s1 * slot_bytes;
+#pragma unroll
+      for (int k = 0; k < TP; ++k) {
+        qoff[2 * k * L + l] = rbase[l] + (uint32_t)tap_slot(s0, ldep, k) * slot_bytes;
+        qoff[(2 * k + 1) * L + l] = rbase[l] + (uint32_t)tap_slot(s1, ldep, k) * slot_bytes;
+      }
     }
     if (tid < ROWS) s.ins[tid] = in0;
   }
@@ -547,8 +644,8 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
   // The launch handshake (the helpers' and the class block's XCD ids, then the group's mode) runs
   // inside the roles' first loads: wave A polls the ids while its weight loads and wave B's first
   // pops are in flight.
-  if (c.w < 4) a_role(c);
-  else b_role(c);
+  if (c.w < 4) a_role<TP, REM>(c);
+  else b_role<TP, REM>(c);
   if (a.mode != MODE_TEACHER && tid < c.nrows) a.last[c.b0 + tid] = s.ins[tid];
 }
 
@@ -707,6 +804,7 @@ __device__ __forceinline__ void helper_steps(const HelperCtx &c, const u32x4 (&h
   }
 }
 
+template <int TP>
 __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, int blk, int h) {
   HelperLds &s = *(HelperLds *)lds_raw;
   const int tid = threadIdx.x, L = a.L;
@@ -727,7 +825,7 @@ __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, i
   // for the whole launch
   u32x4 hw1[8];
   {
-    const u32x4 *w1 = (const u32x4 *)((const char *)a.mf_frags + base_w1(L, h) * 1024);
+    const u32x4 *w1 = (const u32x4 *)((const char *)a.mf_frags + base_w1(L, TP, h) * 1024);
 #pragma unroll
     for (int i = 0; i < 8; ++i) hw1[i] = w1[((w & 3) * (S / 32) + 8 * (w >> 2) + i) * 64 + lane];
   }
@@ -741,7 +839,7 @@ __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, i
   HelperCtx c;
   c.a = &a;
   c.s = &s;
-  c.fw = (const char *)a.mf_frags + base_h(L, h, w) * 1024;
+  c.fw = (const char *)a.mf_frags + base_h(L, TP, h, w) * 1024;
   c.zb = comm_z(a.sp_comm, L, blk);
   c.sw = comm_s(a.sp_comm, L, blk);
   c.hw = comm_hid(a.sp_comm, L, blk);
@@ -767,6 +865,7 @@ __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, i
 // generation draws their samples (written out and returned to the chain block), forced modes write
 // their logits out and return a step-done mark.
 
+template <int TP>
 __device__ __forceinline__ void class_block(const StepArgs &a, char *lds_raw, int blk) {
   ClassLds &s = *(ClassLds *)lds_raw;
   const int tid = threadIdx.x, L = a.L;
@@ -783,7 +882,7 @@ __device__ __forceinline__ void class_block(const StepArgs &a, char *lds_raw, in
   // output 1x1 fragments of classes 32w .. 32w + 31: tile j, k-step ks at j * 16 + ks of slice w
   u32x4 wo[2][H / 32];
   {
-    const u32x4 *src = (const u32x4 *)((const char *)a.mf_frags + base_w2(L, w) * 1024);
+    const u32x4 *src = (const u32x4 *)((const char *)a.mf_frags + base_w2(L, TP, w) * 1024);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -866,41 +965,74 @@ __device__ __forceinline__ void class_block(const StepArgs &a, char *lds_raw, in
   }
 }
 
+// Place of a block in the launch.  Blocks go to the XCDs round-robin, so members 8 blocks apart share
+// an XCD and its L2.  Up to 24 groups the launch is laid out as rows of 8 groups, member m of groups
+// 8k .. 8k + 7 in blocks (10 k + 9 - m) 8 .. + 7 (chain blocks last: 18.48 us per step on the benchmark
+// model, 18.59 with them first); the places of the groups that a ragged last row lacks exit at once.  So every group sits on one XCD whatever their number is, and a row is dispatched
+// before the next: launches that share the device each hold at most one unfinished row (80 places)
+// waiting for room.  With the helpers of every group after all the chain blocks, a number of groups
+// that is not a multiple of 8 put each group's blocks on several XCDs (device-scope words, 2x the
+// step), and two launches could fill the device with blocks that wait for members that found no room.
+// More than 24 groups leave no XCD with room for a fourth row (32 compute units): members nb apart.
+constexpr int GB = 2 + kSpHelpers;  // blocks of a group: chain block, helpers, class block
+__host__ __device__ inline bool rows_of_groups(int nb) { return nb <= 24; }
+__host__ __device__ inline int grid_blocks(int nb) { return rows_of_groups(nb) ? (nb + 7) / 8 * 8 * GB : nb * GB; }
+
+template <int TP, int REM>
 __global__ void __launch_bounds__(NT) split_step_kernel(StepArgs a) {
   extern __shared__ float4 lds_raw[];
   const int nb = a.sp_nb;
-  // helper h of group b sits at nb + h nb + b and its class block at (1 + NHLP) nb + b: with nb a
-  // multiple of 8, all on the XCD of chain block b
-  const int e = (int)blockIdx.x - nb;
-  if (e < 0) {
-    chain_block(a, (char *)lds_raw, blockIdx.x);
-  } else if (e < NHLP * nb) {
-    helper_block(a, (char *)lds_raw, e % nb, e / nb);
+  int m, grp;
+  if (rows_of_groups(nb)) {
+    const int row = (int)blockIdx.x / (8 * GB), at = (int)blockIdx.x % (8 * GB);
+    m = GB - 1 - at / 8;
+    grp = 8 * row + at % 8;
+    if (grp >= nb) return;
   } else {
-    class_block(a, (char *)lds_raw, e - NHLP * nb);
+    m = (int)blockIdx.x / nb;
+    grp = (int)blockIdx.x % nb;
+  }
+  if (m == 0) chain_block<TP, REM>(a, (char *)lds_raw, grp);
+  else if (m <= NHLP) helper_block<TP>(a, (char *)lds_raw, grp, m - 1);
+  else class_block<TP>(a, (char *)lds_raw, grp);
+}
+
+// The instance of a filter width (TP = w - 1) and layer count.
+typedef void (*StepKernel)(StepArgs);
+template <int TP>
+static StepKernel kernel_of(int L) {
+  switch (L % 6) {
+    case 0: return split_step_kernel<TP, 0>;
+    case 1: return split_step_kernel<TP, 7>;
+    case 2: return split_step_kernel<TP, 2>;
+    case 3: return split_step_kernel<TP, 3>;
+    case 4: return split_step_kernel<TP, 4>;
+    default: return split_step_kernel<TP, 5>;
   }
 }
+static StepKernel kernel_of(int L, int w) { return w == 3 ? kernel_of<2>(L) : kernel_of<1>(L); }
 
 // ---------------------------------------------------------------------------
 // Repacking into the fragment streams.  Fragment (tile t, k-step ks) of a matrix M[out][k] gives
 // lane l the 8 values M[16t + l%16][32ks + 8(l/16) + j].
 
-__device__ __forceinline__ uint16_t conv_elem(const uint16_t *conv, int o, int k) {
-  return conv[(o * R + (k % R)) * 2 + (k >= R ? 1 : 0)];
+// Conv weight of output o, input channel k, tap `tap` of w.
+__device__ __forceinline__ uint16_t conv_elem(const uint16_t *conv, int o, int k, int tap, int w) {
+  return conv[(o * R + k) * w + tap];
 }
 __device__ __forceinline__ uint4 pack8(const uint16_t *v) {
   return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
 }
 
-// Layer l: A wave p stream position 6l + f (f 0..3: x-half of tanh tile p k-steps 2,3 and sigmoid
-// tile p k-steps 2,3; f 4,5: residual tile p k-steps 0,1); B wave p stream position 4 ((l-1) mod L)
-// + f (v-half of tanh tile p k-steps 0,1, sigmoid tile p k-steps 0,1); helper (h, l % 8) position
-// 8 (l / 8) + 2j + ks (skip tile 4h + j, k-step ks).
-constexpr int LAYER_FRAGS = 4 * FA + 4 * FB + NHLP * FS;
+// Layer l: A wave p stream position 6l + f (f 0..3: current-input tap of tanh tile p k-steps 0,1 and
+// sigmoid tile p k-steps 0,1; f 4,5: residual tile p k-steps 0,1); B wave p stream position
+// 4 TP ((l-1) mod L) + 4 k + f (popped tap k, the newest first: tanh tile p k-steps 0,1, sigmoid tile p
+// k-steps 0,1); helper (h, l % 8) position 8 (l / 8) + 2j + ks (skip tile 4h + j, k-step ks).
 __global__ void repack_layer_kernel(const uint16_t *conv, const uint16_t *res, const uint16_t *skip, int l, int L,
-                                    uint4 *frags) {
+                                    int TP, uint4 *frags) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= LAYER_FRAGS * 64) return;
+  const int FB = frags_b(TP), w = TP + 1;
+  if (e >= (4 * FA + 4 * FB + NHLP * FS) * 64) return;
   const int lane = e % 64, m = lane % 16, kq = 8 * (lane / 16);
   int fi = e / 64;
   uint16_t v[8];
@@ -908,18 +1040,19 @@ __global__ void repack_layer_kernel(const uint16_t *conv, const uint16_t *res, c
   if (fi < 4 * FA) {
     const int p = fi / FA, f = fi % FA;
     for (int j = 0; j < 8; ++j)
-      v[j] = f < 4 ? conv_elem(conv, (f < 2 ? 0 : R) + 16 * p + m, R + 32 * (f & 1) + kq + j)
+      v[j] = f < 4 ? conv_elem(conv, (f < 2 ? 0 : R) + 16 * p + m, 32 * (f & 1) + kq + j, w - 1, w)
                    : res[(16 * p + m) * R + 32 * (f - 4) + kq + j];
     dst = base_a(L, p) + (size_t)FA * l + f;
   } else if ((fi -= 4 * FA) < 4 * FB) {
-    const int p = fi / FB, f = fi % FB;
-    for (int j = 0; j < 8; ++j) v[j] = conv_elem(conv, (f < 2 ? 0 : R) + 16 * p + m, 32 * (f & 1) + kq + j);
-    dst = base_b(L, p) + (size_t)FB * ((l + L - 1) % L) + f;
+    const int p = fi / FB, f = fi % FB, k = f / 4;
+    for (int j = 0; j < 8; ++j)
+      v[j] = conv_elem(conv, ((f & 2) ? R : 0) + 16 * p + m, 32 * (f & 1) + kq + j, w - 2 - k, w);
+    dst = base_b(L, TP, p) + (size_t)FB * ((l + L - 1) % L) + f;
   } else {
     fi -= 4 * FB;
     const int h = fi / FS, f = fi % FS, t = (SL / 16) * h + f / 2, ks = f % 2;
     for (int j = 0; j < 8; ++j) v[j] = skip[(16 * t + m) * R + 32 * ks + kq + j];
-    dst = base_h(L, h, l % NW) + (size_t)FS * (l / NW) + f;
+    dst = base_h(L, TP, h, l % NW) + (size_t)FS * (l / NW) + f;
   }
   frags[dst * 64 + lane] = pack8(v);
 }
@@ -927,7 +1060,7 @@ __global__ void repack_layer_kernel(const uint16_t *conv, const uint16_t *res, c
 // Head slices h: first 1x1 fragment (tile j, k-step ks) of rows 64h + 16j.. at j * 16 + ks (helper
 // h); output 1x1 fragment (tile j, k-step ks) of classes 32h + 16j.. at j * 16 + ks (class block
 // wave h).
-__global__ void repack_head_kernel(const uint16_t *head, const uint16_t *out, int L, uint4 *frags) {
+__global__ void repack_head_kernel(const uint16_t *head, const uint16_t *out, int L, int TP, uint4 *frags) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= NHLP * (FW1 + FW2) * 64) return;
   const int lane = e % 64, m = lane % 16, kq = 8 * (lane / 16);
@@ -937,11 +1070,11 @@ __global__ void repack_head_kernel(const uint16_t *head, const uint16_t *out, in
   if (f < FW1) {
     const int j = f / (S / 32), ks = f % (S / 32);
     for (int i = 0; i < 8; ++i) v[i] = head[(h * HL + 16 * j + m) * S + 32 * ks + kq + i];
-    dst = base_w1(L, h) + f;
+    dst = base_w1(L, TP, h) + f;
   } else {
     const int g = f - FW1, j = g / (H / 32), ks = g % (H / 32);
     for (int i = 0; i < 8; ++i) v[i] = out[(h * QL + 16 * j + m) * H + 32 * ks + kq + i];
-    dst = base_w2(L, h) + g;
+    dst = base_w2(L, TP, h) + g;
   }
   frags[dst * 64 + lane] = pack8(v);
 }
@@ -971,49 +1104,50 @@ hipError_t split_static_scratch(void **ptr) {
   return hipSuccess;
 }
 
-size_t split_frag_bytes(int L) { return sp::frag_count(L) * 1024; }
+size_t split_frag_bytes(int L, int w) { return sp::frag_count(L, w - 1) * 1024; }
 
 size_t split_comm_bytes(int L, int nb) { return 256 + (size_t)nb * sp::group_words(L) * sizeof(unsigned long long); }
 
-size_t split_lds_bytes(int L) {
-  const size_t chain = sp::chain_fixed_bytes() + sp::dyn_bias_offset(L) + sizeof(float) * ((size_t)L * 3 * kMfR + kMfR);
+size_t split_lds_bytes(int L, int w) {
+  const size_t fixed = w == 3 ? sp::chain_fixed_bytes<2>() + sp::dyn_bias_offset<2>(L)
+                              : sp::chain_fixed_bytes<1>() + sp::dyn_bias_offset<1>(L);
+  const size_t chain = fixed + sizeof(float) * ((size_t)L * 3 * kMfR + kMfR);
   const size_t helper = sizeof(sp::HelperLds), cls = sizeof(sp::ClassLds);
   const size_t m = chain > helper ? chain : helper;
   return m > cls ? m : cls;
 }
 
 hipError_t launch_split_step(const StepArgs &a, hipStream_t s) {
-  const dim3 grid(a.sp_nb * (2 + kSpHelpers)), block(kMfThreads);
-  hipLaunchKernelGGL(sp::split_step_kernel, grid, block, split_lds_bytes(a.L), s, a);
+  const dim3 grid(sp::grid_blocks(a.sp_nb)), block(kMfThreads);
+  hipLaunchKernelGGL(sp::kernel_of(a.L, a.w), grid, block, split_lds_bytes(a.L, a.w), s, a);
   return hipGetLastError();
 }
 
-hipError_t split_setup(int L, int nb, int *coresident_ok) {
-  const size_t lds = split_lds_bytes(L);
-  hipError_t e = hipFuncSetAttribute((const void *)sp::split_step_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds);
+hipError_t split_setup(int L, int w, int nb, int *coresident_ok) {
+  const size_t lds = split_lds_bytes(L, w);
+  const void *k = (const void *)sp::kernel_of(L, w);
+  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int per_cu = 0, dev = 0, cus = 0;
-  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sp::split_step_kernel, kMfThreads, lds)) != hipSuccess)
-    return e;
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kMfThreads, lds)) != hipSuccess) return e;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-  *coresident_ok = (long long)per_cu * cus >= (long long)nb * (2 + kSpHelpers);
+  *coresident_ok = (long long)per_cu * cus >= (long long)sp::grid_blocks(nb);
   return hipSuccess;
 }
 
-hipError_t launch_split_repack_layer(const void *conv, const void *res, const void *skip, int l, int L, void *frags,
-                                     hipStream_t s) {
-  const int n = sp::LAYER_FRAGS * 64;
+hipError_t launch_split_repack_layer(const void *conv, const void *res, const void *skip, int l, int L, int w,
+                                     void *frags, hipStream_t s) {
+  const int n = (4 * sp::FA + 4 * sp::frags_b(w - 1) + sp::NHLP * sp::FS) * 64;
   hipLaunchKernelGGL(sp::repack_layer_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)conv,
-                     (const uint16_t *)res, (const uint16_t *)skip, l, L, (uint4 *)frags);
+                     (const uint16_t *)res, (const uint16_t *)skip, l, L, w - 1, (uint4 *)frags);
   return hipGetLastError();
 }
 
-hipError_t launch_split_repack_head(const void *head, const void *out, int L, void *frags, hipStream_t s) {
+hipError_t launch_split_repack_head(const void *head, const void *out, int L, int w, void *frags, hipStream_t s) {
   const int n = sp::NHLP * (sp::FW1 + sp::FW2) * 64;
   hipLaunchKernelGGL(sp::repack_head_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)head,
-                     (const uint16_t *)out, L, (uint4 *)frags);
+                     (const uint16_t *)out, L, w - 1, (uint4 *)frags);
   return hipGetLastError();
 }
 

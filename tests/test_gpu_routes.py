@@ -1,0 +1,112 @@
+"""GPU parity of the kernels and dispatch branches that tests/test_gpu_parity.py reaches only in part:
+each at the sizes where it can go wrong, against the CPU oracle (bars as stated there) or bit-exact."""
+import os
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+import rounding_model as RM  # noqa: E402
+from paper_1611_09482_amd import binding  # noqa: E402
+
+TOL = {W.F32: 1e-4, W.BF16: 2e-2}
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def row_rel_err(g, o):
+    return (np.abs(g - o).max(axis=-1) / np.maximum(np.abs(o).max(axis=-1), 1e-6)).max()
+
+
+def model(cfg, w, max_batch, **env):
+    os.environ.update(env)
+    try:
+        return binding.from_model(cfg, w, max_batch=max_batch)
+    finally:
+        for k in env:
+            os.environ.pop(k, None)
+
+
+@pytest.mark.parametrize("n_layers", [9, 10, 11, 13, 14, 15, 16, 17, 31])
+def test_split_layer_counts_closed_form(n_layers):
+    """The split kernels at every remainder of the six-layer loop (7-layer tails for a remainder of
+    1) and past 32 streams' worth of skip registers: bit-exact logits of the rounding-point closed
+    form, over a step count that rotates the register rings through every phase."""
+    cfg, w = RM.make_model(n_layers)
+    T = 9
+    want, _ = RM.closed_form(T)
+    fw = model(cfg, w, 5)
+    assert fw.lib.fwg_waits(fw.handle) == 1
+    lg = fw.teacher_forced(dev(W.sequences(6, 5, T))).cpu().numpy()
+    assert np.array_equal(lg, np.broadcast_to(want.astype(np.float32), lg.shape))
+
+
+@pytest.mark.parametrize("width,n_layers,B", [(2, 9, 1), (2, 10, 37), (2, 13, 130), (2, 20, 5), (3, 9, 17), (3, 12, 1),
+                                              (3, 13, 5), (3, 14, 33), (3, 16, 3), (3, 17, 130)])
+def test_split_widths_and_ragged_groups(width, n_layers, B):
+    """Both widths, odd and even layer counts, ragged group rows (1, 2, 3, 9 groups): teacher forcing
+    and online prediction resumed across launches against the oracle on sampled streams; every queue
+    wraps.  Generation equals the class drawn from the same prefix's logits in one piece or two."""
+    dil = tuple((1, 3, 2, 7, 1, 5)[i % 6] for i in range(n_layers))
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, dil, 512, 512, filter_width=width)
+    w = W.make_weights(cfg, 40 + n_layers, bias_scale=0.1)
+    fw = model(cfg, w, B)
+    assert fw.lib.fwg_waits(fw.handle) == 1
+    T = 70
+    x = W.sequences(41, B, T)
+    sel = sorted({0, B // 2, B - 1})
+    want = oracle.Oracle(w).teacher_forced(x[sel])
+    lg = fw.teacher_forced(dev(x)).cpu().numpy()
+    assert row_rel_err(lg[sel], want) <= TOL[W.BF16]
+    # online prediction over x[:, 1:] after a first observed sample: the same logits, bit by bit
+    cfg0 = np.full((B, 1), cfg.seed_input, np.int32)
+    y = np.concatenate([cfg0, x[:, :-1]], axis=1)
+    ref = fw.teacher_forced(dev(y)).cpu().numpy()
+    a = fw.step_forced(dev(x[:, :33])).cpu().numpy()
+    b = fw.step_forced(dev(x[:, 33:])).cpu().numpy()
+    assert np.array_equal(np.concatenate([a, b], axis=1), ref)
+    u = W.uniforms(42, B, 40)
+    fw.reset()
+    g = fw.generate(dev(u)).cpu().numpy()
+    fw.reset()
+    g1 = fw.generate(dev(u[:, :7])).cpu().numpy()
+    g2 = fw.generate(dev(u[:, 7:])).cpu().numpy()
+    assert np.array_equal(np.concatenate([g1, g2], axis=1), g)
+
+
+@pytest.mark.parametrize("n_layers,B", [(12, 11), (14, 20)])
+def test_split_graph_replays(n_layers, B):
+    """A generation recorded into a graph (queues reset, then generate) gives the eager samples on
+    every replay, with eager launches on the same handle between the replays."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, tuple(2 ** (i % 5) for i in range(n_layers)), 512, 512)
+    w = W.make_weights(cfg, 50, bias_scale=0.1)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        fw = binding.from_model(cfg, w, max_batch=B)
+        u = dev(W.uniforms(51, B, 30))
+        out = torch.empty((B, 30), dtype=torch.int32, device="cuda")
+        want = fw.generate(u).cpu().numpy()
+        x = dev(W.sequences(52, B, 20))
+        lg = fw.teacher_forced(x).cpu().numpy()
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            fw.reset()
+            fw.generate(u, out=out, check=False)
+        for _ in range(3):
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want)
+            assert np.array_equal(fw.teacher_forced(x).cpu().numpy(), lg)
+        fw.device_status()
