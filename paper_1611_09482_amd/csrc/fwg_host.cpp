@@ -63,6 +63,9 @@ struct Plan {
   int par_tc;             // steps per chunk; a chunk holds brows * par_tc rows at most
   std::vector<size_t> off_pconv, off_pconv_b, off_pres;
   size_t off_pskip, off_pskip_b, off_phead, off_pout;
+  bool stack_ok;          // the whole-stack kernel takes this model
+  int stack_force;        // FWG_PAR_STACK (test hook): 0 never, 1 always, else -1
+  size_t off_stack;       // its packed layer blocks
   size_t off_px[3], off_pxb[3], off_pz, off_psb, off_phb;  // three rotating row buffers
   // naive generator: the nodes of the output's dependency tree (Fig. 1), level 0 = inputs
   bool nv_ok;
@@ -377,6 +380,12 @@ int make_plan(const fwg_desc *d, Plan *p) {
                                  (p->C % 16 == 0 && ((long long)p->L * p->C) % kt == 0 && p->S % kt == 0 &&
                                   p->H % kt == 0));
   p->par_tc = 0;
+  p->stack_ok = p->par_ok && par_stack_ok(p->kind, p->dtype, p->C, w, p->L);
+  for (int l = 0; l < p->L; ++l)  // it addresses one layer's queue with 32-bit byte offsets
+    p->stack_ok = p->stack_ok && (unsigned long long)d->dilations[l] * p->brows * p->C * p->es < (1ull << 31);
+  p->off_stack = 0;
+  const char *ps = getenv("FWG_PAR_STACK");
+  p->stack_force = ps ? atoi(ps) != 0 : -1;
   if (p->par_ok) {
     const bool gated = p->kind == FWG_GATED;
     const bool fp32_stream = p->kind != FWG_RELU;                  // residual stream kept in float32
@@ -399,6 +408,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
       p->off_pconv_b[l] = take(sizeof(float) * p->Co);
       if (gated) p->off_pres[l] = take((size_t)p->C * p->C * p->es);
     }
+    if (p->stack_ok) p->off_stack = take(kStackLayerBytes * p->L);
     p->off_pskip = gated ? take((size_t)p->S * p->L * p->C * p->es) : 0;
     p->off_pskip_b = gated ? take(sizeof(float) * p->S) : 0;
     p->off_phead = gated ? take((size_t)p->H * p->S * p->es) : 0;
@@ -680,6 +690,16 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
   }
 }
 
+// Whether the whole-stack kernel beats one launch per layer for a chunk.  Measured per layer (30
+// layers): the stack kernel takes 4.0 us for each part of up to 256 steps of a stream (5.0 with every
+// compute unit busy), one block per stream; the per-layer kernel 7.7 us for up to ~8,000 rows and
+// 20 us for 65,536.  So long chunks of few streams (48 x 1,365 steps: 24 us in 6 parts against 20)
+// stay with the per-layer kernel, which spreads a stream's steps over the chip.
+bool stack_pays(int batch, int Tcur) {
+  const long long rounds = (batch + 255) / 256, parts = (Tcur + kStackRows - 1) / kStackRows;
+  return rounds * parts * 4.2 < std::max(7.7, 6.0 + 14.0 * batch * Tcur / 65536.0);
+}
+
 // Time-parallel evaluation of a forced sequence, chunk by chunk (MODE_TEACHER or MODE_ONLINE):
 // every layer is a GEMM over the chunk's rows whose popped operand comes from the chunk or from
 // the layer's queue in `ring`; a layer's queue is refreshed once its product has read it (by the
@@ -701,6 +721,24 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
     const int Tcur = (int)(n - s0 < p.par_tc ? n - s0 : p.par_tc);
     const int M = batch * Tcur;
     const long long t0 = tbase + s0;
+    const bool stack = p.stack_ok && (p.stack_force >= 0 ? p.stack_force != 0 : stack_pays(batch, Tcur));
+    if (stack) {
+      ParStack k;
+      memset(&k, 0, sizeof(k));
+      const int parts = (Tcur + kStackRows - 1) / kStackRows;
+      k.L = L; k.Tcur = Tcur; k.part = (Tcur + parts - 1) / parts; k.mode = mode; k.brows = p.brows;
+      k.t0 = t0; k.s0 = s0; k.n_steps = n;
+      k.inputs = inputs;
+      k.last = (const int32_t *)(ws + p.off_last);
+      k.embed = ws + p.off_embed;
+      k.embed_b = (const float *)(ws + p.off_embed_b);
+      k.packed = ws + p.off_stack;
+      k.layers = (const LayerDev *)(ws + p.off_layers);
+      k.ring = ring;
+      k.zout = logits ? ws + p.off_pz : nullptr;
+      k.ldz = (long long)L * C;
+      HIP_TRY(launch_par_stack(k, batch, s));
+    }
     ParEmbed e;
     memset(&e, 0, sizeof(e));
     e.M = M; e.C = C; e.Tcur = Tcur; e.mode = mode; e.s0 = s0; e.n_steps = n;
@@ -710,7 +748,7 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
     e.embed_b = (const float *)(ws + p.off_embed_b);
     e.xout = f32s ? px[0] : nullptr;
     e.oout = pxb[0];
-    HIP_TRY(launch_par_embed(e, p.dtype, s));
+    if (!stack) HIP_TRY(launch_par_embed(e, p.dtype, s));
     int cur = 0, prev = 0;
     auto refresh = [&](int l, const char *src) {
       ParRing q;
@@ -720,7 +758,7 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
       q.row_bytes = C * es;
       return launch_par_ring(q, s);
     };
-    for (int l = 0; l < L; ++l) {
+    for (int l = 0; l < L && !stack; ++l) {
       const int nxt = (cur + 1) % 3;
       ParGemm g;
       memset(&g, 0, sizeof(g));
@@ -932,6 +970,12 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
   if (p.nv_ok)
     TRY_OR_FREE(hipMemcpyAsync(ws + p.off_nv, p.nv_host.data(), sizeof(int32_t) * p.nv_host.size(),
                                hipMemcpyHostToDevice, s));
+  if (p.stack_ok) {
+    for (int l = 0; l < p.L; ++l)
+      TRY_OR_FREE(launch_par_stack_pack(w->conv[l], w->res[l], w->conv_b ? w->conv_b[l] : nullptr,
+                                        w->res_b ? w->res_b[l] : nullptr, ws + p.off_stack + kStackLayerBytes * l, s));
+    TRY_OR_FREE(set_par_stack_lds_limit(p.L));
+  }
   if (p.par_ok) {
     const int il = p.kind == FWG_GATED;  // gated conv rows interleave tanh and sigmoid channel groups
     for (int l = 0; l < p.L; ++l) {

@@ -77,6 +77,28 @@ hipError_t launch_par_gemm(const ParGemm &g, int dtype, int amode, int emode, hi
 // (par_gated_layer_ok).  Also refreshes the previous layer's queue when g.qring is set.
 bool par_gated_layer_ok(int R, int dtype);
 hipError_t launch_par_gated_layer(const ParGemm &g, int dtype, hipStream_t s);
+// A whole gated bf16 stack (R = 64, width 2) over the rows of a chunk, one block per stream running
+// every layer over `part` steps at a time (at most kStackRows): embedding, layers, z rows, queues.
+constexpr int kStackRows = 256;
+constexpr size_t kStackLayerBytes = 40 * 1024 + 3 * 64 * 4;  // one layer's packed weights and biases
+struct ParStack {
+  int L, Tcur, part, mode, brows;
+  long long t0, s0, n_steps;
+  const int32_t *inputs;   // [batch][n_steps]
+  const int32_t *last;     // pending input per stream (online prediction)
+  const void *embed;       // [Q][64] bf16
+  const float *embed_b;
+  const void *packed;      // [L] layer blocks (launch_par_stack_pack)
+  const LayerDev *layers;
+  void *ring;              // queue region
+  void *zout;              // z rows [batch * Tcur][ldz] (NULL: not wanted)
+  long long ldz;
+};
+bool par_stack_ok(int kind, int dtype, int C, int w, int L);
+hipError_t set_par_stack_lds_limit(int L);
+hipError_t launch_par_stack(const ParStack &g, int batch, hipStream_t s);
+hipError_t launch_par_stack_pack(const void *conv, const void *res, const float *conv_b, const float *res_b, void *dst,
+                                 hipStream_t s);
 hipError_t launch_par_embed(const ParEmbed &e, int dtype, hipStream_t s);
 hipError_t launch_par_ring(const ParRing &r, hipStream_t s);
 hipError_t launch_par_set_last(const int32_t *inputs, int32_t *last, int batch, int n_steps, hipStream_t s);

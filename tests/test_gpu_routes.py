@@ -110,3 +110,30 @@ def test_split_graph_replays(n_layers, B):
             assert np.array_equal(out.cpu().numpy(), want)
             assert np.array_equal(fw.teacher_forced(x).cpu().numpy(), lg)
         fw.device_status()
+
+
+@pytest.mark.parametrize("n_layers,B,T,rows", [(2, 1, 40, None), (9, 3, 700, None), (12, 5, 257, None), (10, 17, 300, 64),
+                                               (30, 2, 1100, None), (7, 33, 31, 96)])
+def test_parallel_stack(n_layers, B, T, rows):
+    """The whole-stack kernel: parts of 256 steps, ragged parts and waves, dilations shorter and longer
+    than a part, small chunks (queues refreshed between launches).  Teacher forcing against the
+    per-layer kernels on every stream and the oracle on one; priming in two pieces leaves the queues
+    the step kernels leave (their logits on the following steps)."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, tuple((1, 2, 4, 8, 16, 32, 64, 128, 256, 512)[i % 10] for i in range(n_layers)),
+                        512, 512)
+    w = W.make_weights(cfg, 60, bias_scale=0.1)
+    env = {} if rows is None else {"FWG_PAR_ROWS": str(rows * (-(-B // 16) * 16))}
+    fw = model(cfg, w, B, FWG_PAR_STACK="1", **env)
+    ref = model(cfg, w, B, FWG_PAR_STACK="0", **env)
+    x = W.sequences(61, B, T)
+    got = fw.teacher_forced_parallel(dev(x)).cpu().numpy()
+    assert row_rel_err(got[-1:], oracle.Oracle(w).teacher_forced(x[-1:])) <= TOL[W.BF16]
+    assert row_rel_err(got, ref.teacher_forced_parallel(dev(x)).cpu().numpy()) <= TOL[W.BF16]
+    h = T // 3 + 1
+    a = fw.prime(dev(x[:, :h]), logits=True).cpu().numpy()
+    fw.prime(dev(x[:, h:]))
+    ra = ref.step_forced(dev(x[:, :h])).cpu().numpy()
+    ref.step_forced(dev(x[:, h:]))
+    y = dev(W.sequences(62, B, 12))
+    assert row_rel_err(a, ra) <= TOL[W.BF16]
+    assert row_rel_err(fw.step_forced(y).cpu().numpy(), ref.step_forced(y).cpu().numpy()) <= TOL[W.BF16]
