@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfwg.so")
 SOURCES = [os.path.join(CSRC, "fwg_host.cpp"), os.path.join(CSRC, "fwg_kernels.hip"),
            os.path.join(CSRC, "fwg_mfma.hip"), os.path.join(CSRC, "fwg_parallel.hip"),
-           os.path.join(CSRC, "fwg_parstack.hip"),
+           os.path.join(CSRC, "fwg_parstack.hip"), os.path.join(CSRC, "fwg_parhead.hip"),
            os.path.join(CSRC, "fwg_wave.hip"), os.path.join(CSRC, "fwg_split.hip"),
            os.path.join(CSRC, "fwg_chain.hip"), os.path.join(CSRC, "fwg_wide.hip")]
 HEADERS = [os.path.join(ROOT, "include", "fwg.h"), os.path.join(CSRC, "fwg_internal.h"),

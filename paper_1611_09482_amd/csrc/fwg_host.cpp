@@ -66,6 +66,8 @@ struct Plan {
   bool stack_ok;          // the whole-stack kernel takes this model
   int stack_force;        // FWG_PAR_STACK (test hook): 0 never, 1 always, else -1
   size_t off_stack;       // its packed layer blocks
+  bool head_ok;           // the fused head kernel takes this model
+  size_t off_head_pack;   // its packed weights
   size_t off_px[3], off_pxb[3], off_pz, off_psb, off_phb;  // three rotating row buffers
   // naive generator: the nodes of the output's dependency tree (Fig. 1), level 0 = inputs
   bool nv_ok;
@@ -384,6 +386,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
   for (int l = 0; l < p->L; ++l)  // it addresses one layer's queue with 32-bit byte offsets
     p->stack_ok = p->stack_ok && (unsigned long long)d->dilations[l] * p->brows * p->C * p->es < (1ull << 31);
   p->off_stack = 0;
+  p->head_ok = p->par_ok && par_head_ok(p->kind, p->dtype, p->C, p->S, p->H, p->Q);
   const char *ps = getenv("FWG_PAR_STACK");
   p->stack_force = ps ? atoi(ps) != 0 : -1;
   if (p->par_ok) {
@@ -409,6 +412,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
       if (gated) p->off_pres[l] = take((size_t)p->C * p->C * p->es);
     }
     if (p->stack_ok) p->off_stack = take(kStackLayerBytes * p->L);
+    p->off_head_pack = p->head_ok ? take(par_head_bytes(p->L)) : 0;
     p->off_pskip = gated ? take((size_t)p->S * p->L * p->C * p->es) : 0;
     p->off_pskip_b = gated ? take(sizeof(float) * p->S) : 0;
     p->off_phead = gated ? take((size_t)p->H * p->S * p->es) : 0;
@@ -804,6 +808,21 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
       cur = nxt;
     }
     if (!logits) continue;
+    if (p.head_ok) {
+      ParHead k;
+      memset(&k, 0, sizeof(k));
+      k.M = M; k.L = L; k.Tcur = Tcur;
+      k.z = ws + p.off_pz; k.ldz = (long long)L * C;
+      k.packed = ws + p.off_head_pack;
+      k.skip_b = (const float *)(ws + p.off_pskip_b);
+      k.head_b = (const float *)(ws + p.off_head_b);
+      k.out_b = (const float *)(ws + p.off_out_b);
+      k.logits = logits; k.n_steps = n; k.s0 = s0;
+      // 64-row blocks while they fill at most one per compute unit (16,384 rows: 45 us against 66 with
+      // 128-row ones; from 24,576 rows on 128 is the faster: 71 against 74 us, at 65,536 178 against 246)
+      HIP_TRY(launch_par_head(k, M <= 64 * 256 ? 64 : 128, s));
+      continue;
+    }
     ParGemm o;
     memset(&o, 0, sizeof(o));
     o.M = M; o.N = p.Q; o.Tcur = Tcur; o.logits = logits; o.n_steps = n; o.s0 = s0;
@@ -975,6 +994,11 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
       TRY_OR_FREE(launch_par_stack_pack(w->conv[l], w->res[l], w->conv_b ? w->conv_b[l] : nullptr,
                                         w->res_b ? w->res_b[l] : nullptr, ws + p.off_stack + kStackLayerBytes * l, s));
     TRY_OR_FREE(set_par_stack_lds_limit(p.L));
+  }
+  if (p.head_ok) {
+    for (int l = 0; l < p.L; ++l) TRY_OR_FREE(launch_par_head_pack_skip(w->skip[l], l, p.L, ws + p.off_head_pack, s));
+    TRY_OR_FREE(launch_par_head_pack(w->head, w->out, p.L, ws + p.off_head_pack, s));
+    TRY_OR_FREE(set_par_head_lds_limit());
   }
   if (p.par_ok) {
     const int il = p.kind == FWG_GATED;  // gated conv rows interleave tanh and sigmoid channel groups

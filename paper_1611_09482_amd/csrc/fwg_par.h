@@ -99,6 +99,22 @@ hipError_t set_par_stack_lds_limit(int L);
 hipError_t launch_par_stack(const ParStack &g, int batch, hipStream_t s);
 hipError_t launch_par_stack_pack(const void *conv, const void *res, const float *conv_b, const float *res_b, void *dst,
                                  hipStream_t s);
+// The head of a gated bf16 chunk (R = 64, S = H = 512, 256 classes) in one kernel: z rows to logits.
+struct ParHead {
+  int M, L, Tcur;
+  const void *z;           // [M][ldz] bf16, layer l's R values at column l R
+  long long ldz;
+  const void *packed;      // launch_par_head_pack_skip (every layer) and launch_par_head_pack
+  const float *skip_b, *head_b, *out_b;  // summed skip biases [S], [H], [Q]
+  float *logits;           // [batch][n_steps][Q]
+  long long n_steps, s0;
+};
+bool par_head_ok(int kind, int dtype, int C, int S, int H, int Q);
+size_t par_head_bytes(int L);
+hipError_t set_par_head_lds_limit();
+hipError_t launch_par_head(const ParHead &g, int rows_per_block, hipStream_t s);  // 64 or 128
+hipError_t launch_par_head_pack_skip(const void *skip, int l, int L, void *packed, hipStream_t s);
+hipError_t launch_par_head_pack(const void *head, const void *out, int L, void *packed, hipStream_t s);
 hipError_t launch_par_embed(const ParEmbed &e, int dtype, hipStream_t s);
 hipError_t launch_par_ring(const ParRing &r, hipStream_t s);
 hipError_t launch_par_set_last(const int32_t *inputs, int32_t *last, int batch, int n_steps, hipStream_t s);

@@ -137,3 +137,26 @@ def test_parallel_stack(n_layers, B, T, rows):
     y = dev(W.sequences(62, B, 12))
     assert row_rel_err(a, ra) <= TOL[W.BF16]
     assert row_rel_err(fw.step_forced(y).cpu().numpy(), ref.step_forced(y).cpu().numpy()) <= TOL[W.BF16]
+
+
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (5, 13), (3, 43), (1, 129)])
+def test_parallel_head_row_tails(B, T):
+    """The fused head at row counts around its 64-row blocks (1, 63, 65, 129 rows), both widths'
+    row producers, against the step kernels on every row."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 1, 2, 4, 8, 1, 3), 512, 512, filter_width=2 + B % 2)
+    w = W.make_weights(cfg, 70, bias_scale=0.1)
+    fw = model(cfg, w, B)
+    x = dev(W.sequences(71, B, T))
+    assert row_rel_err(fw.teacher_forced_parallel(x).cpu().numpy(), fw.teacher_forced(x).cpu().numpy()) <= TOL[W.BF16]
+
+
+def test_parallel_head_large_blocks():
+    """Past 16,384 rows a chunk's head runs in 128-row blocks: ragged last block, sampled streams."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8), 512, 512)
+    w = W.make_weights(cfg, 72, bias_scale=0.1)
+    B, T = 129, 131
+    fw = model(cfg, w, B)
+    x = W.sequences(73, B, T)
+    got = fw.teacher_forced_parallel(dev(x)).cpu().numpy()
+    sel = [0, 64, 128]
+    assert row_rel_err(got[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[W.BF16]
