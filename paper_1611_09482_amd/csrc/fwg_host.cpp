@@ -44,9 +44,9 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct Plan {
-  int kind, dtype, Q, C, S, H, L, bmax, seed_input, Co, es, rpw;
+  int kind, dtype, Q, C, S, H, L, bmax, seed_input, Co, es;
+  int valu_threads;       // general step kernel: threads per block
   size_t valu_block;      // bytes of one layer's weight + bias block (general step kernels)
-  int valu_wbytes;        // the block when the general step kernels stage it in LDS, else 0
   int w;                  // filter width: taps per dilated product
   int regime;
   int brows;              // queue rows per slot (max_batch, padded to whole blocks for the MFMA family)
@@ -225,36 +225,22 @@ int make_plan(const fwg_desc *d, Plan *p) {
     b += sizeof(float) * ((size_t)p->Co + (g ? (size_t)p->C + p->S : 0));
     p->valu_block = (b + 15) & ~(size_t)15;
   }
-  // rows per block and weight staging.  Staging moves a layer's weight loads off its critical path
-  // but costs the copy issue; it pays from two streams per block (measured: at one stream the
-  // layer is too short to hide the copy).  Take the most rows per block (at most 8, fewer for
-  // tiny batches) at which two layers' blocks fit in LDS, else the most rows that fit without
-  // staging.  The popped states of a layer are held in registers between layers (at most
-  // kValuPrefPops per thread).
-  int rmax = 8;
-  while (rmax > 1 && rmax > p->bmax) rmax >>= 1;
-  const char *vs = getenv("FWG_VALU_STAGE");  // "0": never stage (the variant that reads weights from L2)
-  const bool can_stage = p->valu_block <= (size_t)kValuStagePieces * 16 * kThreads && !(vs && strcmp(vs, "0") == 0);
-  const int wf = (int)(p->valu_block / 4);
-  int rpw = 0;
-  bool stage = false;
-  p->lds_bytes = 0;
-  for (int pass = 0; pass < 2 && rpw == 0 && valu_ok; ++pass) {
-    const bool st = pass == 0;
-    if (st && !can_stage) continue;
-    for (int r = rmax; r >= (st ? 2 : 1); r >>= 1) {
-      if (r * (w - 1) * p->C > kValuPrefPops * kThreads) continue;
-      const ValuLds lay = valu_lds_layout(p->kind, p->C, p->S, p->H, p->Q, p->L, r, w, st ? wf : 0);
-      if ((size_t)lay.total_floats * 4 <= 160 * 1024) {
-        rpw = r;
-        stage = st;
-        p->lds_bytes = (size_t)lay.total_floats * 4;
-        break;
-      }
-    }
-  }
-  p->rpw = rpw > 0 ? rpw : 1;
-  p->valu_wbytes = stage ? (int)p->valu_block : 0;
+  // Threads of the general step kernel: 512 where every product splits evenly over them, each stream can
+  // have a compute unit of its own (two blocks of 512 do not share one: at 512 streams 155 us per step
+  // against 96 for R = 64, S = 256 float32) and the layers are large enough (us per step with 256 / 512
+  // threads: ReLU C = 256 float32 101 / 62, C = 128 bf16 23 / 18, gated R = 128, S = 512 float32 148 / 88;
+  // gated R = 64, S = 128 bf16, 56 KB per layer, 67 / 75).
+  auto split_ok = [&](int K, int N, int threads) { return N >= threads || (threads % N == 0 && (K / kb) % (threads / N) == 0); };
+  auto threads_ok = [&](int t) {
+    const bool g = p->kind == FWG_GATED;
+    return split_ok(w * p->C, p->Co, t) && split_ok(g ? p->H : p->C, p->Q, t) &&
+           (!g || (split_ok(p->C, p->C, t) && split_ok(p->C, p->S, t) && split_ok(p->S, p->H, t)));
+  };
+  const bool small_layer = p->kind == FWG_GATED && p->valu_block < 200 * 1024;
+  p->valu_threads = threads_ok(512) && p->bmax <= 256 && !small_layer ? 512 : 256;
+  // the popped states of a layer are held in registers between layers
+  p->lds_bytes = (size_t)valu_lds_layout(p->kind, p->C, p->S, p->H, p->Q, p->L, w, p->valu_threads).total_floats * 4;
+  const bool valu_fits = (w - 1) * p->C <= kValuPrefPops * kThreads && p->lds_bytes <= 160 * 1024;
 
   // kernel family: the MFMA kernel covers gated bf16 stacks with R=64, S=H=512, filter width 2 or 3
   p->regime = REGIME_VALU;
@@ -297,7 +283,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
                 "unsupported shape: every product needs K a multiple of %d, and an output width that "
                 "divides 256 (with K/%d divisible by 256/N) or is at least 256",
                 kb, kb);
-  if (p->regime == REGIME_VALU && rpw == 0)
+  if (p->regime == REGIME_VALU && !valu_fits)
     return fail(FWG_EUNSUPPORTED, "model too wide for one block's LDS and registers");
   const bool mf_family = p->regime == REGIME_MFMA || p->regime == REGIME_SPLIT;
   p->brows = mf_family ? (p->bmax + kMfRows - 1) / kMfRows * kMfRows : p->bmax;
@@ -498,7 +484,6 @@ StepArgs base_args(const fwg_handle *h) {
   a.out_b = (const float *)(h->ws + p.off_out_b);
   a.last = (int32_t *)(h->ws + p.off_last);
   a.bmax = p.brows;
-  a.valu_wbytes = p.valu_wbytes;
   if (p.regime == REGIME_MFMA || p.regime == REGIME_SPLIT) {
     a.mf_frags = h->ws + p.off_frags;
     a.mf_embT = h->ws + p.off_embT;
@@ -690,7 +675,7 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       g.image = (const float *)(h->ws + p.off_wave);
       return launch_wave_step(a, g, h->stream);
     }
-    default: return launch_valu_step(a, p.rpw, p.lds_bytes, h->stream);
+    default: return launch_valu_step(a, p.valu_threads, p.lds_bytes, h->stream);
   }
 }
 
@@ -1077,7 +1062,8 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
                                        (float *)(ws + p.off_bias), s));
     TRY_OR_FREE(set_mfma_lds_limit(mfma_lds_bytes(p.L, p.w)));
   }
-  if (p.lds_bytes > 64 * 1024) TRY_OR_FREE(set_valu_lds_limit(p.lds_bytes));
+  if (h->plan.regime == REGIME_VALU && p.lds_bytes > 64 * 1024)
+    TRY_OR_FREE(set_valu_lds_limit(dt, p.valu_threads, p.kind, p.w, p.lds_bytes));
   int rr = enqueue_reset(h);
   if (rr != FWG_OK) return cleanup_fail(rr);
   // the layer table is copied from host memory owned by this call

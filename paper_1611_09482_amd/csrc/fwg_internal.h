@@ -15,7 +15,7 @@ constexpr int kMaxLayers = 1024;  // per-layer slot counters live in LDS
 // One dilated layer as the step kernels see it (device-resident table).
 struct LayerDev {
   // general step kernels: conv, res and skip weights, then conv_b, res_b and skip_b, are one
-  // contiguous block starting at conv (staged into LDS as a unit)
+  // contiguous block starting at conv
   const void *conv;     // packed conv weights (W_r stacked over W_e), layout per kernel family
   const float *conv_b;  // [Cout]
   const void *res;      // gated: packed [R][R]
@@ -30,8 +30,6 @@ struct LayerDev {
 // Arguments of one step-kernel launch (passed by value).
 struct StepArgs {
   const LayerDev *layers;  // [L]
-  int valu_wbytes;         // general step kernels: bytes of one layer's weights + biases staged in LDS
-                           // one layer ahead (0: read from global memory)
   const void *embed;       // [Q][C] rows (embedding transposed for a row gather)
   const float *embed_b;    // [C]
   const void *head;        // gated: packed [H][S]

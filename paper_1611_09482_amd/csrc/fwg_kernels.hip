@@ -1,11 +1,10 @@
 // HIP kernels of the Fast Wavenet generation library, written for gfx950.
 //
-// This file holds the general ("VALU") step-kernel family and the small
-// utility kernels (weight repacking, fills).  One launch runs n_steps whole
-// generation steps for a block of `RPW` independent streams: every step pops
-// each layer's queue, runs the generation model (one step of a multi-layer
-// RNN, paper Section 2.2, Fig. 4), pushes the new states, computes the output
-// distribution and samples the next input (fed back, Section 1).
+// This file holds the general ("VALU") step kernel and the small utility kernels (weight repacking,
+// fills).  One launch runs n_steps whole generation steps, one block per stream: every step pops
+// each layer's queue, runs the generation model (one step of a multi-layer RNN, paper Section 2.2,
+// Fig. 4), pushes the new states, computes the output distribution and samples the next input (fed
+// back, Section 1).
 //
 // Layout decisions:
 //   * queues: one ring buffer per layer, ring_l[slot][stream][channel] with the
@@ -14,11 +13,9 @@
 //     after every lane has read it (pop before push, Section 2.2);
 //   * weights: streamed from L2 in a 16-byte K-blocked layout, so consecutive
 //     lanes read consecutive 16-byte chunks;
-//   * activations of the block's streams: LDS, float32.
+//   * activations of the block's stream: LDS, float32.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-#include <type_traits>
 
 #include "fwg_bf16.h"
 #include "fwg_internal.h"
@@ -29,15 +26,6 @@
 namespace fwg {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// Direct global-to-LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane i's bytes come
-// from src_wave + lane_off (lane_off = 16 i) and land at LDS byte address lds_dst_wave + 16 i (the
-// LDS base wave-uniform; the compiler sets M0 from it).  Consecutive copies issue back to back;
-// callers wait for completion (vmcnt) before the data is read.
-__device__ __forceinline__ void lds_copy16(const void *src_wave, uint32_t lane_off, const void *lds_dst_wave) {
-  __builtin_amdgcn_global_load_lds((const char *)src_wave + lane_off,
-                                   (__attribute__((address_space(3))) void *)lds_dst_wave, 16, 0, 0);
-}
 
 template <typename WT> struct WTraits;
 template <> struct WTraits<float> {
@@ -64,153 +52,180 @@ template <> struct WTraits<uint16_t> {
 };
 
 // ---------------------------------------------------------------------------
-// Row-block product: part[kg][r][n] = sum over this K-group of W^T[k][n] * A(r, k)
-// for r < RPW.  A(r, k) = A0[r*lda0 + k] for k < ksplit, else A1[r*lda1 + k - ksplit].
-// N >= 256: each thread owns columns tid, tid+256, ... over all of K (one group).
-// N < 256 : 256/N K-groups of N threads each.
-// WP: the weight pointer type, a global (address space 1) or an LDS (address space 3) pointer to
-// 16-byte vectors, so that staged weights are read with LDS instructions.
-typedef __attribute__((address_space(3))) const u32x4 *lds_u4p;
-typedef __attribute__((address_space(1))) const u32x4 *glb_u4p;
-
-template <typename WT, int RPW, typename WP>
-__device__ __forceinline__ void rows_product(WP W, int K, int N, const float *A0, int lda0,
-                                             const float *A1, int lda1, int ksplit, float *part) {
-  constexpr int KB = WTraits<WT>::KB;
-  const int tid = threadIdx.x;
-  const int nkb = K / KB;
-  if (N >= kThreads) {
-    for (int n = tid; n < N; n += kThreads) {
-      float acc[RPW];
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) acc[r] = 0.f;
-      auto kstep = [&](int kb) {
-        float w[KB];
-        WTraits<WT>::unpack(W[(long long)kb * N + n], w);
-        const int k0 = kb * KB;
-        const bool lo = k0 < ksplit;
-        const float *A = lo ? A0 + k0 : A1 + (k0 - ksplit);
-        const int lda = lo ? lda0 : lda1;
-#pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-#pragma unroll
-          for (int j = 0; j < KB; ++j) acc[r] = fmaf(w[j], A[r * lda + j], acc[r]);
-        }
-      };
-      // staged (LDS) weights: 16 k-blocks per unrolled body keep more LDS reads in flight
-      // (gated fp32 64-stream step 89.9 -> 80.3 us); weights read from L2 keep 4, whose
-      // pipelining the compiler does best (16 made the 512-channel ReLU stack 4x slower)
-      if constexpr (std::is_same<WP, lds_u4p>::value) {
-#pragma unroll 16
-        for (int kb = 0; kb < nkb; ++kb) kstep(kb);
-      } else {
-#pragma unroll 4
-        for (int kb = 0; kb < nkb; ++kb) kstep(kb);
-      }
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) part[r * N + n] = acc[r];
-    }
-  } else {
-    const int KG = kThreads / N;
-    const int n = tid % N, kg = tid / N;
-    const int per = nkb / KG;
-    float acc[RPW];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) acc[r] = 0.f;
-#pragma unroll 4
-    for (int i = 0; i < per; ++i) {
-      const int kb = kg * per + i;
-      float w[KB];
-      WTraits<WT>::unpack(W[(long long)kb * N + n], w);
-      const int k0 = kb * KB;
-      const bool lo = k0 < ksplit;
-      const float *A = lo ? A0 + k0 : A1 + (k0 - ksplit);
-      const int lda = lo ? lda0 : lda1;
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) {
-#pragma unroll
-        for (int j = 0; j < KB; ++j) acc[r] = fmaf(w[j], A[r * lda + j], acc[r]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) part[(kg * RPW + r) * N + n] = acc[r];
-  }
+// Products of one stream: part[kg][n] = sum over K-group kg of W^T[k][n] A[k] (+ bias[n] in group 0), A in
+// LDS.  With NT threads:
+// N >= NT: each thread owns columns tid, tid + NT, ... over all of K (one group); N < NT (N divides NT):
+// NT / N K-groups of N threads each.
+// A thread's weights are chunks of U 16-byte pieces (consecutive k-blocks of a column); the first chunk and the bias are
+// loaded by `head` before the barrier that makes A ready (weights depend on no activation), every later
+// chunk while the one before is multiplied.  Weights come through raw buffer
+// loads: one VGPR offset per thread and product, kept for the launch, and a scalar offset per piece
+// (with 64-bit addresses the index arithmetic of runtime shapes cost more than the products).
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ __forceinline__ Rsrc rsrc(const void *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
+}
+// A uniform value that the compiler takes as new here: what follows from it is computed where it is used
+// (hoisted out of the layer loop, the scalar offsets of every piece overflowed the scalar registers).
+__device__ __forceinline__ int fresh(int v) {
+  v = __builtin_amdgcn_readfirstlane(v);
+  asm volatile("" : "+s"(v));
+  return v;
+}
+template <typename T> __device__ __forceinline__ T *uniform_ptr(T *p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T *)(((uint64_t)hi << 32) | lo);
 }
 
-// Sum of the K-group partials of output (r, n).
-template <int RPW>
-__device__ __forceinline__ float part_sum(const float *part, int N, int r, int n) {
-  const int KG = N >= kThreads ? 1 : kThreads / N;
-  float s = 0.f;
-  for (int kg = 0; kg < KG; ++kg) s += part[(kg * RPW + r) * N + n];
+template <typename WT, int NT>
+struct Product {
+  static constexpr int KB = WTraits<WT>::KB, U = 8;
+  // the thread's share: first piece and first column, first k, K-group; k-blocks per column
+  int piece, n, k0, kg, per, N;
+  __device__ __forceinline__ void init(int K, int N_) {
+    const int nkb = K / KB, tid = threadIdx.x;
+    N = N_;
+    if (N >= NT) {
+      n = tid;
+      kg = 0;
+      per = nkb;
+    } else {
+      const int sh = __builtin_ctz(N);
+      n = tid & (N - 1);
+      kg = tid >> sh;
+      per = nkb >> (__builtin_ctz(NT) - sh);
+    }
+    k0 = kg * per * KB;
+    piece = kg * per * N + n;
+  }
+  // byte offset of the thread's first piece in its c-th column (threads past the last column repeat it)
+  __device__ __forceinline__ uint32_t at(int c) const {
+    return (uint32_t)(piece + min(NT * c, N - 1 - n)) * 16u;
+  }
+};
+
+// One product in flight: a ring of U pieces, refilled four at a time as they are multiplied.
+template <typename WT, int NT>
+struct Flight {
+  static constexpr int KB = WTraits<WT>::KB, U = Product<WT, NT>::U;
+  u32x4 w[U];
+  float bias;
+  __device__ __forceinline__ void load4(int N, int per, Rsrc r, uint32_t base, uint32_t voff, int kb, int g) {
+#pragma unroll
+    for (int u = g; u < g + 4; ++u)  // past the end: the last piece again, not multiplied
+      w[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           r, voff, base + (uint32_t)(min(kb + u, per - 1) * N) * 16u, 0));
+  }
+  __device__ __forceinline__ void load_bias(const Product<WT, NT> &p, Rsrc rb, uint32_t bias_at, int c) {
+    bias = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, 4 * min(p.n + NT * c, p.N - 1), bias_at, 0));
+  }
+  // base: byte offset of the product's weights in r; bias_at: byte offset of its biases in rb
+  __device__ __forceinline__ void head(const Product<WT, NT> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at) {
+    load_bias(p, rb, bias_at, 0);
+    const uint32_t voff = p.at(0);
+    const int N = fresh(p.N), per = fresh(p.per);
+#pragma unroll
+    for (int g = 0; g < U; g += 4)
+      if (g < per) load4(N, per, r, base, voff, 0, g);
+  }
+  __device__ __forceinline__ void run(const Product<WT, NT> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at,
+                                      const float *A, float *part) {
+    const int N = fresh(p.N), per = fresh(p.per), cols = (N + NT - 1) / NT;
+    A += p.k0;
+    float *out = part + p.kg * p.N + p.n;
+    for (int c = 0; c < cols; ++c) {
+      float acc = p.kg == 0 ? bias : 0.f;
+      if (c + 1 < cols) load_bias(p, rb, bias_at, c + 1);
+      for (int kb = 0; kb < per; kb += U) {
+        // the chunk after this one: of this column, or the first of the next
+        const bool here = kb + U < per, next = here || c + 1 < cols;
+        const int nkb = here ? kb + U : 0;
+        const uint32_t nvoff = p.at(here ? c : c + 1);
+        const float *x = A + kb * KB;
+        float4 xv[U * KB / 4];
+#pragma unroll
+        for (int i = 0; i < U * KB / 4; ++i) xv[i] = *(const float4 *)(x + 4 * i);  // past the end: not multiplied
+        auto piece = [&](int u) {
+          float wv[KB];
+          WTraits<WT>::unpack(w[u], wv);
+#pragma unroll
+          for (int j = 0; j < KB; j += 4) {
+            const float4 xx = xv[(u * KB + j) / 4];
+            acc = fmaf(wv[j], xx.x, acc);
+            acc = fmaf(wv[j + 1], xx.y, acc);
+            acc = fmaf(wv[j + 2], xx.z, acc);
+            acc = fmaf(wv[j + 3], xx.w, acc);
+          }
+        };
+        const int left = per - kb;
+#pragma unroll
+        for (int g = 0; g < U; g += 4) {
+          if (left >= g + 4) {
+#pragma unroll
+            for (int u = g; u < g + 4; ++u) piece(u);
+          } else {
+#pragma unroll
+            for (int u = g; u < g + 3; ++u)
+              if (u < left) piece(u);
+          }
+          if (next && nkb + g < per) load4(N, per, r, base, nvoff, nkb, g);
+        }
+      }
+      if (p.n + NT * c < p.N) out[NT * c] = acc;
+    }
+  }
+};
+
+// Sum of the K-group partials of output n.
+template <int NT>
+__device__ __forceinline__ float part_sum(const float *part, int N, int n) {
+  float s = part[n];
+  if (N < NT)
+    for (int i = n + N; i < NT; i += N) s += part[i];
   return s;
 }
 
 __device__ __forceinline__ float bias_or0(const float *b, int i) { return b ? b[i] : 0.f; }
 
-
 // ---------------------------------------------------------------------------
-// The general step kernel.  Block = RPW streams, 256 threads.
+// The general step kernel: one block of NT threads per stream.
 //
+// What bounds it is the compute unit's load path: a step streams every weight from the L2 at up to 64
+// bytes per cycle (a layer of R = 64, S = 256 float32 channels, 147 KB, ~1 us).  So a stream gets a
+// compute unit of its own for as long as there are any: with up to 8 streams on a block, to share its
+// weights, most of the chip was idle (16 streams of that 20-layer model: 562 us per step on 2 blocks,
+// 74 now; 512 streams 568 and 96).  Blocks of 256 threads share a compute unit from 257 streams on.
+// At ~3.5 us per layer the chain of barriers, LDS reads and partial sums is still what bounds it.
 // Latency hiding: the states a layer pops do not depend on the current step (they were pushed
 // at least d steps earlier), so the pops of layer l + 1 -- or of layer 0 of the next step -- are
 // loaded into registers while layer l computes and land in the second of two LDS buffers at the
-// end of the layer.  When two layers' weights fit in LDS (a.valu_wbytes > 0) the next layer's
-// weights and biases are copied into the second weight buffer meanwhile, by direct
-// global-to-LDS loads, so a layer's critical path touches LDS only.
-typedef __attribute__((address_space(3))) const float *lds_f32p;
-typedef __attribute__((address_space(1))) const float *glb_f32p;
-
-// Model shapes known at compile time.  The general kernel reads the shape from its launch
-// arguments; at one stream per block a layer is bound by instruction issue, and with the shape as
-// constants the index arithmetic folds and fewer values stay live.  Fields: kind (-1: runtime), C,
-// Q and w (0: runtime), S and H (-1: runtime).
-struct ShapeAny {
-  static constexpr int kind = -1, C = 0, S = -1, H = -1, Q = 0, w = 0;
-};
-template <int KIND, int C_, int S_, int H_, int W_>
-struct ShapeFixed {
-  static constexpr int kind = KIND, C = C_, S = S_, H = H_, Q = 256, w = W_;
-};
-
-template <typename WT, int RPW, bool STAGE, typename SH>
-__global__ void __launch_bounds__(kThreads) valu_step_kernel(StepArgs a) {
+// end of the layer; each product's first weights are in registers before its operands are ready.
+// GATED and W2 (filter width 2) are compile-time: fewer shape values stay live.
+template <typename WT, int NT, bool GATED, bool W2>
+__global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
   extern __shared__ float4 lds_raw[];
   float *lds = (float *)lds_raw;
-  const int wfloats = a.valu_wbytes / 4;
-  // the model shape: compile-time constants in a specialised instantiation, else launch arguments
-  const int kind = SH::kind >= 0 ? SH::kind : a.kind;
-  const int C = SH::C ? SH::C : a.C, S = SH::S >= 0 ? SH::S : a.S, H = SH::H >= 0 ? SH::H : a.H;
-  const int Q = SH::Q ? SH::Q : a.Q, w = SH::w ? SH::w : a.w, L = a.L;
-  const ValuLds lay = valu_lds_layout(kind, C, S, H, Q, L, RPW, w, wfloats);
-  float *xf = lds + lay.xf, *xo = lds + lay.xo, *ao = lds + lay.ao;
-  float *zo = lds + lay.zo, *so = lds + lay.so, *ho = lds + lay.ho, *h2 = lds + lay.h2;
+  const int kind = GATED ? 2 : a.kind, C = a.C, S = a.S, H = a.H, Q = 256, w = W2 ? 2 : a.w, L = a.L;
+  const ValuLds lay = valu_lds_layout(kind, C, S, H, Q, L, w, NT);
+  // the two buffers of operand rows (the w - 1 popped states, oldest first, then the current input)
+  auto vbuf = [&](int p) { return lds + (p ? lay.vx2 : lay.vx); };
+  float *xf = lds + lay.xf, *zo = lds + lay.zo, *so = lds + lay.so, *h2 = lds + lay.h2;
   float *lg = lds + lay.lg, *partA = lds + lay.partA, *partB = lds + lay.partB;
-  // the two buffers of popped states and of staged weights, selected by arithmetic on the LDS base
-  // (a pointer array indexed at run time would turn LDS accesses into generic ones)
-  auto vbuf = [&](int p) { return lds + (p ? lay.vo2 : lay.vo); };
-  auto wbuf = [&](int p) { return (uint4 *)(lds + (p ? lay.wb1 : lay.wb0)); };
   int *slots = (int *)(lds + lay.slots);
   int *ins = (int *)(lds + lay.ins);
   ValuLayer *ltab = (ValuLayer *)(lds + lay.ltab);
-  (void)ao;
 
-  const int tid = threadIdx.x;
-  const int Co = kind == 2 ? 2 * C : C;
-  const int K = w * C;
-  const int b0 = blockIdx.x * RPW;
-  const int nrows = min(RPW, a.batch - b0);
-  if (nrows <= 0) return;
-  constexpr bool stage = STAGE;  // the host launches the staging variant iff a.valu_wbytes > 0
-  const int nw16 = a.valu_wbytes / 16;       // 16-byte pieces of one layer's staged block
-  const int VP = RPW * (w - 1) * C;          // popped elements per layer
-  const int es = sizeof(WT);
+  const int tid = threadIdx.x, b = blockIdx.x;
+  const int Co = GATED ? 2 * C : C;
+  const int K = w * C, XO = (w - 1) * C;  // row length of the operands; where the current input starts
+  const uint32_t es = sizeof(WT);
   // offsets inside a layer's block: conv | res | skip weights, then conv_b | res_b | skip_b
-  const size_t o_res = (size_t)K * Co * es, o_skip = o_res + (size_t)C * C * es;
-  const size_t o_cb = kind == 2 ? o_skip + (size_t)S * C * es : o_res;
-  const size_t o_rb = o_cb + (size_t)Co * 4, o_sb = o_rb + (size_t)C * 4;
+  const uint32_t o_res = (uint32_t)K * Co * es, o_skip = o_res + (uint32_t)C * C * es;
+  const uint32_t o_cb = GATED ? o_skip + (uint32_t)S * C * es : o_res;
+  const uint32_t o_rb = o_cb + (uint32_t)Co * 4, o_sb = o_rb + (uint32_t)C * 4, o_end = GATED ? o_sb + S * 4 : o_rb;
 
-  for (int l = tid; l < L; l += kThreads) {
+  for (int l = tid; l < L; l += NT) {
     const LayerDev ld = a.layers[l];
     ValuLayer v;
     v.block = ld.conv;
@@ -221,71 +236,72 @@ __global__ void __launch_bounds__(kThreads) valu_step_kernel(StepArgs a) {
     ltab[l] = v;
     slots[l] = (int)(a.t0 % (long long)ld.depth);
   }
-  if (tid < RPW) {
-    int v = 0;
-    if (tid < nrows) v = a.mode == MODE_TEACHER ? a.inputs[(long long)(b0 + tid) * a.n_steps] : a.last[b0 + tid];
-    ins[tid] = v;
-  }
+  if (tid == 0) ins[0] = a.mode == MODE_TEACHER ? a.inputs[(long long)b * a.n_steps] : a.last[b];
   __syncthreads();
 
-  // prefetch registers of the next layer's popped states
+  // prefetch registers of the next layer's popped states: element i is tap i / C, channel i % C
   float pp[kValuPrefPops];
-  const uint32_t lane16 = 16u * (uint32_t)(tid & 63);
-  // tap k of layer l at the step whose slot is `slot`: the state k d slots after the oldest one;
-  // with staging, the layer's weight block is copied straight into weight buffer `par`
-  auto fetch = [&](int l, int slot, int par) {
+  auto fetch = [&](int l, int slot_) {
     const ValuLayer ld = ltab[l];
+    const int slot = fresh(slot_), depth = fresh(ld.depth), dil = fresh(ld.dil);
+    const char *row = uniform_ptr((const char *)a.ring + (ld.ring_off + (long long)b * C) * es);
+    const long long slot_bytes = (long long)fresh(a.bmax) * C * es;
 #pragma unroll
     for (int j = 0; j < kValuPrefPops; ++j) {
-      const int i = tid + j * kThreads;
+      if (j * NT >= XO) break;
+      const int i = tid + j * NT;
       float v = 0.f;
-      if (i < VP) {
-        const int r = i / ((w - 1) * C), kc = i - r * ((w - 1) * C), k = kc / C, c = kc - k * C;
-        int sk = slot + k * ld.dil;
-        if (sk >= ld.depth) sk -= ld.depth;
-        if (r < nrows)
-          v = WTraits<WT>::load1(a.ring, ld.ring_off + (long long)sk * a.bmax * C + (long long)(b0 + r) * C + c);
+      if (i < XO) {
+        int k = 0, c = i;
+        if (!W2) {
+          k = i / C;
+          c = i - k * C;
+        }
+        int sk = slot + (W2 ? 0 : k * dil);  // k dilations after the oldest state
+        if (!W2 && sk >= depth) sk -= depth;
+        v = WTraits<WT>::load1(row + sk * slot_bytes, c);
       }
       pp[j] = v;
-    }
-    if (stage) {
-      // each wave copies 64 consecutive 16-byte pieces per instruction
-      const uint4 *src = (const uint4 *)ld.block;
-      const int wv = tid >> 6;
-#pragma unroll
-      for (int j = 0; j < kValuStagePieces; ++j) {
-        const int base = j * kThreads + wv * 64;
-        if (base < nw16 && (tid & 63) + base < nw16) lds_copy16(src + base, lane16, wbuf(par) + base);
-      }
     }
   };
   auto land = [&](int par) {
     float *vb = vbuf(par);
 #pragma unroll
     for (int j = 0; j < kValuPrefPops; ++j) {
-      const int i = tid + j * kThreads;
-      if (i < VP) vb[i] = pp[j];
+      if (j * NT >= XO) break;
+      const int i = tid + j * NT;
+      if (i < XO) vb[i] = pp[j];
     }
-    // the copies into the weight buffer have completed once the memory counter drains
-    if (stage) __builtin_amdgcn_s_waitcnt(0);
   };
+  auto layer_rsrc = [&](int l) { return rsrc(uniform_ptr((const char *)ltab[l].block), o_end); };
 
-  fetch(0, slots[0], 0);
+  Product<WT, NT> pconv, pres, pskip, phead, pout;
+  const int Ktop = GATED ? H : C;
+  pconv.init(K, Co);
+  pout.init(Ktop, Q);
+  if constexpr (GATED) {
+    pres.init(C, C);
+    pskip.init(C, S);
+    phead.init(S, H);
+  }
+  Flight<WT, NT> conv;
+
+  fetch(0, slots[0]);
   land(0);
-  __syncthreads();
-  int par = 0;  // buffer holding the current layer's pops and weights
+  Rsrc rl = layer_rsrc(0);
+  conv.head(pconv, rl, 0, rl, o_cb);
+  int par = 0;  // buffer holding the current layer's operands
 
   for (int s = 0; s < a.n_steps; ++s) {
-    // ---- current input (h^0_e) is ins[]: set before the loop and at the end of every step
-    // ---- embedding: a row gather of the transposed 1x1 convolution
-    for (int i = tid; i < RPW * C; i += kThreads) {
-      const int r = i / C, c = i % C;
-      const float v = WTraits<WT>::load1(a.embed, (long long)ins[r] * C + c) + bias_or0(a.embed_b, c);
-      xf[i] = v;
-      xo[i] = WTraits<WT>::opnd(v);
+    // ---- current input (h^0_e): a row gather of the transposed 1x1 convolution
+    const int tok = ins[0];
+    for (int c = tid; c < C; c += NT) {
+      const float v = WTraits<WT>::load1(a.embed, (long long)tok * C + c) + bias_or0(a.embed_b, c);
+      xf[c] = v;
+      vbuf(par)[XO + c] = WTraits<WT>::opnd(v);
     }
-    if (kind == 2)
-      for (int i = tid; i < RPW * S; i += kThreads) so[i] = 0.f;
+    if constexpr (GATED)
+      for (int i = tid; i < S; i += NT) so[i] = 0.f;
     __syncthreads();
 
     for (int l = 0; l < L; ++l) {
@@ -295,64 +311,60 @@ __global__ void __launch_bounds__(kThreads) valu_step_kernel(StepArgs a) {
       const int nl = l + 1 < L ? l + 1 : 0;
       int nslot = slots[nl];
       if (l + 1 == L) nslot = nslot + 1 == ltab[0].depth ? 0 : nslot + 1;
+      const float *vo = vbuf(par);
+      float *xn = vbuf(par ^ 1) + XO;  // the layer's output: the current input of the next one
       // with one layer, the next step's pops include the state this layer pushes now: fetch after it
-      if (more && L > 1) fetch(nl, nslot, par ^ 1);
+      if (more && L > 1) fetch(nl, nslot);
       // ---- push phase for this queue: the layer's input x^{l-1}_t replaces the oldest state,
       // whose pop has landed in LDS already
-      const long long qbase = ld.ring_off + (long long)slots[l] * a.bmax * C;
-      for (int i = tid; i < RPW * C; i += kThreads) {
-        const int r = i / C, c = i % C;
-        if (r < nrows) WTraits<WT>::store1(a.ring, qbase + (long long)(b0 + r) * C + c, xo[i]);
-      }
+      char *qrow = uniform_ptr((char *)a.ring + (ld.ring_off + ((long long)slots[l] * a.bmax + b) * C) * es);
+      for (int c = tid; c < C; c += NT) WTraits<WT>::store1(qrow, c, vo[XO + c]);
       if (more && L == 1) {
         __syncthreads();
-        fetch(nl, nslot, par ^ 1);
+        fetch(nl, nslot);
       }
-      const char *wb = stage ? (const char *)wbuf(par) : (const char *)ld.block;
-      // staged weights and biases through LDS pointers (LDS loads), else global pointers
-      typedef typename std::conditional<STAGE, lds_u4p, glb_u4p>::type WP;
-      typedef typename std::conditional<STAGE, lds_f32p, glb_f32p>::type BP;
-      auto wp = [&](size_t off) { return (WP)(wb + off); };
-      const BP cb = (BP)(wb + o_cb);
-      const float *vo = vbuf(par);
       // ---- dilated convolution of width w: [v_0 .. v_{w-2} x] . [W_0 ; .. ; W_{w-1}]
-      rows_product<WT, RPW, WP>(wp(0), K, Co, vo, (w - 1) * C, xo, C, (w - 1) * C, partA);
-      __syncthreads();
-      if (kind == 2) {
-        const BP rb = (BP)(wb + o_rb), sb = (BP)(wb + o_sb);
+      conv.run(pconv, rl, 0, rl, o_cb, vo, partA);
+      if constexpr (GATED) {
+        Flight<WT, NT> res, skip;
+        res.head(pres, rl, o_res, rl, o_rb);
+        skip.head(pskip, rl, o_skip, rl, o_sb);
+        __syncthreads();
         // gate: z = tanh(a[0:R]) * sigmoid(a[R:2R])
-        for (int i = tid; i < RPW * C; i += kThreads) {
-          const int r = i / C, c = i % C;
-          const float af = cb[c] + part_sum<RPW>(partA, Co, r, c);
-          const float ag = cb[C + c] + part_sum<RPW>(partA, Co, r, C + c);
+        for (int c = tid; c < C; c += NT) {
+          const float af = part_sum<NT>(partA, Co, c), ag = part_sum<NT>(partA, Co, C + c);
           // tanh(a) = 1 - 2 / (e^{2a} + 1) and sigmoid(g) = 1 / (1 + e^{-g}), one exp and one
           // reciprocal each (absolute error ~1e-7, saturating correctly at both ends)
           const float z = (1.f - 2.f * __builtin_amdgcn_rcpf(__expf(2.f * af) + 1.f)) *
                           __builtin_amdgcn_rcpf(1.f + __expf(-ag));
-          zo[i] = WTraits<WT>::opnd(z);
+          zo[c] = WTraits<WT>::opnd(z);
         }
         __syncthreads();
         // residual and skip 1x1 products
-        rows_product<WT, RPW, WP>(wp(o_res), C, C, zo, C, zo, C, C, partB);
-        rows_product<WT, RPW, WP>(wp(o_skip), C, S, zo, C, zo, C, C, partA);
+        res.run(pres, rl, o_res, rl, o_rb, zo, partB);
+        skip.run(pskip, rl, o_skip, rl, o_sb, zo, partA);
+        if (more) {
+          rl = layer_rsrc(nl);
+          conv.head(pconv, rl, 0, rl, o_cb);
+        }
         __syncthreads();
-        for (int i = tid; i < RPW * C; i += kThreads) {
-          const int r = i / C, c = i % C;
-          const float v = xf[i] + rb[c] + part_sum<RPW>(partB, C, r, c);
-          xf[i] = v;
-          xo[i] = WTraits<WT>::opnd(v);
+        for (int c = tid; c < C; c += NT) {
+          const float v = xf[c] + part_sum<NT>(partB, C, c);
+          xf[c] = v;
+          xn[c] = WTraits<WT>::opnd(v);
         }
-        for (int i = tid; i < RPW * S; i += kThreads) {
-          const int r = i / S, k = i % S;
-          so[i] += sb[k] + part_sum<RPW>(partA, S, r, k);
-        }
+        for (int k = tid; k < S; k += NT) so[k] += part_sum<NT>(partA, S, k);
       } else {
-        for (int i = tid; i < RPW * C; i += kThreads) {
-          const int r = i / C, c = i % C;
-          const float pre = cb[c] + part_sum<RPW>(partA, Co, r, c);
-          const float v = (kind == 1 ? xf[i] : 0.f) + fmaxf(pre, 0.f);
-          xf[i] = v;
-          xo[i] = WTraits<WT>::opnd(v);
+        if (more) {
+          rl = layer_rsrc(nl);
+          conv.head(pconv, rl, 0, rl, o_cb);
+        }
+        __syncthreads();
+        for (int c = tid; c < C; c += NT) {
+          const float pre = part_sum<NT>(partA, Co, c);
+          const float v = (kind == 1 ? xf[c] : 0.f) + fmaxf(pre, 0.f);
+          xf[c] = v;
+          xn[c] = WTraits<WT>::opnd(v);
         }
       }
       if (more) land(par ^ 1);
@@ -360,125 +372,73 @@ __global__ void __launch_bounds__(kThreads) valu_step_kernel(StepArgs a) {
       par ^= 1;
     }
 
-    // ---- output head
-    const float *top = xo;
-    int Ktop = C;
-    if (kind == 2) {
-      for (int i = tid; i < RPW * S; i += kThreads) ho[i] = WTraits<WT>::opnd(fmaxf(so[i], 0.f));
+    // ---- output head (the top layer's output sits where layer 0's next input will)
+    Flight<WT, NT> top;
+    const float *x = vbuf(par) + XO;
+    const Rsrc ro = rsrc(a.out, (uint32_t)Ktop * Q * es), rob = rsrc(a.out_b, Q * 4);
+    if constexpr (GATED) {
+      const Rsrc rh = rsrc(a.head, (uint32_t)S * H * es), rhb = rsrc(a.head_b, H * 4);
+      top.head(phead, rh, 0, rhb, 0);
+      for (int i = tid; i < S; i += NT) so[i] = WTraits<WT>::opnd(fmaxf(so[i], 0.f));
       __syncthreads();
-      rows_product<WT, RPW, glb_u4p>((glb_u4p)a.head, S, H, ho, S, ho, S, S, partA);
+      top.run(phead, rh, 0, rhb, 0, so, partA);
+      top.head(pout, ro, 0, rob, 0);
       __syncthreads();
-      for (int i = tid; i < RPW * H; i += kThreads) {
-        const int r = i / H, n = i % H;
-        h2[i] = WTraits<WT>::opnd(fmaxf(bias_or0(a.head_b, n) + part_sum<RPW>(partA, H, r, n), 0.f));
-      }
+      for (int n = tid; n < H; n += NT) h2[n] = WTraits<WT>::opnd(fmaxf(part_sum<NT>(partA, H, n), 0.f));
       __syncthreads();
-      top = h2;
-      Ktop = H;
+      x = h2;
+    } else {
+      top.head(pout, ro, 0, rob, 0);
     }
-    rows_product<WT, RPW, glb_u4p>((glb_u4p)a.out, Ktop, Q, top, Ktop, top, Ktop, Ktop, partA);
+    top.run(pout, ro, 0, rob, 0, x, partA);
     __syncthreads();
-    for (int i = tid; i < RPW * Q; i += kThreads) {
-      const int r = i / Q, q = i % Q;
-      lg[i] = bias_or0(a.out_b, q) + part_sum<RPW>(partA, Q, r, q);
-    }
+    if (tid < Q) lg[tid] = part_sum<NT>(partA, Q, tid);
     __syncthreads();
 
     if (a.mode != MODE_GENERATE) {
-      if (a.logits)
-        for (int i = tid; i < nrows * Q; i += kThreads) {
-          const int r = i / Q, q = i % Q;
-          a.logits[((long long)(b0 + r) * a.n_steps + s) * Q + q] = lg[i];
-        }
+      if (a.logits && tid < Q) a.logits[((long long)b * a.n_steps + s) * Q + tid] = lg[tid];
       // the next input: the following element of the forced sequence (teacher forcing), or this
       // step's observed sample (online prediction)
       const int nx = s + forced_shift(a.mode);
-      if (tid < nrows && nx < a.n_steps) ins[tid] = a.inputs[(long long)(b0 + tid) * a.n_steps + nx];
-    } else {
+      if (tid == 0 && nx < a.n_steps) ins[0] = a.inputs[(long long)b * a.n_steps + nx];
+    } else if (tid < 64) {
       // ---- sample and feed back
-      const int wv = tid >> 6;
-      for (int r = wv; r < nrows; r += kThreads / 64) {
-        const float u = a.uniforms[(long long)(b0 + r) * a.n_steps + s];
-        const int k = sample_row_256(lg + r * Q, u);
-        if ((tid & 63) == 0) {
-          a.samples[(long long)(b0 + r) * a.n_steps + s] = k;
-          ins[r] = k;
-        }
+      const float u = a.uniforms[(long long)b * a.n_steps + s];
+      const int k = sample_row_256(lg, u);
+      if (tid == 0) {
+        a.samples[(long long)b * a.n_steps + s] = k;
+        ins[0] = k;
       }
     }
     // ---- advance every queue's slot
-    for (int l = tid; l < L; l += kThreads) {
+    for (int l = tid; l < L; l += NT) {
       const int nx = slots[l] + 1;
       slots[l] = nx == ltab[l].depth ? 0 : nx;
     }
     __syncthreads();
   }
-  if (a.mode != MODE_TEACHER && tid < nrows) a.last[b0 + tid] = ins[tid];
+  if (a.mode != MODE_TEACHER && tid == 0) a.last[b] = ins[0];
 }
 
-template <typename WT, bool STAGE, typename SH>
-static hipError_t launch_valu_t(const StepArgs &a, int rpw, size_t lds, hipStream_t s) {
-  const dim3 grid((a.batch + rpw - 1) / rpw), block(kThreads);
-  switch (rpw) {
-    case 1: hipLaunchKernelGGL((valu_step_kernel<WT, 1, STAGE, SH>), grid, block, lds, s, a); break;
-    case 2: hipLaunchKernelGGL((valu_step_kernel<WT, 2, STAGE, SH>), grid, block, lds, s, a); break;
-    case 4: hipLaunchKernelGGL((valu_step_kernel<WT, 4, STAGE, SH>), grid, block, lds, s, a); break;
-    case 8: hipLaunchKernelGGL((valu_step_kernel<WT, 8, STAGE, SH>), grid, block, lds, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
+typedef void (*ValuKernel)(StepArgs);
+template <typename WT, int NT>
+static ValuKernel valu_kernel_of(int kind, int w) {
+  if (kind == 2) return w == 2 ? valu_step_kernel<WT, NT, true, true> : valu_step_kernel<WT, NT, true, false>;
+  return w == 2 ? valu_step_kernel<WT, NT, false, true> : valu_step_kernel<WT, NT, false, false>;
+}
+static ValuKernel valu_kernel_of(int dtype, int threads, int kind, int w) {
+  if (dtype == 1) return threads == 512 ? valu_kernel_of<uint16_t, 512>(kind, w) : valu_kernel_of<uint16_t, 256>(kind, w);
+  return threads == 512 ? valu_kernel_of<float, 512>(kind, w) : valu_kernel_of<float, 256>(kind, w);
+}
+
+hipError_t launch_valu_step(const StepArgs &a, int threads, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL(valu_kernel_of(a.dtype, threads, a.kind, a.w), dim3(a.batch), dim3(threads), lds, s, a);
   return hipGetLastError();
 }
 
-template <typename WT, typename SH>
-static hipError_t launch_valu_s(const StepArgs &a, int rpw, size_t lds, hipStream_t s) {
-  return a.valu_wbytes > 0 ? launch_valu_t<WT, true, SH>(a, rpw, lds, s) : launch_valu_t<WT, false, SH>(a, rpw, lds, s);
-}
-
-// fp32 shapes with instantiations of their own: gated R = 32, S = H = 256 at widths 2 and 3.  (A
-// 512-channel ReLU + residual instantiation ran 3x slower than the runtime-shaped kernel.)
-typedef ShapeFixed<2, 32, 256, 256, 2> ShapeG32;
-typedef ShapeFixed<2, 32, 256, 256, 3> ShapeG32W3;
-template <typename SH>
-static bool shape_is(const StepArgs &a) {
-  return a.kind == SH::kind && a.C == SH::C && a.S == SH::S && a.H == SH::H && a.Q == SH::Q && a.w == SH::w;
-}
-
-hipError_t launch_valu_step(const StepArgs &a, int rpw, size_t lds, hipStream_t s) {
-  if (a.dtype == 1) return launch_valu_s<uint16_t, ShapeAny>(a, rpw, lds, s);
-  if (shape_is<ShapeG32>(a)) return launch_valu_s<float, ShapeG32>(a, rpw, lds, s);
-  if (shape_is<ShapeG32W3>(a)) return launch_valu_s<float, ShapeG32W3>(a, rpw, lds, s);
-  return launch_valu_s<float, ShapeAny>(a, rpw, lds, s);
-}
-
-template <typename WT, int RPW, typename SH>
-static hipError_t set_lds_sh(size_t bytes) {
-  hipError_t e = hipFuncSetAttribute((const void *)valu_step_kernel<WT, RPW, true, SH>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void *)valu_step_kernel<WT, RPW, false, SH>,
+hipError_t set_valu_lds_limit(int dtype, int threads, int kind, int w, size_t bytes) {
+  return hipFuncSetAttribute((const void *)valu_kernel_of(dtype, threads, kind, w),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-template <typename WT, int RPW>
-static hipError_t set_lds_one(size_t bytes) {
-  hipError_t e = set_lds_sh<WT, RPW, ShapeAny>(bytes);
-  if constexpr (sizeof(WT) == 4) {
-    if (e != hipSuccess) return e;
-    if ((e = set_lds_sh<WT, RPW, ShapeG32>(bytes)) != hipSuccess) return e;
-    e = set_lds_sh<WT, RPW, ShapeG32W3>(bytes);
-  }
-  return e;
-}
-
-hipError_t set_valu_lds_limit(size_t bytes) {
-  hipError_t e;
-  if ((e = set_lds_one<float, 1>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<float, 2>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<float, 4>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<float, 8>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<uint16_t, 1>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<uint16_t, 2>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_one<uint16_t, 4>(bytes)) != hipSuccess) return e;
-  return set_lds_one<uint16_t, 8>(bytes);
 }
 
 // ---------------------------------------------------------------------------

@@ -160,3 +160,38 @@ def test_parallel_head_large_blocks():
     got = fw.teacher_forced_parallel(dev(x)).cpu().numpy()
     sel = [0, 64, 128]
     assert row_rel_err(got[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[W.BF16]
+
+
+# shapes of the general kernel: 512 and 256 threads, several columns per thread (N > 512, N no multiple of
+# the thread count), K-groups with fewer than 8 and more than 8 k-blocks, wide pops, more streams than
+# compute units
+GENERAL = {
+    "gated_f32_r64": (W.ModelConfig(W.GATED, W.F32, 64, (1, 2, 4, 1), 256, 128), 3),
+    "gated_bf16_r64": (W.ModelConfig(W.GATED, W.BF16, 64, (1, 3, 2), 128, 320), 2),
+    "gated_f32_r128": (W.ModelConfig(W.GATED, W.F32, 128, (2, 1), 640, 512), 5),
+    "relu_f32_c320": (W.ModelConfig(W.RELU, W.F32, 320, (1, 2)), 2),
+    "relures_bf16_c576": (W.ModelConfig(W.RELU_RESIDUAL, W.BF16, 576, (1, 2, 3)), 2),
+    "relu_f32_c256_l1": (W.ModelConfig(W.RELU, W.F32, 256, (3,)), 1),
+    "relures_f32_c128_w5": (W.ModelConfig(W.RELU_RESIDUAL, W.F32, 128, (1, 2, 1), filter_width=5), 2),
+    "gated_f32_r64_b300": (W.ModelConfig(W.GATED, W.F32, 64, (1, 2), 64, 64), 300),
+}
+
+
+@pytest.mark.parametrize("name", list(GENERAL))
+def test_general_kernel_shapes(name):
+    """Teacher forcing through the step kernel against the oracle (sampled streams), and the state
+    carried across calls: online prediction in two pieces equals one, bit by bit."""
+    cfg, B = GENERAL[name]
+    w = W.make_weights(cfg, 80, bias_scale=0.1)
+    fw = model(cfg, w, B)
+    assert fw.regime == "valu"
+    T = 30
+    x = W.sequences(81, B, T)
+    sel = sorted({0, B // 2, B - 1})
+    got = fw.teacher_forced(dev(x)).cpu().numpy()
+    assert row_rel_err(got[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[cfg.dtype]
+    one = fw.step_forced(dev(x)).cpu().numpy()
+    fw.reset()
+    a = fw.step_forced(dev(x[:, :11])).cpu().numpy()
+    b = fw.step_forced(dev(x[:, 11:])).cpu().numpy()
+    assert np.array_equal(np.concatenate([a, b], axis=1), one)
