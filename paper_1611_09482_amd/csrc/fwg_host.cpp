@@ -398,7 +398,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
       if (gated) p->off_pres[l] = take((size_t)p->C * p->C * p->es);
     }
     if (p->stack_ok) p->off_stack = take(kStackLayerBytes * p->L);
-    p->off_head_pack = p->head_ok ? take(par_head_bytes(p->L)) : 0;
+    p->off_head_pack = p->head_ok ? take(par_head_bytes(p->dtype, p->L)) : 0;
     p->off_pskip = gated ? take((size_t)p->S * p->L * p->C * p->es) : 0;
     p->off_pskip_b = gated ? take(sizeof(float) * p->S) : 0;
     p->off_phead = gated ? take((size_t)p->H * p->S * p->es) : 0;
@@ -754,8 +754,8 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
       g.M = M; g.N = p.Co; g.K = p.w * C;
       g.A = pxb[cur]; g.lda = C;
       g.ring = ring + (size_t)p.ring_off[l] * es;
-      g.t0 = t0; g.dil = h->dil[l]; g.brows = p.brows; g.Tcur = Tcur; g.C = C;
-      g.w = p.w; g.depth = (p.w - 1) * h->dil[l];
+      g.dil = h->dil[l]; g.brows = p.brows; g.Tcur = Tcur; g.C = C;
+      g.w = p.w; g.depth = (p.w - 1) * h->dil[l]; g.t0m = (int)(t0 % g.depth);
       g.W = ws + p.off_pconv[l];
       g.bias = (const float *)(ws + p.off_pconv_b[l]);
       int em = PAR_E_GATE;
@@ -764,6 +764,7 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
         // queue refresh
         if (l > 0) {
           g.qring = ring + (size_t)p.ring_off[l - 1] * es; g.qsrc = pxb[prev]; g.qdepth = (p.w - 1) * h->dil[l - 1];
+          g.qlo = (int)((t0 + std::max(0, Tcur - g.qdepth)) % g.qdepth);
         }
         g.zout = ws + p.off_pz; g.ldz = (long long)L * C; g.zoff = l * C;
         g.W2 = ws + p.off_pres[l];
@@ -805,7 +806,7 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
       k.logits = logits; k.n_steps = n; k.s0 = s0;
       // 64-row blocks while they fill at most one per compute unit (16,384 rows: 45 us against 66 with
       // 128-row ones; from 24,576 rows on 128 is the faster: 71 against 74 us, at 65,536 178 against 246)
-      HIP_TRY(launch_par_head(k, M <= 64 * 256 ? 64 : 128, s));
+      HIP_TRY(launch_par_head(k, p.dtype, M <= 64 * 256 ? 64 : 128, s));
       continue;
     }
     ParGemm o;
@@ -981,8 +982,8 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
     TRY_OR_FREE(set_par_stack_lds_limit(p.L));
   }
   if (p.head_ok) {
-    for (int l = 0; l < p.L; ++l) TRY_OR_FREE(launch_par_head_pack_skip(w->skip[l], l, p.L, ws + p.off_head_pack, s));
-    TRY_OR_FREE(launch_par_head_pack(w->head, w->out, p.L, ws + p.off_head_pack, s));
+    for (int l = 0; l < p.L; ++l) TRY_OR_FREE(launch_par_head_pack_skip(w->skip[l], dt, l, p.L, ws + p.off_head_pack, s));
+    TRY_OR_FREE(launch_par_head_pack(w->head, w->out, dt, p.L, ws + p.off_head_pack, s));
     TRY_OR_FREE(set_par_head_lds_limit());
   }
   if (p.par_ok) {

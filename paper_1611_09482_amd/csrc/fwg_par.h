@@ -13,7 +13,7 @@ struct ParGemm {
   const void *A;           // plain: operand rows with stride lda; conv: the layer input rows (stride C)
   long long lda;
   const void *ring;        // conv: this layer's queue, [depth][brows][C] operand-typed
-  long long t0;            // time of row j = 0
+  int t0m;                 // conv: time of row j = 0, mod depth
   int dil, brows, Tcur, C;
   int w, depth;            // conv / tree: taps (K = w C) and queue slots ((w - 1) dil)
   const void *W;
@@ -39,11 +39,12 @@ struct ParGemm {
   void *zout;
   long long ldz;
   // fused gated layer: the previous layer's queue refresh rides along (qring NULL: none).  Row m =
-  // b * Tcur + j of qsrc (the previous layer's input rows, C operands each) goes to slot
-  // (t0 + j) mod qdepth, stream b, of qring when it is among the chunk's last qdepth steps.
+  // b * Tcur + j of qsrc (the previous layer's input rows, C operands each) goes to the slot of its
+  // time (mod qdepth), stream b, of qring when it is among the chunk's last qdepth steps (the first of
+  // those goes to slot qlo).
   void *qring;
   const void *qsrc;
-  int qdepth;
+  int qdepth, qlo;
 };
 struct ParEmbed {
   int M, C, Tcur, mode;
@@ -99,10 +100,11 @@ hipError_t set_par_stack_lds_limit(int L);
 hipError_t launch_par_stack(const ParStack &g, int batch, hipStream_t s);
 hipError_t launch_par_stack_pack(const void *conv, const void *res, const float *conv_b, const float *res_b, void *dst,
                                  hipStream_t s);
-// The head of a gated bf16 chunk (R = 64, S = H = 512, 256 classes) in one kernel: z rows to logits.
+// The head of a gated chunk (bf16 with R = 64, S = H = 512, or float32 with R = 32, S = H = 256; 256
+// classes) in one kernel: z rows to logits.
 struct ParHead {
   int M, L, Tcur;
-  const void *z;           // [M][ldz] bf16, layer l's R values at column l R
+  const void *z;           // [M][ldz] operands, layer l's R values at column l R
   long long ldz;
   const void *packed;      // launch_par_head_pack_skip (every layer) and launch_par_head_pack
   const float *skip_b, *head_b, *out_b;  // summed skip biases [S], [H], [Q]
@@ -110,11 +112,11 @@ struct ParHead {
   long long n_steps, s0;
 };
 bool par_head_ok(int kind, int dtype, int C, int S, int H, int Q);
-size_t par_head_bytes(int L);
+size_t par_head_bytes(int dtype, int L);
 hipError_t set_par_head_lds_limit();
-hipError_t launch_par_head(const ParHead &g, int rows_per_block, hipStream_t s);  // 64 or 128
-hipError_t launch_par_head_pack_skip(const void *skip, int l, int L, void *packed, hipStream_t s);
-hipError_t launch_par_head_pack(const void *head, const void *out, int L, void *packed, hipStream_t s);
+hipError_t launch_par_head(const ParHead &g, int dtype, int rows_per_block, hipStream_t s);  // 64 or 128
+hipError_t launch_par_head_pack_skip(const void *skip, int dtype, int l, int L, void *packed, hipStream_t s);
+hipError_t launch_par_head_pack(const void *head, const void *out, int dtype, int L, void *packed, hipStream_t s);
 hipError_t launch_par_embed(const ParEmbed &e, int dtype, hipStream_t s);
 hipError_t launch_par_ring(const ParRing &r, hipStream_t s);
 hipError_t launch_par_set_last(const int32_t *inputs, int32_t *last, int batch, int n_steps, hipStream_t s);

@@ -109,31 +109,47 @@ constexpr int A_PLAIN = PAR_A_PLAIN, A_CONV = PAR_A_CONV, A_TREE = PAR_A_TREE;
 constexpr int E_RELU = PAR_E_RELU, E_RELU_RES = PAR_E_RELU_RES, E_RES_ADD = PAR_E_RES_ADD, E_GATE = PAR_E_GATE,
               E_LOGITS = PAR_E_LOGITS;
 
+// One staged row of A: where its operands for the current tap start.  A row's stream and time are decoded
+// once, and its source once per tap (decoded at every k-tile, with 64-bit queue slots, the index
+// arithmetic took about as long as the products).
 template <typename OT, int AM>
-__device__ __forceinline__ uint4 load_a(const ParGemm &g, int m, int k) {
-  if (m >= g.M) return make_uint4(0, 0, 0, 0);
-  if (AM == A_PLAIN) return *(const uint4 *)((const OT *)g.A + (long long)m * g.lda + k);
-  // tap k / C of the width-w dilated product reads the state (w - 1 - tap) d steps back
-  const int tap = k / g.C, kc = k - tap * g.C;
-  const int shift = (g.w - 1 - tap) * g.dil;
-  const int b = m / g.Tcur, j = m - b * g.Tcur;
-  if (AM == A_TREE) {
-    if (g.tnow + g.toff[j] - shift < 0) return make_uint4(0, 0, 0, 0);  // zero padding before time 0
-    const long long row = (long long)b * g.nprev + g.tsrc[tap * g.Tcur + j];
-    return *(const uint4 *)((const OT *)g.A + row * g.C + kc);
+struct ARow {
+  int m, b, j;
+  const OT *src;  // NULL: zeros
+  __device__ __forceinline__ void init(const ParGemm &g, int m_) {
+    m = m_;
+    b = j = 0;
+    src = nullptr;
+    if (m >= g.M) return;
+    if (AM == A_PLAIN) {
+      src = (const OT *)g.A + (long long)m * g.lda;
+      return;
+    }
+    b = m / g.Tcur;
+    j = m - b * g.Tcur;
+    tap(g, 0);
   }
-  // dilated convolution over the chunk: the row `shift` steps back, or, before the chunk, the queue
-  // slot of that time (depth = (w - 1) d slots, slot = time mod depth)
-  const OT *src;
-  if (j >= shift) {
-    src = (const OT *)g.A + (long long)(m - shift) * g.C + kc;
-  } else {
-    const long long tau = g.t0 + j - shift;  // >= -depth: before time 0 the slot holds zeros
-    const long long slot = tau >= 0 ? tau % g.depth : tau + g.depth;
-    src = (const OT *)g.ring + (slot * g.brows + b) * (long long)g.C + kc;
+  // tap t of the width-w dilated product reads the state (w - 1 - t) d steps back
+  __device__ __forceinline__ void tap(const ParGemm &g, int t) {
+    if (AM == A_PLAIN || m >= g.M) return;
+    const int shift = (g.w - 1 - t) * g.dil;
+    if (AM == A_TREE) {
+      // zero padding before time 0
+      src = g.tnow + g.toff[j] - shift < 0 ? nullptr
+                                           : (const OT *)g.A + ((long long)b * g.nprev + g.tsrc[t * g.Tcur + j]) * g.C;
+    } else if (j >= shift) {
+      src = (const OT *)g.A + (long long)(m - shift) * g.C;  // the chunk's row `shift` steps back
+    } else {
+      // before the chunk: the queue slot of that time (slot = time mod depth; zeros before time 0)
+      int slot = g.t0m + j - shift;
+      slot = slot < 0 ? slot + g.depth : slot;
+      src = (const OT *)g.ring + ((long long)slot * g.brows + b) * (long long)g.C;
+    }
   }
-  return *(const uint4 *)src;
-}
+  __device__ __forceinline__ uint4 load(int k) const {
+    return src ? *(const uint4 *)(src + k) : make_uint4(0, 0, 0, 0);
+  }
+};
 
 template <typename OT>
 __device__ __forceinline__ uint4 load_w(const ParGemm &g, int n, int k) {
@@ -164,11 +180,14 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
 
   const int nk = g.K / KT;
   uint4 ra[MT], rb[MT];
+  ARow<OT, AM> row[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    ra[i] = load_a<OT, AM>(g, m0 + sr + 32 * i, sq * EPC);
+    row[i].init(g, m0 + sr + 32 * i);
+    ra[i] = row[i].load(sq * EPC);
     rb[i] = load_w<OT>(g, n0 + sr + 32 * i, sq * EPC);
   }
+  int kc = 0, tap = 0;  // the next tile's column inside its tap (C is a multiple of KT)
   const int lr = lane & 15, lg = lane >> 4;
   for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
@@ -179,9 +198,16 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
     __syncthreads();
     if (kt + 1 < nk) {
       const int k = (kt + 1) * KT + sq * EPC;
+      kc += KT;
+      if (AM != A_PLAIN && kc == g.C) {
+        kc = 0;
+        ++tap;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) row[i].tap(g, tap);
+      }
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
-        ra[i] = load_a<OT, AM>(g, m0 + sr + 32 * i, k);
+        ra[i] = row[i].load(kc + sq * EPC);
         rb[i] = load_w<OT>(g, n0 + sr + 32 * i, k);
       }
     }
@@ -228,6 +254,29 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
     }
     return;
   }
+  if (EM == E_LOGITS) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int mb = m0 + TW * wm + 16 * i + 4 * lg;
+      int b = mb / g.Tcur, jj = mb - b * g.Tcur;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (mb + e < g.M) {
+          float *dst = g.logits + ((long long)b * g.n_steps + g.s0 + jj) * g.N;
+#pragma unroll
+          for (int j = 0; j < MT; ++j) {
+            const int n = n0 + TW * wn + 16 * j + lr;
+            if (n < g.N) dst[n] = acc[i][j][e] + g.bias[n];
+          }
+        }
+        if (++jj == g.Tcur) {
+          jj = 0;
+          ++b;
+        }
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < MT; ++j) {
     const int n = n0 + TW * wn + 16 * j + lr;
@@ -242,7 +291,7 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
         const float v = acc[i][j][e] + bn;
         if (EM == E_RELU) {
           Op<OT>::put(g.oout, (long long)m * g.ldo + n, fmaxf(v, 0.f));
-        } else if (EM == E_RELU_RES || EM == E_RES_ADD) {
+        } else {  // E_RELU_RES, E_RES_ADD
           const long long at = (long long)m * g.ldo + n;
           long long xr = at;
           if (g.tsrc1) {  // naive tree: x_in is the same-time node of the level below
@@ -252,9 +301,6 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
           const float x = g.xres[xr] + (EM == E_RELU_RES ? fmaxf(v, 0.f) : v);
           g.xout[at] = x;
           if (g.oout) Op<OT>::put(g.oout, at, x);
-        } else {  // E_LOGITS
-          const int b = m / g.Tcur, jj = m - b * g.Tcur;
-          g.logits[((long long)b * g.n_steps + g.s0 + jj) * g.N + n] = v;
         }
       }
   }
@@ -273,10 +319,20 @@ static hipError_t launch_em_t(const ParGemm &g, int em, dim3 grid, hipStream_t s
   return hipGetLastError();
 }
 
-// 128-wide tiles for outputs at least 128 wide over at least 4096 rows, else 64-wide tiles
+// 128-wide tiles for outputs at least 128 wide over at least 4096 rows, else 64-wide tiles.  float32
+// products are bound by the matrix cores at either size (64-wide tiles stage twice the bytes per product
+// but their products are 4x slower than bf16 ones), so they take the tiles whose count fills the compute
+// units more evenly: 10,656 x 512 outputs are 336 large tiles (2 rounds of 256) or 1,336 small ones (6
+// rounds of a quarter), K = 1024: 161 us against 122.
 template <typename OT, int AM>
 static hipError_t launch_em(const ParGemm &g, int em, hipStream_t s) {
-  if (g.N >= 128 && g.M >= 4096) {
+  bool wide = g.N >= 128 && g.M >= 4096;
+  if (sizeof(OT) == 4 && wide) {
+    const long long big = ((g.M + 127) / 128) * (long long)((g.N + 127) / 128);
+    const long long small = ((g.M + 63) / 64) * (long long)((g.N + 63) / 64);
+    wide = (big + 255) / 256 * 4 <= (small + 255) / 256;
+  }
+  if (wide) {
     const dim3 grid((g.M + 127) / 128, (g.N + 127) / 128);
     return launch_em_t<OT, AM, 2>(g, em, grid, s);
   }
@@ -337,9 +393,11 @@ __global__ void __launch_bounds__(NT) par_gated_layer_kernel(ParGemm g) {
       const int r = c / RC, q = c % RC, m = m0 + r;
       if (m >= g.M) break;
       const int b = m / g.Tcur, j = m - b * g.Tcur;
-      if (j < g.Tcur - g.qdepth) continue;
-      const long long slot = (g.t0 + j) % g.qdepth;
-      *(uint4 *)((char *)g.qring + (slot * g.brows + b) * (long long)ZB + 16 * q) =
+      const int lo = max(0, g.Tcur - g.qdepth);
+      if (j < lo) continue;
+      int slot = g.qlo + (j - lo);
+      slot = slot >= g.qdepth ? slot - g.qdepth : slot;
+      *(uint4 *)((char *)g.qring + ((long long)slot * g.brows + b) * (long long)ZB + 16 * q) =
           *(const uint4 *)((const char *)g.qsrc + (long long)m * ZB + 16 * q);
     }
   }
@@ -353,8 +411,13 @@ __global__ void __launch_bounds__(NT) par_gated_layer_kernel(ParGemm g) {
   const int nk = g.K / KT;
   constexpr int WR = CO / 32;  // W staging rows per thread
   uint4 ra[2], rb[WR];
+  ARow<OT, A_CONV> row[2];
+  int kc = 0, tap = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) ra[i] = load_a<OT, A_CONV>(g, m0 + sr + 32 * i, sq * EPC);
+  for (int i = 0; i < 2; ++i) {
+    row[i].init(g, m0 + sr + 32 * i);
+    ra[i] = row[i].load(sq * EPC);
+  }
 #pragma unroll
   for (int i = 0; i < WR; ++i) rb[i] = load_w<OT>(g, sr + 32 * i, sq * EPC);
   for (int kt = 0; kt < nk; ++kt) {
@@ -365,8 +428,15 @@ __global__ void __launch_bounds__(NT) par_gated_layer_kernel(ParGemm g) {
     __syncthreads();
     if (kt + 1 < nk) {
       const int k = (kt + 1) * KT + sq * EPC;
+      kc += KT;
+      if (kc == g.C) {
+        kc = 0;
+        ++tap;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) ra[i] = load_a<OT, A_CONV>(g, m0 + sr + 32 * i, k);
+        for (int i = 0; i < 2; ++i) row[i].tap(g, tap);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) ra[i] = row[i].load(kc + sq * EPC);
 #pragma unroll
       for (int i = 0; i < WR; ++i) rb[i] = load_w<OT>(g, sr + 32 * i, k);
     }
