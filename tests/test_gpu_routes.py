@@ -210,3 +210,21 @@ def test_general_kernel_shapes(name):
     a = fw.step_forced(dev(x[:, :11])).cpu().numpy()
     b = fw.step_forced(dev(x[:, 11:])).cpu().numpy()
     assert np.array_equal(np.concatenate([a, b], axis=1), one)
+
+
+@pytest.mark.parametrize("B", [1, 6])
+@pytest.mark.parametrize("t0", [0, 1, 2, 5, 40])
+def test_wide_state_across_launches(t0, B):
+    """The wide kernel's state pass at launch: nothing written yet, fewer steps than the shortest and
+    the longest dilation, every queue wrapped.  The second launch's logits against the oracle's."""
+    cfg = W.ModelConfig(W.RELU_RESIDUAL, W.F32, 512, (1, 2, 4, 8, 16, 3))
+    w = W.make_weights(cfg, 90, bias_scale=0.1)
+    fw = model(cfg, w, B)
+    assert fw.regime == "wide_f32_c512"
+    x = W.sequences(91, B, t0 + 9)
+    if t0:
+        fw.step_forced(dev(x[:, :t0]))
+    got = fw.step_forced(dev(x[:, t0:])).cpu().numpy()
+    st = oracle.Oracle(w).state(B)
+    want = st.step_forced(x)
+    assert row_rel_err(got, want[:, t0:]) <= TOL[W.F32]
