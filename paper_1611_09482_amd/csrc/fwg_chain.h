@@ -59,7 +59,7 @@ hipError_t launch_chain_gated_pack(const void *embed, const float *embed_b, cons
                                    const float *head_b, const void *out, const float *out_b, int L, int w, bool pair,
                                    const ChainGatedArgs &g, hipStream_t s);
 // Pair variant (two blocks of one XCD per stream, exchanging tagged words; pack with pair = true):
-// LDS bytes of a launch, exchange-region bytes for `batch` streams (zeroed before every launch;
+// LDS bytes of a launch, exchange-region bytes for `batch` streams (tagged words;
 // an abort word, then 736 + 32 L words per stream), grid blocks, set-up (LDS limit; whether every
 // block of a launch of bmax streams can be resident at once) and launch (a.sp_comm, a.sp_sticky).
 size_t chain_pair_lds_bytes(int L);

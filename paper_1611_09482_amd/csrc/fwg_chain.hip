@@ -456,11 +456,9 @@ __device__ __forceinline__ long long lane_i64(long long v, int l) {
 // The chain wave's layer l with its weights in Wc (W_e row chunks, then W_res half-row chunks); the
 // next layer's weights are fetched into Wn first.  x: the layer input in (lane o and o + 32 both
 // hold channel o), the layer output out.  qptr: this step's push address of the layer's queue.
-// zw (pair variant): z of the layer also goes out as 32 tagged words zw[32 l + o].
 __device__ __forceinline__ void chain_gated_layer(const Lay &s, float4 (&Wc)[FCH], float4 (&Wn)[FCH], Rsrc rw,
                                                   int next_off, float *qptr, int l, int L, int par, int step,
-                                                  int lane, float &x, xg::u64 *zw = nullptr,
-                                                  bool local = false) {
+                                                  int lane, float &x) {
   const int o = lane & (R - 1), h = lane >> 5;
   if (lane < R) {
     qptr[o] = x;
@@ -487,7 +485,6 @@ __device__ __forceinline__ void chain_gated_layer(const Lay &s, float4 (&Wc)[FCH
   if (lane < R) s.zrow[l * R + o] = z;
   compiler_fence();
   if (lane == 0) s.fz[l] = step + 1;
-  if (zw != nullptr && lane < R) xg::put_word(zw + l * R + o, __builtin_bit_cast(uint32_t, z), step + 1, local);
   // the residual 1x1 over this half of K, z read back from its row
   const float4 *zr4 = (const float4 *)(s.zrow + l * R + 16 * h);
   float r0 = 0.f, r1 = 0.f;
@@ -843,8 +840,8 @@ __global__ void __launch_bounds__(NT) chain_gated_kernel(StepArgs a, ChainGatedA
 // the classes (thread: one K half of one class row) and in generation the helper publishes its
 // logits.  The chain block samples.
 //
-// Hand-offs are the tagged words of fwg_xchg.h (tag = step index in the launch + 1; zeroed before
-// every launch).  No block overwrites a word before the other has read it: each block's next write
+// Hand-offs are the tagged words of fwg_xchg.h (tags above every earlier launch's, so that only a
+// handle's first launch clears them: a fill before each launch took 4 us of a one-step call's 27.7).  No block overwrites a word before the other has read it: each block's next write
 // of a word depends, through the step's hand-offs, on the other's read of the previous one.  Block i
 // of the launch: XCD slot i mod 8, pair (i / 16) 8 + i mod 8, role (i / 8) mod 2, so a pair's blocks
 // i and i + 8 share an XCD under round-robin dispatch (a launch handshake checks; words go through
@@ -912,6 +909,7 @@ __device__ __forceinline__ float dot32(const float4 (&w)[FZ], const float *row, 
 struct PairX {
   xg::u64 *pw;            // this pair's words
   uint32_t *abort_w, *sticky;
+  uint32_t mark;          // tag of the launch's handshake words and abort mark; step s uses mark + 1 + s
   bool local;             // both blocks on one XCD
 };
 
@@ -945,13 +943,13 @@ __device__ __forceinline__ void pair_head(const PL &s, const float4 (&W1)[PH], c
                                           const PairX &px, const StepArgs &a, int L, int b, int h, int step,
                                           float hbias, float obias) {
   const int tid = threadIdx.x, kh = tid >> 7, t2 = tid & 127;
-  const uint32_t tag = step + 1;
+  const uint32_t tag = px.mark + 1u + (uint32_t)step;
   __syncthreads();  // the helper: every skip channel in LDS
   if (h == 1) {
     xg::put_word(px.pw + pw_s(L) + tid, __builtin_bit_cast(uint32_t, s.srow[tid]), tag, px.local);
   } else {
     uint32_t v[1];
-    xg::wait_words<1, 1>(px.pw + pw_s(L) + tid, tag, v, px.abort_w, px.sticky);
+    xg::wait_words<1, 1>(px.pw + pw_s(L) + tid, tag, v, px.abort_w, px.sticky, px.mark);
     s.srow[tid] = __builtin_bit_cast(float, v[0]);
     __syncthreads();  // relu(skip sum) of all 256 channels
   }
@@ -965,7 +963,7 @@ __device__ __forceinline__ void pair_head(const PL &s, const float4 (&W1)[PH], c
       xg::put_word(px.pw + pw_p(L) + tid, __builtin_bit_cast(uint32_t, pl), tag, px.local);
     } else {
       uint32_t v[1];
-      xg::wait_words<1, 1>(px.pw + pw_p(L) + tid, tag, v, px.abort_w, px.sticky);
+      xg::wait_words<1, 1>(px.pw + pw_p(L) + tid, tag, v, px.abort_w, px.sticky, px.mark);
       const float lv = pl + __builtin_bit_cast(float, v[0]) + obias;
       s.lrow[tid] = lv;
       if (a.mode != MODE_GENERATE && a.logits) a.logits[((long long)b * a.n_steps + step) * Q + tid] = lv;
@@ -979,7 +977,7 @@ __device__ __forceinline__ void pair_head(const PL &s, const float4 (&W1)[PH], c
     xg::put_word(px.pw + pw_h(L, h) + tid, __builtin_bit_cast(uint32_t, hv), tag, px.local);
   } else {
     uint32_t v[1];
-    xg::wait_words<1, 1>(px.pw + pw_h(L, 1 - h) + t2, tag, v, px.abort_w, px.sticky);
+    xg::wait_words<1, 1>(px.pw + pw_h(L, 1 - h) + t2, tag, v, px.abort_w, px.sticky, px.mark);
     s.hrow[128 * (1 - h) + t2] = __builtin_bit_cast(float, v[0]);
   }
   __syncthreads();  // the hidden layer
@@ -995,7 +993,7 @@ __device__ __forceinline__ void pair_head(const PL &s, const float4 (&W1)[PH], c
     }
   } else if (h == 0 && a.mode == MODE_GENERATE) {
     uint32_t v[1];
-    xg::wait_words<1, 1>(px.pw + pw_l(L) + t2, tag, v, px.abort_w, px.sticky);
+    xg::wait_words<1, 1>(px.pw + pw_l(L) + t2, tag, v, px.abort_w, px.sticky, px.mark);
     s.lrow[128 + t2] = __builtin_bit_cast(float, v[0]);
   }
   __syncthreads();  // the chain block has every logit in generation
@@ -1015,19 +1013,20 @@ __global__ void __launch_bounds__(NT) chain_pair_kernel(StepArgs a, ChainGatedAr
   px.pw = (xg::u64 *)((char *)a.sp_comm + 256) + (size_t)b * pair_words(L);
   px.abort_w = (uint32_t *)a.sp_comm;
   px.sticky = a.sp_sticky;
+  px.mark = a.sp_tag0 + 1u;
 
   // ---- launch handshake: both blocks report their XCD; the chain block tells the helper whether
   // they share one
   if (tid == 0) {
-    xg::put_word(px.pw + PW_HS + 32 * h, xg::xcd_id(), 1, false);
+    xg::put_word(px.pw + PW_HS + 32 * h, xg::xcd_id(), px.mark, false);
     uint32_t v[1];
     if (h == 0) {
-      xg::wait_words<1, 1>(px.pw + PW_HS + 32, 1, v, px.abort_w, px.sticky);
+      xg::wait_words<1, 1>(px.pw + PW_HS + 32, px.mark, v, px.abort_w, px.sticky, px.mark);
       const uint32_t loc = v[0] == xg::xcd_id() ? 1u : 0u;
-      xg::put_word(px.pw + PW_HS + 64, loc, 1, false);
+      xg::put_word(px.pw + PW_HS + 64, loc, px.mark, false);
       *s.mode = (int)loc;
     } else {
-      xg::wait_words<1, 1>(px.pw + PW_HS + 64, 1, v, px.abort_w, px.sticky);
+      xg::wait_words<1, 1>(px.pw + PW_HS + 64, px.mark, v, px.abort_w, px.sticky, px.mark);
       *s.mode = (int)v[0];
     }
   }
@@ -1147,7 +1146,8 @@ __global__ void __launch_bounds__(NT) chain_pair_kernel(StepArgs a, ChainGatedAr
             if (wave == 0) {
               if (lane < R) {
                 uint32_t v[1];
-                xg::wait_words<1, 1>(px.pw + PW_Z + le * R + lane, step + 1, v, px.abort_w, px.sticky);
+                xg::wait_words<1, 1>(px.pw + PW_Z + le * R + lane, px.mark + 1u + (uint32_t)step, v, px.abort_w, px.sticky,
+                                     px.mark);
                 s.zrow[le * R + lane] = __builtin_bit_cast(float, v[0]);
               }
               compiler_fence();
@@ -1194,7 +1194,8 @@ __global__ void __launch_bounds__(NT) chain_pair_kernel(StepArgs a, ChainGatedAr
             if (lane < R) s.zrow[le * R + o] = z;
             compiler_fence();
             if (lane == 0) s.fz[le] = step + 1;
-            if (lane < R) xg::put_word(px.pw + PW_Z + le * R + o, __builtin_bit_cast(uint32_t, z), step + 1, px.local);
+            if (lane < R) xg::put_word(px.pw + PW_Z + le * R + o, __builtin_bit_cast(uint32_t, z),
+                                          px.mark + 1u + (uint32_t)step, px.local);
             // the next layer's weights, fetched once this layer's result is out
             load_chunks(Wn, rw, lane * 16, o_m + (le + 1 < L ? le + 1 : 0) * lstr, 1024);
           }

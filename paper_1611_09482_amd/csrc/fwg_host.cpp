@@ -445,7 +445,7 @@ struct fwg_handle {
   long long nv_t;   // naive generator: its own time and batch binding (its state is the input history)
   int nv_bound_batch;
   void *static_scratch;  // split family: this device's static exchange-word array (fwg_generate_noalloc)
-  // split family, the workspace's exchange words: the next launch's tag base (every tag written since
+  // families with exchange words, those in the workspace: the next launch's tag base (every tag written since
   // the region was last zeroed is at most this), and whether the region has been zeroed since create
   uint32_t sp_tag = 0;
   bool sp_comm_zeroed = false;
@@ -597,6 +597,36 @@ bool capturing(hipStream_t s) {
   return s && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
 }
 
+// Sets a launch's tag base (b->sp_tag0) and clears its exchange words (b->sp_comm) where that is due.
+// Tags are never reused between two zero fills of the words (a fill kernel, no memset node).  The
+// static array of fwg_generate_noalloc is shared by every handle on the device: it is zeroed before
+// every launch (the `launch_bytes` this launch uses), whose tags then start at 1.  The workspace's
+// region belongs to this handle: zeroed whole (`all_bytes`: what the handle's largest batch uses, since
+// a later call may use more than this one) before its first launch and when the tags would wrap; every
+// launch takes the tags above the previous launch's (handshake base + 1, step s base + 2 + s).  A launch
+// recorded into a graph clears the words itself and starts its tags at 1, since every replay writes the
+// same ones.
+hipError_t exchange_words(fwg_handle *h, StepArgs *b, bool shared, size_t launch_bytes, size_t all_bytes) {
+  const uint32_t need = (uint32_t)b->n_steps + 2u;
+  const bool graph = !shared && capturing(h->stream);
+  if (shared || graph || !h->sp_comm_zeroed || h->sp_tag > 0xFFFFFFFFu - need) {
+    const hipError_t e = launch_fill_zero(b->sp_comm, shared ? launch_bytes : all_bytes, h->stream);
+    if (e != hipSuccess) return e;
+    if (!shared && !graph) {
+      h->sp_comm_zeroed = true;
+      h->sp_tag = h->sp_graph_tag;
+    }
+  }
+  b->sp_tag0 = shared || graph ? 0u : h->sp_tag;
+  if (graph) {
+    h->sp_graph_tag = std::max(h->sp_graph_tag, need - 1u);
+    h->sp_tag = std::max(h->sp_tag, h->sp_graph_tag);
+  } else if (!shared) {
+    h->sp_tag += need - 1u;
+  }
+  return hipSuccess;
+}
+
 // One step-kernel launch of the handle's kernel family.  comm: where the split family's exchange
 // words go (NULL: the workspace's region).
 hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
@@ -608,33 +638,9 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       b.sp_nb = (a.batch + kMfRows - 1) / kMfRows;
       b.sp_comm = comm ? comm : h->ws + p.off_comm;
       b.sp_sticky = (uint32_t *)(h->ws + p.off_sticky);
-      // Tags are never reused between two zero fills of the exchange words (a fill kernel, no memset
-      // node).  The static array of fwg_generate_noalloc is shared by every handle on the device: it
-      // is zeroed before every launch (this launch's groups), whose tags then start at 1.  The
-      // workspace's region belongs to this handle: zeroed whole (every group the handle's largest
-      // batch uses, since a later call may use more groups than this one) before its first launch
-      // and when the tags would wrap; every launch takes the tags above the previous launch's
-      // (handshake base + 1, step s base + 2 + s).
-      // A launch recorded into a graph clears the words itself and starts its tags at 1, since every
-      // replay writes the same ones.
-      const uint32_t need = (uint32_t)a.n_steps + 2u;
-      const bool graph = !comm && capturing(h->stream);
-      if (comm || graph || !h->sp_comm_zeroed || h->sp_tag > 0xFFFFFFFFu - need) {
-        const size_t bytes = split_comm_bytes(p.L, comm ? b.sp_nb : p.brows / kMfRows);
-        hipError_t e = launch_fill_zero(b.sp_comm, bytes, h->stream);
-        if (e != hipSuccess) return e;
-        if (!comm && !graph) {
-          h->sp_comm_zeroed = true;
-          h->sp_tag = h->sp_graph_tag;
-        }
-      }
-      b.sp_tag0 = comm || graph ? 0u : h->sp_tag;
-      if (graph) {
-        h->sp_graph_tag = std::max(h->sp_graph_tag, need - 1u);
-        h->sp_tag = std::max(h->sp_tag, h->sp_graph_tag);
-      } else if (!comm) {
-        h->sp_tag += need - 1u;
-      }
+      const hipError_t e = exchange_words(h, &b, comm != nullptr, split_comm_bytes(p.L, b.sp_nb),
+                                          split_comm_bytes(p.L, p.brows / kMfRows));
+      if (e != hipSuccess) return e;
       return launch_split_step(b, h->stream);
     }
     case REGIME_WIDE: {
@@ -642,8 +648,7 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       b.sp_nb = (a.batch + kWideStreams - 1) / kWideStreams;
       b.sp_comm = comm ? comm : h->ws + p.off_comm;
       b.sp_sticky = (uint32_t *)(h->ws + p.off_sticky);
-      // tags restart at 1 every launch: clear the exchange words first (a fill kernel, no memset node)
-      hipError_t e = launch_fill_zero(b.sp_comm, p.wide_comm, h->stream);
+      const hipError_t e = exchange_words(h, &b, comm != nullptr, p.wide_comm, p.wide_comm);
       if (e != hipSuccess) return e;
       WideArgs g = p.wide;
       g.wl = h->ws + p.off_wl;
@@ -665,8 +670,8 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       StepArgs b = a;
       b.sp_comm = comm ? comm : h->ws + p.off_comm;
       b.sp_sticky = (uint32_t *)(h->ws + p.off_sticky);
-      // tags restart at 1 every launch: clear the exchange words first (a fill kernel, no memset node)
-      hipError_t e = launch_fill_zero(b.sp_comm, chain_pair_comm_bytes(p.L, a.batch), h->stream);
+      const hipError_t e = exchange_words(h, &b, comm != nullptr, chain_pair_comm_bytes(p.L, a.batch),
+                                          chain_pair_comm_bytes(p.L, p.bmax));
       if (e != hipSuccess) return e;
       return launch_chain_pair_step(b, chain_gated_arrays(h->ws + p.off_cg, p.L, p.w), p.cp_lds, h->stream);
     }
@@ -1028,16 +1033,21 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
     TRY_OR_FREE(split_setup(p.L, p.w, p.brows / kMfRows, &coresident));
     if (!coresident) h->plan.regime = REGIME_MFMA;  // same workspace layout
   }
-  if (h->plan.regime == REGIME_SPLIT) {
-    // set-up of fwg_generate_noalloc: this device's static exchange-word array, looked up once
-    TRY_OR_FREE(split_static_scratch(&h->static_scratch));
+  if (fwg_waits(h)) {
     // test hook: the workspace's exchange words zeroed now and the tag base started at the given
     // value (e.g. just below the 32-bit wrap, so that later launches cross it)
     if (const char *tb = getenv("FWG_SPLIT_TAG_BASE")) {
-      TRY_OR_FREE(launch_fill_zero(ws + p.off_comm, split_comm_bytes(p.L, p.brows / kMfRows), s));
+      const size_t bytes = h->plan.regime == REGIME_SPLIT  ? split_comm_bytes(p.L, p.brows / kMfRows)
+                           : h->plan.regime == REGIME_WIDE ? p.wide_comm
+                                                           : chain_pair_comm_bytes(p.L, p.bmax);
+      TRY_OR_FREE(launch_fill_zero(ws + p.off_comm, bytes, s));
       h->sp_comm_zeroed = true;
       h->sp_tag = (uint32_t)strtoul(tb, nullptr, 0);
     }
+  }
+  if (h->plan.regime == REGIME_SPLIT) {
+    // set-up of fwg_generate_noalloc: this device's static exchange-word array, looked up once
+    TRY_OR_FREE(split_static_scratch(&h->static_scratch));
     char *frags = ws + p.off_frags;
     for (int l = 0; l < p.L; ++l)
       TRY_OR_FREE(launch_split_repack_layer(w->conv[l], w->res[l], w->skip[l], l, p.L, p.w, frags, s));

@@ -250,20 +250,21 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
   }
   // ---- launch handshake: every block reports its XCD; block 0 tells the group whether all share one
   u64 *hs = g_hs(a.sp_comm, L, g);
+  const uint32_t mark = a.sp_tag0 + 1u;  // tag of the handshake words and the abort mark; step s: mark + 1 + s
   if (tid == 0) {
-    put_word(hs + HSLOT * j, xcd_id(), 1, false);
+    put_word(hs + HSLOT * j, xcd_id(), mark, false);
     uint32_t v[1];
     if (j == 0) {
       bool local = true;
       const uint32_t mine = xcd_id();
       for (int jb = 0; jb < NBG; ++jb) {
-        wait_words<1>(hs + HSLOT * jb, 1, v, abort_word, sticky);
+        wait_words<1>(hs + HSLOT * jb, mark, v, abort_word, sticky, mark);
         local = local && v[0] == mine;
       }
-      put_word(hs + HSLOT * NBG, local ? 1u : 0u, 1, false);
+      put_word(hs + HSLOT * NBG, local ? 1u : 0u, mark, false);
       s.mode = local ? 1 : 0;
     } else {
-      wait_words<1>(hs + HSLOT * NBG, 1, v, abort_word, sticky);
+      wait_words<1>(hs + HSLOT * NBG, mark, v, abort_word, sticky, mark);
       s.mode = (int)v[0];
     }
   }
@@ -415,7 +416,7 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
   const float *embT = w.embT, *embb = w.embb, *outb = w.outb;
   long long k = 0;  // chunk of the launch the compute waves take next
   for (int step = 0; step < a.n_steps; ++step) {
-    const uint32_t tag = (uint32_t)(step + 1);
+    const uint32_t tag = mark + 1u + (uint32_t)step;
     // ---- layer input x^0 (the embedding of the step's inputs), all 512 channels
     for (int e = tid; e < SG * C; e += NT) {
       const int st = e / C, c = e % C;
@@ -467,7 +468,7 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
       // gather the whole layer output into the other buffer (this block's own slice included)
       {
         uint32_t v[8];
-        wait_words<8, NT>(g_x(a.sp_comm, L, g, l) + tid, tag, v, abort_word, sticky);
+        wait_words<8, NT>(g_x(a.sp_comm, L, g, l) + tid, tag, v, abort_word, sticky, mark);
 #pragma unroll
         for (int ee = 0; ee < 8; ++ee) {
           const int wi = ee * NT + tid, jb = wi / (OC * SG), rr = wi % (OC * SG), st = rr / OC, ch = 16 * jb + rr % OC;
@@ -533,7 +534,7 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
     if (j < SG && wave == 0) {
       uint32_t v[4];
       const u64 *src = g_lg(a.sp_comm, L, g) + (lane >> 1) * QB * SG + j * QB + 4 * (lane & 1);
-      wait_words<4>(src, tag, v, abort_word, sticky);
+      wait_words<4>(src, tag, v, abort_word, sticky, mark);
       uint32_t res = 0u;
       if (a.mode == MODE_GENERATE) {
         const float4 lg4 = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]),
@@ -547,7 +548,7 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
     // ---- the step's samples (step-done marks in forced modes) from the group's sampler blocks
     if (tid < SG) {
       uint32_t v[1];
-      wait_words<1>(g_smp(a.sp_comm, L, g) + HSLOT * tid, tag, v, abort_word, sticky);
+      wait_words<1>(g_smp(a.sp_comm, L, g) + HSLOT * tid, tag, v, abort_word, sticky, mark);
       s.in[tid] = a.mode == MODE_GENERATE ? (int)v[0] : s.fin[(step / KCH) & 1][step % KCH][tid];
     }
     // slot advance, then staging of the next chunk (every forced input before it is used)

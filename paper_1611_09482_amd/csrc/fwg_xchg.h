@@ -45,8 +45,8 @@ __device__ __forceinline__ uint32_t get_flag(const uint32_t *p) {
   return __hip_atomic_load((uint32_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // A wait ran out: end every other wait of the launch, and leave a sticky mark for the host.  `mark`
-// identifies the launch (families that zero the region before every launch use 1).
-__device__ __forceinline__ void raise_abort(uint32_t *abort_word, uint32_t *sticky, uint32_t mark = 1u) {
+// identifies the launch.
+__device__ __forceinline__ void raise_abort(uint32_t *abort_word, uint32_t *sticky, uint32_t mark) {
   __hip_atomic_store(abort_word, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(sticky, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -59,7 +59,7 @@ __device__ __forceinline__ void raise_abort(uint32_t *abort_word, uint32_t *stic
 // the tile gathers 2-3x slower.
 template <int N, int STRIDE = 1>
 __device__ __forceinline__ void wait_words(const u64 *p, uint32_t tag, uint32_t (&out)[N], uint32_t *abort_word,
-                                           uint32_t *sticky, uint32_t mark = 1u) {
+                                           uint32_t *sticky, uint32_t mark) {
   u64 v[N];
   for (int it = 0;; ++it) {
 #pragma unroll

@@ -228,3 +228,46 @@ def test_wide_state_across_launches(t0, B):
     st = oracle.Oracle(w).state(B)
     want = st.step_forced(x)
     assert row_rel_err(got, want[:, t0:]) <= TOL[W.F32]
+
+
+@pytest.mark.parametrize("name", ["pair", "pair_w3", "wide"])
+def test_exchange_tags_across_launches(name):
+    """The gated chain pair and wide kernels' exchange words are cleared only before a handle's first
+    launch and when the 32-bit tags would wrap: on poisoned memory, a small batch's launch before a
+    larger one, launches that cross the wrap, and graph replays between eager launches give the logits
+    and samples of a fresh handle."""
+    cfg = {"pair": W.ModelConfig(W.GATED, W.F32, 32, (1, 2, 4, 8), 256, 256),
+           "pair_w3": W.ModelConfig(W.GATED, W.F32, 32, (1, 3, 9), 256, 256, filter_width=3),
+           "wide": W.ModelConfig(W.RELU_RESIDUAL, W.F32, 512, (1, 2, 4))}[name]
+    w = W.make_weights(cfg, 95, bias_scale=0.1)
+    B = 11
+    x, u = dev(W.sequences(96, B, 30)), dev(W.uniforms(97, B, 90))
+    ref = model(cfg, w, B)
+    assert ref.lib.fwg_waits(ref.handle) == 1
+    lg = ref.teacher_forced(x).cpu().numpy()
+    want = ref.generate(u).cpu().numpy()
+    words = (ref.ws_bytes + 7) // 8
+    poison = ((torch.arange(words, dtype=torch.int64, device="cuda") % 64 + 1) << 32) | 5
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        clean = binding.from_model(cfg, w, max_batch=B, workspace=poison.view(torch.uint8))
+        clean.generate(u[:3, :10].contiguous())
+        clean.reset()
+        assert np.array_equal(clean.teacher_forced(x).cpu().numpy(), lg)
+        out = torch.empty((B, 90), dtype=torch.int32, device="cuda")
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            clean.reset()
+            clean.generate(u, out=out, check=False)
+        for _ in range(3):
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want)
+            assert np.array_equal(clean.teacher_forced(x).cpu().numpy(), lg)
+        clean.device_status()
+    wrap = model(cfg, w, B, FWG_SPLIT_TAG_BASE=str(0xFFFFFFFF - 60))
+    got = [wrap.generate(u[:, i:i + 30].contiguous()).cpu().numpy() for i in (0, 30, 60)]
+    assert np.array_equal(np.concatenate(got, axis=1), want)
