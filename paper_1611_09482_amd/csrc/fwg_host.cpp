@@ -248,7 +248,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
   const bool mfma_shape = (w == 2 || w == 3) && p->kind == FWG_GATED && p->dtype == FWG_BF16 && p->C == kMfR &&
                           p->S == kMfS && p->H == kMfH && p->Q == 256 && p->L <= kMfMaxLayers &&
                           mfma_lds_bytes(p->L, w) <= 160 * 1024;
-  // the split family takes the MFMA family's shape from 9 layers on (FWG_REGIME=mfma keeps the
+  // the split family takes the MFMA family's shape from 6 layers on (FWG_REGIME=mfma keeps the
   // single-block kernel); fwg_create falls back to it when the split launch's blocks cannot all be
   // resident at once
   const bool split_shape = mfma_shape && split_layers_ok(p->L) && split_lds_bytes(p->L, w) <= 160 * 1024;

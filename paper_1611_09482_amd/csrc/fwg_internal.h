@@ -90,14 +90,14 @@ __host__ __device__ inline size_t mfma_all_frag_bytes(int L, int w) {
 }
 __host__ __device__ inline size_t mfma_bias_floats(int L) { return (size_t)L * 3 * kMfR + kMfS + kMfH + 256 + kMfR; }
 
-// Split MFMA family (the MFMA family's model shape, filter width 2 or 3, at least 9 layers: a pop is
-// issued 8 layers ahead, and its layer's push of the step before has to be past): per 16 streams one
+// Split MFMA family (the MFMA family's model shape, filter width 2 or 3, at least 6 layers: a pop is
+// issued 5 or more layers ahead, and its layer's push of the step before has to be past): per 16 streams one
 // chain block (the layers), kSpHelpers helper blocks, each owning S / kSpHelpers skip channels and
 // H / kSpHelpers hidden channels, and one class block (output 1x1 and sampling).
 // Fragments per layer of chain waves A and (per popped tap) B, and per layer and helper wave.
 constexpr int kSpHelpers = 8;
 constexpr int kSpFA = 6, kSpFB = 4, kSpFS = 8;
-inline bool split_layers_ok(int L) { return L >= 9; }
+inline bool split_layers_ok(int L) { return L >= 6; }
 size_t split_frag_bytes(int L, int w);
 size_t split_comm_bytes(int L, int nb);
 size_t split_lds_bytes(int L, int w);

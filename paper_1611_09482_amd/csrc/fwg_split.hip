@@ -41,7 +41,7 @@
 //    sigmoid tile p, plus W_r v + b from LDS, the gate, the residual 1x1 for channel tile p;
 //  - wave B (p): W_r v + b of the next layer (v = the popped states, one per tap but the current one,
 //    known early) and the queue
-//    pops of stream rows 4p..4p+3, issued five layers before they land in LDS; between the layer's
+//    pops of stream rows 4p..4p+3, issued up to five layers before they land in LDS; between the layer's
 //    two barriers, while A runs the residual product, the publication of z^l to the helpers and the
 //    push of the layer input.
 // Every chain wave streams its own pre-packed weight fragments from L2 through a ring of registers,
@@ -346,23 +346,24 @@ __device__ __forceinline__ void a_layer(Ctx<TP> &c, int l, int par, u32x4 (&W)[D
 }
 
 // Layer l on wave B, ring slots PBS.. (W_r of the next layer), pop registers rotated by G6, the
-// running layer count mod 6: the pop of running layer index g sits in P[g mod 6] from its issue, five
-// layers ahead of landing, until it lands in vbuf[g mod 3] before the first barrier of layer g - 3,
+// running layer count mod 6: the pop of running layer index g sits in P[g mod 6] from its issue, AH
+// layers ahead of its own (8, or 5 in stacks of 6 to 8 layers, whose pop 8 ahead would come before the
+// push it has to see), until it lands in vbuf[g mod 3] before the first barrier of layer g - 3,
 // four block barriers before its product.  par, v3: the running layer count mod 2 and mod 3.
-template <int PBS, int G6, int TP>
+template <int PBS, int G6, int AH, int TP>
 __device__ __forceinline__ void b_layer(Ctx<TP> &c, int l, int par, int v3, u32x4 (&W)[DB], u32x4 (&P)[6], uint32_t tag) {
   const int L = c.L;
   const int ln = l + 1 < L ? l + 1 : 0;
   // queue offset of the pop issued below, read with the product's LDS reads
-  const int j = l + 8 < L ? l + 8 : l + 8 - L;
-  const uint32_t joff = c.pqoff[(l + 8 < L ? 0 : L) + j];
+  const int j = l + AH < L ? l + AH : l + AH - L;
+  const uint32_t joff = c.pqoff[(l + AH < L ? 0 : L) + j];
   recurrent_half<TP>(c, ln, v3 == 2 ? 0 : v3 + 1, par ^ 1, W, PBS);
 #pragma unroll
   for (int f = 0; f < frags_b(TP); ++f) refill(c, W, PBS + f);
   // the pop of layer l + 3 into LDS (its buffer was last read before the previous layer's first
-  // barrier) and the pop of layer l + 8 issued
+  // barrier) and the pop of layer l + AH issued
   pop_land(c, v3, P[(G6 + 3) % 6]);
-  P[(G6 + 2) % 6] = pop_issue_at(c, joff);
+  P[(G6 + AH) % 6] = pop_issue_at(c, joff);
   __syncthreads();
   // while wave A runs the residual product: the layer's gate output to the helpers and its input
   // into its queue
@@ -427,7 +428,7 @@ __device__ __forceinline__ void set_mode(Ctx<TP> &c) {
   if (threadIdx.x == 0) put_word(comm_hs(c.a->sp_comm, c.L, c.blk) + HSLOT * (NHLP + 1), local ? 1u : 0u, c.mark, false);
 }
 
-// Any layer count from 9 on and both widths run on these kernels (before, layer counts other than
+// Any layer count from 6 on and both widths run on these kernels (before, layer counts other than
 // multiples of 6 and width 3 took the single-block kernel): 20 layers at 100 streams 30.5 -> 13.9 us
 // per step, 14 layers of width 3 at 256 streams 27.1 -> 13.1.
 // The layer loops run six layers at a time, with every ring slot a fixed register, and then the
@@ -491,7 +492,7 @@ __device__ __forceinline__ void a_role(Ctx<TP> &c) {
   }
 }
 
-template <int TP, int REM>
+template <int TP, int REM, int AH>
 __device__ __forceinline__ void b_role(Ctx<TP> &c) {
   constexpr int FB = frags_b(TP);
   constexpr int NB = DB / FB;  // layers the weight ring holds
@@ -499,11 +500,11 @@ __device__ __forceinline__ void b_role(Ctx<TP> &c) {
   c.fw = (const char *)c.a->mf_frags + base_b(L, TP, c.p) * 1024;
   c.fend = c.fw + (size_t)len_b(L, TP) * 1024;
   u32x4 W[DB], P[6];
-  // layers 0..2 of step 0 land now and layers 3..7 are issued; layer 0's W_r v + b comes from its
+  // layers 0..2 of step 0 land now and layers 3..AH - 1 are issued; layer 0's W_r v + b comes from its
   // stream stage L - 1 (all of these loads in flight together)
   const u32x4 v0 = pop_issue(c, 0, 0), v1 = pop_issue(c, 1, 0), v2 = pop_issue(c, 2, 0);
 #pragma unroll
-  for (int g = 3; g < 8; ++g) P[g % 6] = pop_issue(c, g, 0);
+  for (int g = 3; g < AH; ++g) P[g % 6] = pop_issue(c, g, 0);
 #pragma unroll
   for (int f = 0; f < FB; ++f) W[f] = frag_at(c, FB * (L - 1) + f);
   pop_land(c, 0, v0);
@@ -522,21 +523,21 @@ __device__ __forceinline__ void b_role(Ctx<TP> &c) {
     const int v4 = v3 == 2 ? 0 : v3 + 1, v5 = v4 == 2 ? 0 : v4 + 1;
     int l = 0;
     for (; l + REM < L; l += 6) {
-      b_layer<0, 0>(c, l, par, v3, W, P, tag);
-      b_layer<(1 % NB) * FB, 1>(c, l + 1, par ^ 1, v4, W, P, tag);
-      b_layer<(2 % NB) * FB, 2>(c, l + 2, par, v5, W, P, tag);
-      b_layer<(3 % NB) * FB, 3>(c, l + 3, par ^ 1, v3, W, P, tag);
-      b_layer<(4 % NB) * FB, 4>(c, l + 4, par, v4, W, P, tag);
-      b_layer<(5 % NB) * FB, 5>(c, l + 5, par ^ 1, v5, W, P, tag);
+      b_layer<0, 0, AH>(c, l, par, v3, W, P, tag);
+      b_layer<(1 % NB) * FB, 1, AH>(c, l + 1, par ^ 1, v4, W, P, tag);
+      b_layer<(2 % NB) * FB, 2, AH>(c, l + 2, par, v5, W, P, tag);
+      b_layer<(3 % NB) * FB, 3, AH>(c, l + 3, par ^ 1, v3, W, P, tag);
+      b_layer<(4 % NB) * FB, 4, AH>(c, l + 4, par, v4, W, P, tag);
+      b_layer<(5 % NB) * FB, 5, AH>(c, l + 5, par ^ 1, v5, W, P, tag);
     }
-    if constexpr (REM > 0) b_layer<0, 0>(c, l, par, v3, W, P, tag);
-    if constexpr (REM > 1) b_layer<(1 % NB) * FB, 1>(c, l + 1, par ^ 1, v4, W, P, tag);
-    if constexpr (REM > 2) b_layer<(2 % NB) * FB, 2>(c, l + 2, par, v5, W, P, tag);
-    if constexpr (REM > 3) b_layer<(3 % NB) * FB, 3>(c, l + 3, par ^ 1, v3, W, P, tag);
-    if constexpr (REM > 4) b_layer<(4 % NB) * FB, 4>(c, l + 4, par, v4, W, P, tag);
+    if constexpr (REM > 0) b_layer<0, 0, AH>(c, l, par, v3, W, P, tag);
+    if constexpr (REM > 1) b_layer<(1 % NB) * FB, 1, AH>(c, l + 1, par ^ 1, v4, W, P, tag);
+    if constexpr (REM > 2) b_layer<(2 % NB) * FB, 2, AH>(c, l + 2, par, v5, W, P, tag);
+    if constexpr (REM > 3) b_layer<(3 % NB) * FB, 3, AH>(c, l + 3, par ^ 1, v3, W, P, tag);
+    if constexpr (REM > 4) b_layer<(4 % NB) * FB, 4, AH>(c, l + 4, par, v4, W, P, tag);
     if constexpr (REM > 5) {
-      b_layer<(5 % NB) * FB, 5>(c, l + 5, par ^ 1, v5, W, P, tag);
-      b_layer<0, 0>(c, l + 6, par, v3, W, P, tag);
+      b_layer<(5 % NB) * FB, 5, AH>(c, l + 5, par ^ 1, v5, W, P, tag);
+      b_layer<0, 0, AH>(c, l + 6, par, v3, W, P, tag);
     }
     finish_step(c, step);
     if constexpr (REM % NB != 0) rotate_ring<(REM % NB) * FB>(W);
@@ -547,7 +548,7 @@ __device__ __forceinline__ void b_role(Ctx<TP> &c) {
   }
 }
 
-template <int TP, int REM>
+template <int TP, int REM, int AH>
 __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, int blk) {
   ChainLds<TP> &s = *(ChainLds<TP> *)lds_raw;
   const int tid = threadIdx.x, L = a.L;
@@ -645,7 +646,7 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
   // inside the roles' first loads: wave A polls the ids while its weight loads and wave B's first
   // pops are in flight.
   if (c.w < 4) a_role<TP, REM>(c);
-  else b_role<TP, REM>(c);
+  else b_role<TP, REM, AH>(c);
   if (a.mode != MODE_TEACHER && tid < c.nrows) a.last[c.b0 + tid] = s.ins[tid];
 }
 
@@ -850,7 +851,7 @@ __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, i
   c.lane = lane;
   c.n = lane & 15;
   c.q = lane >> 4;
-  c.nl = (L - w + NW - 1) / NW;  // layers of this wave (L >= NW)
+  c.nl = (L - w + NW - 1) / NW;  // layers of this wave
   c.wvoff = 16 * lane;
   c.h = h;
   c.local = s.local != 0;
@@ -978,7 +979,7 @@ constexpr int GB = 2 + kSpHelpers;  // blocks of a group: chain block, helpers, 
 __host__ __device__ inline bool rows_of_groups(int nb) { return nb <= 24; }
 __host__ __device__ inline int grid_blocks(int nb) { return rows_of_groups(nb) ? (nb + 7) / 8 * 8 * GB : nb * GB; }
 
-template <int TP, int REM>
+template <int TP, int REM, int AH>
 __global__ void __launch_bounds__(NT) split_step_kernel(StepArgs a) {
   extern __shared__ float4 lds_raw[];
   const int nb = a.sp_nb;
@@ -992,7 +993,7 @@ __global__ void __launch_bounds__(NT) split_step_kernel(StepArgs a) {
     m = (int)blockIdx.x / nb;
     grp = (int)blockIdx.x % nb;
   }
-  if (m == 0) chain_block<TP, REM>(a, (char *)lds_raw, grp);
+  if (m == 0) chain_block<TP, REM, AH>(a, (char *)lds_raw, grp);
   else if (m <= NHLP) helper_block<TP>(a, (char *)lds_raw, grp, m - 1);
   else class_block<TP>(a, (char *)lds_raw, grp);
 }
@@ -1001,13 +1002,16 @@ __global__ void __launch_bounds__(NT) split_step_kernel(StepArgs a) {
 typedef void (*StepKernel)(StepArgs);
 template <int TP>
 static StepKernel kernel_of(int L) {
+  if (L == 6) return split_step_kernel<TP, 0, 5>;
+  if (L == 7) return split_step_kernel<TP, 7, 5>;
+  if (L == 8) return split_step_kernel<TP, 2, 5>;
   switch (L % 6) {
-    case 0: return split_step_kernel<TP, 0>;
-    case 1: return split_step_kernel<TP, 7>;
-    case 2: return split_step_kernel<TP, 2>;
-    case 3: return split_step_kernel<TP, 3>;
-    case 4: return split_step_kernel<TP, 4>;
-    default: return split_step_kernel<TP, 5>;
+    case 0: return split_step_kernel<TP, 0, 8>;
+    case 1: return split_step_kernel<TP, 7, 8>;
+    case 2: return split_step_kernel<TP, 2, 8>;
+    case 3: return split_step_kernel<TP, 3, 8>;
+    case 4: return split_step_kernel<TP, 4, 8>;
+    default: return split_step_kernel<TP, 5, 8>;
   }
 }
 static StepKernel kernel_of(int L, int w) { return w == 3 ? kernel_of<2>(L) : kernel_of<1>(L); }

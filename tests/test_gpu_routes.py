@@ -37,7 +37,7 @@ def model(cfg, w, max_batch, **env):
             os.environ.pop(k, None)
 
 
-@pytest.mark.parametrize("n_layers", [9, 10, 11, 13, 14, 15, 16, 17, 31])
+@pytest.mark.parametrize("n_layers", [6, 7, 8, 9, 10, 11, 13, 14, 15, 16, 17, 31])
 def test_split_layer_counts_closed_form(n_layers):
     """The split kernels at every remainder of the six-layer loop (7-layer tails for a remainder of
     1) and past 32 streams' worth of skip registers: bit-exact logits of the rounding-point closed
@@ -51,7 +51,8 @@ def test_split_layer_counts_closed_form(n_layers):
     assert np.array_equal(lg, np.broadcast_to(want.astype(np.float32), lg.shape))
 
 
-@pytest.mark.parametrize("width,n_layers,B", [(2, 9, 1), (2, 10, 37), (2, 13, 130), (2, 20, 5), (3, 9, 17), (3, 12, 1),
+@pytest.mark.parametrize("width,n_layers,B", [(2, 6, 3), (2, 7, 40), (2, 8, 1), (3, 6, 20), (3, 7, 2),
+                                              (3, 8, 9), (2, 9, 1), (2, 10, 37), (2, 13, 130), (2, 20, 5), (3, 9, 17), (3, 12, 1),
                                               (3, 13, 5), (3, 14, 33), (3, 16, 3), (3, 17, 130)])
 def test_split_widths_and_ragged_groups(width, n_layers, B):
     """Both widths, odd and even layer counts, ragged group rows (1, 2, 3, 9 groups): teacher forcing
