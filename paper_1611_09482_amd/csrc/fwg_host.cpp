@@ -384,7 +384,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
     if (opnd_copy) row_bytes += 2 * (size_t)p->C * p->es;
     if (gated) row_bytes += ((size_t)p->L * p->C + p->S + p->H) * p->es;
     // chunk rows: about 64K rows, at most 512 MB of chunk buffers, at least one step
-    long long rows = 65536;
+    long long rows = 65536;  // (par_forward spreads them over the streams of a call)
     const char *pr = getenv("FWG_PAR_ROWS");
     if (pr && atoll(pr) > 0) rows = atoll(pr);
     const long long cap = (512ll << 20) / (long long)row_bytes;
@@ -711,8 +711,16 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
   float *px[3] = {(float *)(ws + p.off_px[0]), (float *)(ws + p.off_px[1]), (float *)(ws + p.off_px[2])};
   char *pxb[3] = {ws + p.off_pxb[0], ws + p.off_pxb[1], ws + p.off_pxb[2]};
   const bool fused = gated && par_gated_layer_ok(C, p.dtype);
-  for (long long s0 = 0; s0 < n; s0 += p.par_tc) {
-    const int Tcur = (int)(n - s0 < p.par_tc ? n - s0 : p.par_tc);
+  // Steps per chunk: as many as the chunk buffers hold rows for at this batch (they are sized for the
+  // padded largest one: 4 of 16 streams have room for 16,384 steps, not 4,096, and a launch per layer of
+  // few rows is bound by its latency); whole parts where the whole-stack kernel runs.
+  long long tc = (long long)p.par_tc * p.brows / batch;
+  if (p.stack_ok && tc > kStackRows) {
+    const long long whole = tc - tc % kStackRows;
+    if (stack_pays(batch, (int)whole)) tc = whole;
+  }
+  for (long long s0 = 0; s0 < n; s0 += tc) {
+    const int Tcur = (int)(n - s0 < tc ? n - s0 : tc);
     const int M = batch * Tcur;
     const long long t0 = tbase + s0;
     const bool stack = p.stack_ok && (p.stack_force >= 0 ? p.stack_force != 0 : stack_pays(batch, Tcur));

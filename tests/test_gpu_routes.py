@@ -272,3 +272,22 @@ def test_exchange_tags_across_launches(name):
     wrap = model(cfg, w, B, FWG_SPLIT_TAG_BASE=str(0xFFFFFFFF - 60))
     got = [wrap.generate(u[:, i:i + 30].contiguous()).cpu().numpy() for i in (0, 30, 60)]
     assert np.array_equal(np.concatenate(got, axis=1), want)
+
+
+@pytest.mark.parametrize("kind,dtype,C,S", [(W.GATED, W.BF16, 64, 512), (W.GATED, W.F32, 32, 256), (W.RELU, W.F32, 64, 0)])
+def test_parallel_chunks_of_a_small_batch(kind, dtype, C, S):
+    """A call with fewer streams than the handle's largest batch cuts its steps into longer chunks:
+    teacher forcing and priming of 1 and 3 streams on handles for 20 whose buffers hold 40 steps of
+    all of them, against the oracle and the step kernels' state."""
+    cfg = W.ModelConfig(kind, dtype, C, (1, 2, 4, 8, 16, 32, 64), S, S)
+    w = W.make_weights(cfg, 99, bias_scale=0.1)
+    brows = 32 if dtype == W.BF16 else 20
+    fw = model(cfg, w, 20, FWG_PAR_ROWS=str(40 * brows))
+    orc = oracle.Oracle(w)
+    for B in (1, 3):
+        x = W.sequences(98, B, 1000)
+        assert row_rel_err(fw.teacher_forced_parallel(dev(x)).cpu().numpy(), orc.teacher_forced(x)) <= TOL[dtype]
+        fw.reset()
+        fw.prime(dev(x[:, :777]))
+        got = fw.step_forced(dev(x[:, 777:800])).cpu().numpy()
+        assert row_rel_err(got, orc.state(B).step_forced(x[:, :800])[:, 777:]) <= TOL[dtype]
