@@ -135,7 +135,8 @@ struct Flight {
     A += p.k0;
     float *out = part + p.kg * p.N + p.n;
     for (int c = 0; c < cols; ++c) {
-      float acc = p.kg == 0 ? bias : 0.f;
+      const float b = p.kg == 0 ? bias : 0.f;
+      float acc = 0.f;  // the bias joins the finished sum
       if (c + 1 < cols) load_bias(p, rb, bias_at, c + 1);
       for (int kb = 0; kb < per; kb += U) {
         // the chunk after this one: of this column, or the first of the next
@@ -172,7 +173,7 @@ struct Flight {
           if (next && nkb + g < per) load4(N, per, r, base, nvoff, nkb, g);
         }
       }
-      if (p.n + NT * c < p.N) out[NT * c] = acc;
+      if (p.n + NT * c < p.N) out[NT * c] = acc + b;
     }
   }
 };

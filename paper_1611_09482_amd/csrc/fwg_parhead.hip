@@ -15,7 +15,7 @@
 //  - nothing but the logits goes back to memory.
 // Measured (30 layers): 65,536 rows 178 us (1,015 TFLOP/s; the three launches 390 us), 32,768 rows 75 us
 // (1,204 TFLOP/s; a large library product reaches ~1,130 on this card): the matrix cores bound it.
-// float32, 20 layers: 64 x 3,001 steps 2.05 -> 1.72 ms for the whole call.
+// float32, 20 layers: 64 x 3,001 steps 2.05 -> 1.75 ms for the whole call.
 // BM = 128 halves the weight traffic per row; BM = 64 fits two blocks per compute unit and splits small
 // row counts over more of them.
 #include <hip/hip_runtime.h>
