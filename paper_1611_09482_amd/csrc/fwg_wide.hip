@@ -448,11 +448,19 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
       float xin = 0.f;
       if (wave == 0) {
         const int o2 = tid & (OC - 1), st = tid >> 4, ch = 16 * j + o2;
-        float ee = 0.f, rr = 0.f;
+        // every partial sum is read before the first add: left to itself the compiler may wait for each
+        // read in turn (16 LDS round trips per layer: 25 layers 83.3 us per step, 78.0 with the reads first)
+        float ee = 0.f, rr = 0.f, pe[KP], pr[KP];
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
-          ee += s.red[p][o2][st];
-          rr += s.red[p][o2][SG + st];
+          pe[p] = s.red[p][o2][st];
+          pr[p] = s.red[p][o2][SG + st];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+          ee += pe[p];
+          rr += pr[p];
         }
         const size_t ent = ((size_t)(qoff[l] + slot[l]) * OC + o2) * SG + st;
         xin = s.xg[cur][st][ch / KW][ch % KW];
@@ -517,8 +525,12 @@ __global__ void __launch_bounds__(NT + NTL) wide_step_kernel(StepArgs a, WideArg
       if (wave == 0) {
         // lanes 0..31: (s, class); lanes 32..63 repeat them and store nothing
         const int cc = tid & (QB - 1), st = (tid >> 3) & (SG - 1), cls = QB * j + cc;
-        float lg = outb[cls];
-        for (int p = 0; p < NT / QB; ++p) lg += r2[(p * QB + cc) * SG + st];
+        float lg = outb[cls], pl[NT / QB];
+#pragma unroll
+        for (int p = 0; p < NT / QB; ++p) pl[p] = r2[(p * QB + cc) * SG + st];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < NT / QB; ++p) lg += pl[p];
         const float lg1 = __shfl_down(lg, 1, 64);
         if (tid < QB * SG) {
           if (a.mode != MODE_GENERATE && a.logits && st < nval)
