@@ -372,7 +372,8 @@ int make_plan(const fwg_desc *d, Plan *p) {
   for (int l = 0; l < p->L; ++l)  // it addresses one layer's queue with 32-bit byte offsets
     p->stack_ok = p->stack_ok && (unsigned long long)d->dilations[l] * p->brows * p->C * p->es < (1ull << 31);
   p->off_stack = 0;
-  p->head_ok = p->par_ok && par_head_ok(p->kind, p->dtype, p->C, p->S, p->H, p->Q);
+  const char *ph = getenv("FWG_PAR_HEAD");  // test hook: "0" keeps the head on the GEMM kernels
+  p->head_ok = p->par_ok && par_head_ok(p->kind, p->dtype, p->C, p->S, p->H, p->Q) && !(ph && atoi(ph) == 0);
   const char *ps = getenv("FWG_PAR_STACK");
   p->stack_force = ps ? atoi(ps) != 0 : -1;
   if (p->par_ok) {
@@ -684,14 +685,16 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
   }
 }
 
-// Whether the whole-stack kernel beats one launch per layer for a chunk.  Measured per layer (30
-// layers): the stack kernel takes 4.0 us for each part of up to 256 steps of a stream (5.0 with every
-// compute unit busy), one block per stream; the per-layer kernel 7.7 us for up to ~8,000 rows and
-// 20 us for 65,536.  So long chunks of few streams (48 x 1,365 steps: 24 us in 6 parts against 20)
-// stay with the per-layer kernel, which spreads a stream's steps over the chip.
+// Whether the whole-stack kernel beats one launch per layer for a chunk (both give the same bits).  Measured
+// per layer (30 layers): the stack kernel takes 7.0 us for each part of up to 256 steps of a stream (8.5 with
+// every compute unit busy), one block per stream; the per-layer kernel 7.8 us for few rows, 10.2 for 16,384, 12.9
+// for 32,768, 15.9 for 49,152 (three blocks per compute unit) and 23 to 25 for 61,440 to 65,536.  So long chunks
+// of few streams (48 x 1,280 steps: 34.6 us in 5 parts against 22.2) stay with the per-layer kernel, which
+// spreads a stream's steps over the chip.
 bool stack_pays(int batch, int Tcur) {
   const long long rounds = (batch + 255) / 256, parts = (Tcur + kStackRows - 1) / kStackRows;
-  return rounds * parts * 4.2 < std::max(7.7, 6.0 + 14.0 * batch * Tcur / 65536.0);
+  const double rows = (double)batch * Tcur;
+  return rounds * parts * 7.0 < 7.8 + 8.0 * rows / 49152.0 + (rows > 49152.0 ? 8.0 : 0.0);
 }
 
 // Time-parallel evaluation of a forced sequence, chunk by chunk (MODE_TEACHER or MODE_ONLINE):

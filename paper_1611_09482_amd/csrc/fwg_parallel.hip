@@ -79,17 +79,11 @@ template <> struct Op<uint16_t> {
   }
 };
 
-// tanh(a) * sigmoid(g).  bf16 models: one hardware exp and reciprocal each, tanh(a) = 1 - 2 / (exp(2a) + 1),
-// whose absolute error of ~1e-7 the bf16 rounding of z hides (with the library's tanhf and a full division
-// the gate was the larger part of the layer kernels' time: 22.8 -> 20.6 us per 65,536-row launch at
-// R = 64).  float32 models keep the library's: the hardware forms, also with a polynomial for small a and
-// refined reciprocals, gained 2.6% of a 20-layer call for 0.7% more error against 64 bits.
-template <typename OT>
-__device__ __forceinline__ float gate(float a, float g) {
-  if (sizeof(OT) == 4) return tanhf(a) * (1.f / (1.f + __expf(-g)));
-  const float t = 1.f - 2.f * __builtin_amdgcn_rcpf(__expf(2.f * a) + 1.f);
-  return t * __builtin_amdgcn_rcpf(1.f + __expf(-g));
-}
+// tanh(a) * sigmoid(g) with the library's tanhf and a full division, for both operand types.  bf16 models too:
+// 1 - 2 / (exp(2a) + 1) on the hardware's exp and reciprocal loses the relative bits of small a (its error of
+// ~1e-7 against z: 5e-3 at |a| = 1e-5, more than a bf16 rounding) and gained 22.8 -> 20.6 us per 65,536-row
+// launch at R = 64; for float32 models 2.6% of a 20-layer call for 0.7% more error against 64 bits.
+__device__ __forceinline__ float gate(float a, float g) { return tanhf(a) * (1.f / (1.f + __expf(-g))); }
 
 // Row sources of the A operand.
 constexpr int A_PLAIN = PAR_A_PLAIN, A_CONV = PAR_A_CONV, A_TREE = PAR_A_TREE;
@@ -236,7 +230,7 @@ __global__ void __launch_bounds__(NT) par_gemm_kernel(ParGemm g) {
         for (int e = 0; e < 4; ++e) {
           const int m = m0 + TW * wm + 16 * i + 4 * lg + e;
           if (m < g.M) {
-            const float z = gate<OT>(acc[i][2 * q][e] + bt, acc[i][2 * q + 1][e] + bs);
+            const float z = gate(acc[i][2 * q][e] + bt, acc[i][2 * q + 1][e] + bs);
             Op<OT>::put(g.oout, (long long)m * g.ldo + g.zoff + ch, z);
             if (AM == A_TREE && g.ztop) {
               const int b = m / g.Tcur;
@@ -461,7 +455,7 @@ __global__ void __launch_bounds__(NT) par_gated_layer_kernel(ParGemm g) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = 32 * wm + 16 * i + 4 * lg + e;
-        const float z = gate<OT>(acc[i][2 * q][e] + bt, acc[i][2 * q + 1][e] + bs);
+        const float z = gate(acc[i][2 * q][e] + bt, acc[i][2 * q + 1][e] + bs);
         Op<OT>::put(lds_z + r * ROWB, ch, z);
       }
   }

@@ -85,16 +85,8 @@ __device__ __forceinline__ void tile(f32x4 (&acc)[NC][NM], u32x4 (&w)[2][NC], co
   }
 }
 
-template <int NC, int NM>
-__device__ __forceinline__ void start(f32x4 (&acc)[NC][NM], const float *bias, int ch, int q) {
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const float4 b = *(const float4 *)(bias + ch + 16 * c + 4 * q);
-#pragma unroll
-    for (int m = 0; m < NM; ++m) acc[c][m] = f32x4{b.x, b.y, b.z, b.w};
-  }
-}
-// float32: from zero, the bias added to the finished sum (the order with the smaller error against 64 bits)
+// Sums start from zero and the bias joins the finished sum (the order with the smaller error against 64 bits,
+// and the GEMM kernels').
 template <int NC, int NM>
 __device__ __forceinline__ void zero(f32x4 (&acc)[NC][NM]) {
 #pragma unroll
@@ -125,13 +117,6 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
   const u32x4 *wh = (const u32x4 *)g.packed + (NW * (size_t)L + (size_t)w * KX) * (2 * NC) * 64;
   const u32x4 *wo = (const u32x4 *)g.packed + ((NW * (size_t)L + NW * KX) * (2 * NC) + (size_t)w * KX * 4) * 64;
 
-  auto begin = [&](auto &a, const float *bias, int ch) {
-    if constexpr (E == 4) zero(a);
-    else start(a, bias, ch, q);
-  };
-  auto end = [&](auto &a, const float *bias, int ch) {
-    if constexpr (E == 4) add_bias(a, bias, ch, q);
-  };
   // z rows: thread -> row tid / 8 (+ 64), 16-byte piece tid % 8 of a k-tile (= one layer)
   constexpr int NZ = BM / 64;
   uint32_t zo[NZ];  // byte offsets (a chunk's z rows take at most 512 MB)
@@ -146,7 +131,7 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
   load_tile(wf, ws, 0, lane);
 #pragma unroll
   for (int i = 0; i < NZ; ++i) zr[i] = *(const u32x4 *)((const char *)g.z + zo[i]);
-  begin(acc, g.skip_b, 16 * NC * w);
+  zero(acc);
 #pragma unroll
   for (int i = 0; i < NZ; ++i) *(u32x4 *)(sm + ((tid >> 3) + 64 * i) * PZ + 16 * (tid & 7)) = zr[i];
   __syncthreads();
@@ -169,9 +154,9 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
         Op<OT>::put4(sm + (16 * m + n) * PS + (16 * (NC * w + c) + 4 * q) * E, relu4(acc[c][m]));
   };
   load_tile(wf, wh, 0, lane);
-  end(acc, g.skip_b, 16 * NC * w);
+  add_bias(acc, g.skip_b, 16 * NC * w, q);
   rows_out();
-  begin(acc, g.head_b, 16 * NC * w);
+  zero(acc);
   __syncthreads();
 #pragma unroll (UX)
   for (int kt = 0; kt < KX; ++kt) tile<OT>(acc, wf, sm + ZB * kt, PS, wh, kt + 1 < KX ? kt + 1 : kt, lane);
@@ -179,14 +164,14 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
   // relu(hidden) rows over them
   u32x4 wq[2][2];
   load_tile(wq, wo, 0, lane);
-  end(acc, g.head_b, 16 * NC * w);
+  add_bias(acc, g.head_b, 16 * NC * w, q);
   rows_out();
   f32x4 lg[2][NM];
-  begin(lg, g.out_b, 32 * w);
+  zero(lg);
   __syncthreads();
 #pragma unroll (UX)
   for (int kt = 0; kt < KX; ++kt) tile<OT>(lg, wq, sm + ZB * kt, PS, wo, kt + 1 < KX ? kt + 1 : kt, lane);
-  end(lg, g.out_b, 32 * w);
+  add_bias(lg, g.out_b, 32 * w, q);
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
     const int row = m0 + 16 * m + n;

@@ -10,13 +10,12 @@
 // the layer's queue, which the block itself refreshed at the previous 256 steps, so blocks never wait
 // for each other.  Weights (40 KB per layer) are double-buffered in LDS.
 //
-// Measured: 30 layers over 256 streams x 256 steps 150 us (5.0 us per layer; 606 us with a launch per
-// layer), 3.8 us per layer when few blocks run.  What bounds it now is the compute unit's own work:
-// per layer and SIMD two waves of ~2,400 cycles of vector instructions (the gate: two exps and two
-// reciprocals of 8 cycles), 1,280 cycles of products and ~0.5 KB of LDS operands per product, which
-// overlap only in part.  What helped: accesses without branches around them (see Rsrc), the products
-// of one tile pair between the gate instructions of the pair before, and the next layer's loads
-// spread over the layer instead of issued right after the barrier (-8%).
+// Measured: 30 layers over 256 streams x 256 steps 254 us (8.5 us per layer; 24 us with a launch per layer),
+// 7.0 us per layer when few blocks run.  What bounds it is the gate: 32 of tanhf, exp and a full division per
+// lane and layer, two waves per SIMD, of which the products (1,280 cycles per layer and SIMD) hide behind
+// little.  (With the hardware's exps and reciprocals alone it took 5.0 us, but lost bits of z, see gate.)  What
+// helped: accesses without branches around them (see Rsrc), and the next layer's loads spread over the layer
+// instead of issued right after the barrier (-8%).
 //
 // Wave w owns rows 32w .. 32w + 31.  Products are transposed, D[channel][row] = W[channel][k]
 // X[row][k]: each lane's result is 4 consecutive channels of one row, so z and x go back to LDS as
@@ -76,11 +75,8 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// The step kernels' gate (tanh(a) = 1 - 2 / (exp(2a) + 1)) with the factors folded into the base-2 exps.
-__device__ __forceinline__ float gate2(float a, float g) {
-  const float t = 1.f - 2.f * __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(2.8853900818f * a) + 1.f);
-  return t * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950409f * g));
-}
+// The per-layer kernel's gate, bit by bit: 1 - 2 / (exp(2a) + 1) loses the relative bits of small a.
+__device__ __forceinline__ float gate(float a, float g) { return tanhf(a) * (1.f / (1.f + __expf(-g))); }
 
 __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
   extern __shared__ float4 lds_raw[];
@@ -203,7 +199,8 @@ __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
         }
       };
       // ---- 2b. dilated product and gate, one pair of tiles at a time: the products of pair p + 1 are
-      // issued between the gate's instructions of pair p, and the fragments of pair p + 2 read
+      // issued before the gate of pair p, and the fragments of pair p + 2 read.  Sums start from zero and the
+      // biases join the finished sums, as in the per-layer kernel (the same bits, and the smaller error).
       u32x4 wf[2][8];
       f32x4 at[2][2], ag[2][2];
       auto frags = [&](int p) {
@@ -211,12 +208,8 @@ __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
         for (int f = 0; f < 8; ++f) wf[p & 1][f] = *(const u32x4 *)(wl + ((p * 8 + f) * 64 + lane) * 16);
       };
       auto product = [&](int p) {
-        const f32x4 bt = ldsf4(bias + 16 * p + 4 * q), bg = ldsf4(bias + R + 16 * p + 4 * q);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          at[p & 1][t] = bt;
-          ag[p & 1][t] = bg;
-        }
+        for (int t = 0; t < 2; ++t) at[p & 1][t] = ag[p & 1][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -247,20 +240,13 @@ __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
         }
         if (p < 3) product(p + 1);
         if (p < 3) frags(p + 2);  // p = 2: the residual fragments
+        const f32x4 bt = ldsf4(bias + 16 * p + 4 * q), bg = ldsf4(bias + R + 16 * p + 4 * q);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           f32x4 z;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) z[i] = gate2(at[p & 1][t][i], ag[p & 1][t][i]);
+          for (int i = 0; i < 4; ++i) z[i] = gate(at[p & 1][t][i] + bt[i], ag[p & 1][t][i] + bg[i]);
           lds8(xn + (32 * w + 16 * t + n) * PX + 16 * p + 4 * q, pack4(z));
-        }
-        if (p < 3) {
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // gate arithmetic
-            __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);  // exps and reciprocals
-          }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -279,11 +265,10 @@ __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
         for (int c = 0; c < 4; ++c) {
           const f32x4 rb = ldsf4(bias + 2 * R + 16 * c + 4 * q);
 #pragma unroll
-          for (int t = 0; t < 2; ++t) xr[c][t] += rb;
-#pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t) xr[c][t] = mfma(wf[0][2 * c + ks], zb[t][ks], xr[c][t]);
+          for (int t = 0; t < 2; ++t) {
+            f32x4 r = mfma(wf[0][2 * c], zb[t][0], f32x4{0.f, 0.f, 0.f, 0.f});
+            r = mfma(wf[0][2 * c + 1], zb[t][1], r);
+            xr[c][t] += r + rb;
           }
 #pragma unroll
           for (int t = 0; t < 2; ++t)

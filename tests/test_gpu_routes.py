@@ -178,6 +178,39 @@ def test_parallel_f32_tiles(B, T):
     assert row_rel_err(got[-1:], oracle.Oracle(w).teacher_forced(x[-1:])) <= TOL[W.F32]
 
 
+@pytest.mark.parametrize("stack", ["0", "1"])
+def test_parallel_gate_small_arguments(stack):
+    """The gate of the time-parallel kernels where |a| is small: conv weights of ~1e-6, so that z is ~1e-6
+    and below (skip weights of ~1e6 bring it back), where 1 - 2 / (exp(2a) + 1) keeps only a few bits.
+    The whole-stack and the per-layer kernel against the oracle at the bf16 bar."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4), 512, 512)
+    w = W.make_weights(cfg, 64)
+    for l in range(cfg.n_layers):
+        w.conv[l] *= 2.0 ** -20
+        w.skip[l] *= 2.0 ** 20
+    fw = model(cfg, w, 5, FWG_PAR_STACK=stack)
+    x = W.sequences(65, 5, 40)
+    got = fw.teacher_forced_parallel(dev(x)).cpu().numpy()
+    assert row_rel_err(got, oracle.Oracle(w).teacher_forced(x)) <= TOL[W.BF16]
+
+
+@pytest.mark.parametrize("B,T", [(1, 1), (3, 43), (5, 300), (17, 257)])
+def test_parallel_kernels_give_the_same_bits(B, T):
+    """The whole-stack kernel and the fused head take their sums in the order of the per-layer and GEMM
+    kernels (from zero, the bias last) and the same gate: teacher forcing and priming agree with them
+    bit by bit, logits and (through the step kernels' next logits) queues."""
+    for dtype, R, S, env in ((W.BF16, 64, 512, ("FWG_PAR_STACK", "FWG_PAR_HEAD")), (W.F32, 32, 256, ("FWG_PAR_HEAD",))):
+        cfg = W.ModelConfig(W.GATED, dtype, R, (1, 2, 4, 8, 64, 300, 3), S, S)
+        w = W.make_weights(cfg, 66, bias_scale=0.1)
+        x, y = W.sequences(67, B, T), dev(W.sequences(68, B, 9))
+        outs = []
+        for on in ("0", "1"):
+            fw = model(cfg, w, B, **{k: on for k in env})
+            outs.append([fw.teacher_forced_parallel(dev(x)), fw.prime(dev(x), logits=True), fw.step_forced(y)])
+        for a, b in zip(*outs):
+            assert torch.equal(a, b)
+
+
 # shapes of the general kernel: 512 and 256 threads, several columns per thread (N > 512, N no multiple of
 # the thread count), K-groups with fewer than 8 and more than 8 k-blocks, wide pops, more streams than
 # compute units
