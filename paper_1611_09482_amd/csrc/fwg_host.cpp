@@ -67,6 +67,7 @@ struct Plan {
   int stack_force;        // FWG_PAR_STACK (test hook): 0 never, 1 always, else -1
   size_t off_stack;       // its packed layer blocks
   bool head_ok;           // the fused head kernel takes this model
+  bool head_force;        // FWG_PAR_HEAD (test hook): 0 never (head_ok false), 1 always
   size_t off_head_pack;   // its packed weights
   size_t off_px[3], off_pxb[3], off_pz, off_psb, off_phb;  // three rotating row buffers
   // naive generator: the nodes of the output's dependency tree (Fig. 1), level 0 = inputs
@@ -372,8 +373,9 @@ int make_plan(const fwg_desc *d, Plan *p) {
   for (int l = 0; l < p->L; ++l)  // it addresses one layer's queue with 32-bit byte offsets
     p->stack_ok = p->stack_ok && (unsigned long long)d->dilations[l] * p->brows * p->C * p->es < (1ull << 31);
   p->off_stack = 0;
-  const char *ph = getenv("FWG_PAR_HEAD");  // test hook: "0" keeps the head on the GEMM kernels
+  const char *ph = getenv("FWG_PAR_HEAD");
   p->head_ok = p->par_ok && par_head_ok(p->kind, p->dtype, p->C, p->S, p->H, p->Q) && !(ph && atoi(ph) == 0);
+  p->head_force = ph && atoi(ph) != 0;
   const char *ps = getenv("FWG_PAR_STACK");
   p->stack_force = ps ? atoi(ps) != 0 : -1;
   if (p->par_ok) {
@@ -697,6 +699,12 @@ bool stack_pays(int batch, int Tcur) {
   return rounds * parts * 7.0 < 7.8 + 8.0 * rows / 49152.0 + (rows > 49152.0 ? 8.0 : 0.0);
 }
 
+// Whether the fused head beats the three GEMM launches for a chunk (both give the same bits).  A block takes its
+// rows through all three products, which for few rows leaves most of the chip idle.  Measured (whole call, us,
+// GEMM / fused): float32 with 8 layers 86 / 105 for 64 rows, 111 / 115 for 8,192, 128 / 118 for 12,288, with 20
+// layers 174 / 208, 214 / 230 and 239 / 235.  bf16: never worse (6 layers, 64 rows 63 / 56; 30 layers 241 / 239).
+bool head_pays(int dtype, int M, int L) { return dtype == FWG_BF16 || M >= 8192 + 160 * L; }
+
 // Time-parallel evaluation of a forced sequence, chunk by chunk (MODE_TEACHER or MODE_ONLINE):
 // every layer is a GEMM over the chunk's rows whose popped operand comes from the chunk or from
 // the layer's queue in `ring`; a layer's queue is refreshed once its product has read it (by the
@@ -810,7 +818,7 @@ int par_forward(fwg_handle *h, int mode, int batch, int n, const int32_t *inputs
       cur = nxt;
     }
     if (!logits) continue;
-    if (p.head_ok) {
+    if (p.head_ok && (p.head_force || head_pays(p.dtype, M, L))) {
       ParHead k;
       memset(&k, 0, sizeof(k));
       k.M = M; k.L = L; k.Tcur = Tcur;

@@ -140,14 +140,15 @@ def test_parallel_stack(n_layers, B, T, rows):
     assert row_rel_err(fw.step_forced(y).cpu().numpy(), ref.step_forced(y).cpu().numpy()) <= TOL[W.BF16]
 
 
+@pytest.mark.parametrize("width", [2, 3])
 @pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (5, 13), (3, 43), (1, 129)])
-def test_parallel_head_row_tails(B, T):
+def test_parallel_head_row_tails(B, T, width):
     """The fused head at row counts around its 64-row blocks (1, 63, 65, 129 rows), both widths'
     row producers, against the step kernels on every row."""
     for dtype, R, S in ((W.BF16, 64, 512), (W.F32, 32, 256)):
-        cfg = W.ModelConfig(W.GATED, dtype, R, (1, 2, 4, 1, 2, 4, 8, 1, 3), S, S, filter_width=2 + B % 2)
+        cfg = W.ModelConfig(W.GATED, dtype, R, (1, 2, 4, 1, 2, 4, 8, 1, 3), S, S, filter_width=width)
         w = W.make_weights(cfg, 70, bias_scale=0.1)
-        fw = model(cfg, w, B)
+        fw = model(cfg, w, B, FWG_PAR_HEAD="1")
         x = dev(W.sequences(71, B, T))
         got = fw.teacher_forced_parallel(x).cpu().numpy()
         assert row_rel_err(got, fw.teacher_forced(x).cpu().numpy()) <= TOL[dtype]
