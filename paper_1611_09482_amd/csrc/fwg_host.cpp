@@ -45,7 +45,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct Plan {
   int kind, dtype, Q, C, S, H, L, bmax, seed_input, Co, es;
-  int valu_threads;       // general step kernel: threads per block
+  ValuVariant valu;       // general step kernel
   size_t valu_block;      // bytes of one layer's weight + bias block (general step kernels)
   int w;                  // filter width: taps per dilated product
   int regime;
@@ -226,22 +226,39 @@ int make_plan(const fwg_desc *d, Plan *p) {
     b += sizeof(float) * ((size_t)p->Co + (g ? (size_t)p->C + p->S : 0));
     p->valu_block = (b + 15) & ~(size_t)15;
   }
-  // Threads of the general step kernel: 512 where every product splits evenly over them, each stream can
-  // have a compute unit of its own (two blocks of 512 do not share one: at 512 streams 155 us per step
-  // against 96 for R = 64, S = 256 float32) and the layers are large enough (us per step with 256 / 512
-  // threads: ReLU C = 256 float32 101 / 62, C = 128 bf16 23 / 18, gated R = 128, S = 512 float32 148 / 88;
-  // gated R = 64, S = 128 bf16, 56 KB per layer, 67 / 75).
+  // Variant of the general step kernel.
+  //  512 threads where every product splits evenly over them, each stream can have a compute unit of its own
+  //  (two blocks of 512 do not share one: at 512 streams 155 us per step against 96 for R = 64, S = 256
+  //  float32) and the layers are large enough (us per step with 256 / 512 threads: ReLU C = 256 float32
+  //  101 / 62, C = 128 bf16 23 / 18, gated R = 128, S = 512 float32 148 / 88; gated R = 64, S = 128 bf16, 56 KB
+  //  per layer, 67 / 75).
+  //  From 513 streams on four blocks share a compute unit instead of two (2,048 streams, us per step of 10
+  //  layers: gated R = 32, S = 64 float32 137 -> 75, ReLU C = 128 float32 100 -> 95, bf16 96 -> 67), except gated bf16
+  //  stacks (R = 64, S = 256: 172 either way, and their registers spill), and from 100 KB of weights per layer on
+  //  a block of a ReLU stack takes two streams, so that half the weights pass through the compute unit's load path
+  //  (2,048 streams: C = 128 float32, 131 KB, 95 -> 77; C = 512 float32, 6 layers, 867 -> 718; C = 1024 bf16, 3
+  //  layers, 965 -> 841; below, C = 128 bf16, 66 KB, 67 -> 65, C = 32 float32 35 -> 43).
   auto split_ok = [&](int K, int N, int threads) { return N >= threads || (threads % N == 0 && (K / kb) % (threads / N) == 0); };
   auto threads_ok = [&](int t) {
     const bool g = p->kind == FWG_GATED;
     return split_ok(w * p->C, p->Co, t) && split_ok(g ? p->H : p->C, p->Q, t) &&
            (!g || (split_ok(p->C, p->C, t) && split_ok(p->C, p->S, t) && split_ok(p->S, p->H, t)));
   };
-  const bool small_layer = p->kind == FWG_GATED && p->valu_block < 200 * 1024;
-  p->valu_threads = threads_ok(512) && p->bmax <= 256 && !small_layer ? 512 : 256;
-  // the popped states of a layer are held in registers between layers
-  p->lds_bytes = (size_t)valu_lds_layout(p->kind, p->C, p->S, p->H, p->Q, p->L, w, p->valu_threads).total_floats * 4;
-  const bool valu_fits = (w - 1) * p->C <= kValuPrefPops * kThreads && p->lds_bytes <= 160 * 1024;
+  auto lds_of = [&](const ValuVariant &v) {
+    return (size_t)valu_lds_layout(p->kind, p->C, p->S, p->H, p->Q, p->L, w, v.threads, v.rows).total_floats * 4;
+  };
+  auto valu_fits = [&](const ValuVariant &v) {
+    // the popped states of a layer are held in registers between layers
+    return v.rows * (w - 1) * p->C <= kValuPrefPops * kThreads && lds_of(v) <= 160 * 1024;
+  };
+  const bool gated_bf16 = p->kind == FWG_GATED && p->dtype == FWG_BF16;
+  const ValuVariant plain{256, false, 1}, wide{512, false, 1}, many{256, true, 1}, pairs{256, true, 2};
+  p->valu = plain;
+  if (p->bmax <= 256 && threads_ok(512) && !(p->kind == FWG_GATED && p->valu_block < 200 * 1024) && valu_fits(wide))
+    p->valu = wide;
+  if (p->bmax > 512 && !gated_bf16)
+    p->valu = p->kind != FWG_GATED && p->valu_block >= 100 * 1024 && valu_fits(pairs) ? pairs : many;
+  p->lds_bytes = lds_of(p->valu);
 
   // kernel family: the MFMA kernel covers gated bf16 stacks with R=64, S=H=512, filter width 2 or 3
   p->regime = REGIME_VALU;
@@ -284,7 +301,7 @@ int make_plan(const fwg_desc *d, Plan *p) {
                 "unsupported shape: every product needs K a multiple of %d, and an output width that "
                 "divides 256 (with K/%d divisible by 256/N) or is at least 256",
                 kb, kb);
-  if (p->regime == REGIME_VALU && !valu_fits)
+  if (p->regime == REGIME_VALU && !valu_fits(plain))
     return fail(FWG_EUNSUPPORTED, "model too wide for one block's LDS and registers");
   const bool mf_family = p->regime == REGIME_MFMA || p->regime == REGIME_SPLIT;
   p->brows = mf_family ? (p->bmax + kMfRows - 1) / kMfRows * kMfRows : p->bmax;
@@ -683,7 +700,7 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       g.image = (const float *)(h->ws + p.off_wave);
       return launch_wave_step(a, g, h->stream);
     }
-    default: return launch_valu_step(a, p.valu_threads, p.lds_bytes, h->stream);
+    default: return launch_valu_step(a, p.valu, p.lds_bytes, h->stream);
   }
 }
 
@@ -1093,7 +1110,7 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
     TRY_OR_FREE(set_mfma_lds_limit(mfma_lds_bytes(p.L, p.w)));
   }
   if (h->plan.regime == REGIME_VALU && p.lds_bytes > 64 * 1024)
-    TRY_OR_FREE(set_valu_lds_limit(dt, p.valu_threads, p.kind, p.w, p.lds_bytes));
+    TRY_OR_FREE(set_valu_lds_limit(p.valu, dt, p.kind, p.w, p.lds_bytes));
   int rr = enqueue_reset(h);
   if (rr != FWG_OK) return cleanup_fail(rr);
   // the layer table is copied from host memory owned by this call

@@ -78,9 +78,9 @@ template <typename T> __device__ __forceinline__ T *uniform_ptr(T *p) {
   return (T *)(((uint64_t)hi << 32) | lo);
 }
 
-template <typename WT, int NT>
+template <typename WT, int NT, int U_>
 struct Product {
-  static constexpr int KB = WTraits<WT>::KB, U = 8;
+  static constexpr int KB = WTraits<WT>::KB, U = U_;
   // the thread's share: first piece and first column, first k, K-group; k-blocks per column
   int piece, n, k0, kg, per, N;
   __device__ __forceinline__ void init(int K, int N_) {
@@ -106,9 +106,9 @@ struct Product {
 };
 
 // One product in flight: a ring of U pieces, refilled four at a time as they are multiplied.
-template <typename WT, int NT>
+template <typename WT, int NT, int U>
 struct Flight {
-  static constexpr int KB = WTraits<WT>::KB, U = Product<WT, NT>::U;
+  static constexpr int KB = WTraits<WT>::KB;
   u32x4 w[U];
   float bias;
   __device__ __forceinline__ void load4(int N, int per, Rsrc r, uint32_t base, uint32_t voff, int kb, int g) {
@@ -117,11 +117,11 @@ struct Flight {
       w[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                            r, voff, base + (uint32_t)(min(kb + u, per - 1) * N) * 16u, 0));
   }
-  __device__ __forceinline__ void load_bias(const Product<WT, NT> &p, Rsrc rb, uint32_t bias_at, int c) {
+  __device__ __forceinline__ void load_bias(const Product<WT, NT, U> &p, Rsrc rb, uint32_t bias_at, int c) {
     bias = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, 4 * min(p.n + NT * c, p.N - 1), bias_at, 0));
   }
   // base: byte offset of the product's weights in r; bias_at: byte offset of its biases in rb
-  __device__ __forceinline__ void head(const Product<WT, NT> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at) {
+  __device__ __forceinline__ void head(const Product<WT, NT, U> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at) {
     load_bias(p, rb, bias_at, 0);
     const uint32_t voff = p.at(0);
     const int N = fresh(p.N), per = fresh(p.per);
@@ -129,14 +129,18 @@ struct Flight {
     for (int g = 0; g < U; g += 4)
       if (g < per) load4(N, per, r, base, voff, 0, g);
   }
-  __device__ __forceinline__ void run(const Product<WT, NT> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at,
-                                      const float *A, float *part) {
+  // R streams: operand rows `lda` apart, partial sums valu_part_cols(N, NT) apart
+  template <int R = 1>
+  __device__ __forceinline__ void run(const Product<WT, NT, U> &p, Rsrc r, uint32_t base, Rsrc rb, uint32_t bias_at,
+                                      const float *A, float *part, int lda = 0) {
     const int N = fresh(p.N), per = fresh(p.per), cols = (N + NT - 1) / NT;
     A += p.k0;
     float *out = part + p.kg * p.N + p.n;
     for (int c = 0; c < cols; ++c) {
       const float b = p.kg == 0 ? bias : 0.f;
-      float acc = 0.f;  // the bias joins the finished sum
+      float acc[R];  // the bias joins the finished sum
+#pragma unroll
+      for (int i = 0; i < R; ++i) acc[i] = 0.f;
       if (c + 1 < cols) load_bias(p, rb, bias_at, c + 1);
       for (int kb = 0; kb < per; kb += U) {
         // the chunk after this one: of this column, or the first of the next
@@ -144,24 +148,33 @@ struct Flight {
         const int nkb = here ? kb + U : 0;
         const uint32_t nvoff = p.at(here ? c : c + 1);
         const float *x = A + kb * KB;
-        float4 xv[U * KB / 4];
+        constexpr int XU = R == 1 ? U : 4;  // pieces whose operands are held at a time
+        float4 xv[R][XU * KB / 4];
+        auto operands = [&](int g) {  // past the end: not multiplied
 #pragma unroll
-        for (int i = 0; i < U * KB / 4; ++i) xv[i] = *(const float4 *)(x + 4 * i);  // past the end: not multiplied
+          for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < XU * KB / 4; ++j) xv[i][j] = *(const float4 *)(x + i * lda + g * KB + 4 * j);
+        };
+        if (R == 1) operands(0);
         auto piece = [&](int u) {
           float wv[KB];
           WTraits<WT>::unpack(w[u], wv);
 #pragma unroll
-          for (int j = 0; j < KB; j += 4) {
-            const float4 xx = xv[(u * KB + j) / 4];
-            acc = fmaf(wv[j], xx.x, acc);
-            acc = fmaf(wv[j + 1], xx.y, acc);
-            acc = fmaf(wv[j + 2], xx.z, acc);
-            acc = fmaf(wv[j + 3], xx.w, acc);
-          }
+          for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < KB; j += 4) {
+              const float4 xx = xv[i][(u % XU * KB + j) / 4];
+              acc[i] = fmaf(wv[j], xx.x, acc[i]);
+              acc[i] = fmaf(wv[j + 1], xx.y, acc[i]);
+              acc[i] = fmaf(wv[j + 2], xx.z, acc[i]);
+              acc[i] = fmaf(wv[j + 3], xx.w, acc[i]);
+            }
         };
         const int left = per - kb;
 #pragma unroll
         for (int g = 0; g < U; g += 4) {
+          if (R > 1) operands(g);
           if (left >= g + 4) {
 #pragma unroll
             for (int u = g; u < g + 4; ++u) piece(u);
@@ -173,7 +186,10 @@ struct Flight {
           if (next && nkb + g < per) load4(N, per, r, base, nvoff, nkb, g);
         }
       }
-      if (p.n + NT * c < p.N) out[NT * c] = acc + b;
+      if (p.n + NT * c < p.N) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) out[i * valu_part_cols(p.N, NT) + NT * c] = acc[i] + b;
+      }
     }
   }
 };
@@ -190,7 +206,7 @@ __device__ __forceinline__ float part_sum(const float *part, int N, int n) {
 __device__ __forceinline__ float bias_or0(const float *b, int i) { return b ? b[i] : 0.f; }
 
 // ---------------------------------------------------------------------------
-// The general step kernel: one block of NT threads per stream.
+// The general step kernel: one block of NT threads per stream (ROWS = 2: per two streams).
 //
 // What bounds it is the compute unit's load path: a step streams every weight from the L2 at up to 64
 // bytes per cycle (a layer of R = 64, S = 256 float32 channels, 147 KB, ~1 us).  So a stream gets a
@@ -198,17 +214,24 @@ __device__ __forceinline__ float bias_or0(const float *b, int i) { return b ? b[
 // weights, most of the chip was idle (16 streams of that 20-layer model: 562 us per step on 2 blocks,
 // 74 now; 512 streams 568 and 96).  Blocks of 256 threads share a compute unit from 257 streams on.
 // At ~3.5 us per layer the chain of barriers, LDS reads and partial sums is still what bounds it.
+// MANY: past two streams per compute unit throughput counts, so half the registers (and pieces in flight) let
+// four blocks share one.  ROWS = 2 (ReLU stacks of large layers, with MANY): there the weight stream itself is the
+// bound, and two streams of a block share it.  2,048 streams, us per step, with 8 streams on a block / one
+// stream, two blocks per compute unit / now: gated R = 32, S = 64 float32, 10 layers 86 / 138 / 75; ReLU C = 512
+// float32, 6 layers 814 / 1,060 / 718; ReLU C = 1024 bf16, 3 layers 830 / 1,438 / 841.
 // Latency hiding: the states a layer pops do not depend on the current step (they were pushed
 // at least d steps earlier), so the pops of layer l + 1 -- or of layer 0 of the next step -- are
 // loaded into registers while layer l computes and land in the second of two LDS buffers at the
 // end of the layer; each product's first weights are in registers before its operands are ready.
 // GATED and W2 (filter width 2) are compile-time: fewer shape values stay live.
-template <typename WT, int NT, bool GATED, bool W2>
-__global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
+template <typename WT, int NT, bool GATED, bool W2, bool MANY, int ROWS>
+__global__ void __launch_bounds__(NT, MANY && ROWS == 1 ? 4 : 2) valu_step_kernel(StepArgs a) {
+  static_assert(ROWS == 1 || !GATED, "several streams per block: ReLU stacks");
+  constexpr int U = MANY && ROWS == 1 ? 4 : 8;  // pieces in flight per product
   extern __shared__ float4 lds_raw[];
   float *lds = (float *)lds_raw;
   const int kind = GATED ? 2 : a.kind, C = a.C, S = a.S, H = a.H, Q = 256, w = W2 ? 2 : a.w, L = a.L;
-  const ValuLds lay = valu_lds_layout(kind, C, S, H, Q, L, w, NT);
+  const ValuLds lay = valu_lds_layout(kind, C, S, H, Q, L, w, NT, ROWS);
   // the two buffers of operand rows (the w - 1 popped states, oldest first, then the current input)
   auto vbuf = [&](int p) { return lds + (p ? lay.vx2 : lay.vx); };
   float *xf = lds + lay.xf, *zo = lds + lay.zo, *so = lds + lay.so, *h2 = lds + lay.h2;
@@ -217,7 +240,8 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
   int *ins = (int *)(lds + lay.ins);
   ValuLayer *ltab = (ValuLayer *)(lds + lay.ltab);
 
-  const int tid = threadIdx.x, b = blockIdx.x;
+  const int tid = threadIdx.x, b = blockIdx.x * ROWS;  // the block's first stream
+  const int nrows = ROWS == 1 ? 1 : min(ROWS, a.batch - b);
   const int Co = GATED ? 2 * C : C;
   const int K = w * C, XO = (w - 1) * C;  // row length of the operands; where the current input starts
   const uint32_t es = sizeof(WT);
@@ -237,10 +261,14 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     ltab[l] = v;
     slots[l] = (int)(a.t0 % (long long)ld.depth);
   }
-  if (tid == 0) ins[0] = a.mode == MODE_TEACHER ? a.inputs[(long long)b * a.n_steps] : a.last[b];
+  // the thread that handles a stream's input: thread r for stream r
+  const bool owner = ROWS == 1 ? tid == 0 : tid < nrows;
+  const int own = ROWS == 1 ? 0 : tid;
+  if (owner) ins[own] = a.mode == MODE_TEACHER ? a.inputs[(long long)(b + own) * a.n_steps] : a.last[b + own];
   __syncthreads();
 
-  // prefetch registers of the next layer's popped states: element i is tap i / C, channel i % C
+  // prefetch registers of the next layer's popped states: element i of a stream is tap i / C, channel i % C
+  // (streams past the last one repeat it)
   float pp[kValuPrefPops];
   auto fetch = [&](int l, int slot_) {
     const ValuLayer ld = ltab[l];
@@ -249,10 +277,10 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     const long long slot_bytes = (long long)fresh(a.bmax) * C * es;
 #pragma unroll
     for (int j = 0; j < kValuPrefPops; ++j) {
-      if (j * NT >= XO) break;
-      const int i = tid + j * NT;
+      if (j * NT >= ROWS * XO) break;
+      const int e = tid + j * NT, r = ROWS == 1 ? 0 : e / XO, i = e - r * XO;
       float v = 0.f;
-      if (i < XO) {
+      if (e < ROWS * XO) {
         int k = 0, c = i;
         if (!W2) {
           k = i / C;
@@ -260,7 +288,7 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
         }
         int sk = slot + (W2 ? 0 : k * dil);  // k dilations after the oldest state
         if (!W2 && sk >= depth) sk -= depth;
-        v = WTraits<WT>::load1(row + sk * slot_bytes, c);
+        v = WTraits<WT>::load1(row + sk * slot_bytes, min(r, nrows - 1) * C + c);
       }
       pp[j] = v;
     }
@@ -269,14 +297,14 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     float *vb = vbuf(par);
 #pragma unroll
     for (int j = 0; j < kValuPrefPops; ++j) {
-      if (j * NT >= XO) break;
-      const int i = tid + j * NT;
-      if (i < XO) vb[i] = pp[j];
+      if (j * NT >= ROWS * XO) break;
+      const int e = tid + j * NT;
+      if (e < ROWS * XO) vb[ROWS == 1 ? e : e / XO * K + e % XO] = pp[j];
     }
   };
   auto layer_rsrc = [&](int l) { return rsrc(uniform_ptr((const char *)ltab[l].block), o_end); };
 
-  Product<WT, NT> pconv, pres, pskip, phead, pout;
+  Product<WT, NT, U> pconv, pres, pskip, phead, pout;
   const int Ktop = GATED ? H : C;
   pconv.init(K, Co);
   pout.init(Ktop, Q);
@@ -285,7 +313,7 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     pskip.init(C, S);
     phead.init(S, H);
   }
-  Flight<WT, NT> conv;
+  Flight<WT, NT, U> conv;
 
   fetch(0, slots[0]);
   land(0);
@@ -295,11 +323,14 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
 
   for (int s = 0; s < a.n_steps; ++s) {
     // ---- current input (h^0_e): a row gather of the transposed 1x1 convolution
-    const int tok = ins[0];
-    for (int c = tid; c < C; c += NT) {
-      const float v = WTraits<WT>::load1(a.embed, (long long)tok * C + c) + bias_or0(a.embed_b, c);
-      xf[c] = v;
-      vbuf(par)[XO + c] = WTraits<WT>::opnd(v);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int tok = ins[min(r, nrows - 1)];
+      for (int c = tid; c < C; c += NT) {
+        const float v = WTraits<WT>::load1(a.embed, (long long)tok * C + c) + bias_or0(a.embed_b, c);
+        xf[r * C + c] = v;
+        vbuf(par)[r * K + XO + c] = WTraits<WT>::opnd(v);
+      }
     }
     if constexpr (GATED)
       for (int i = tid; i < S; i += NT) so[i] = 0.f;
@@ -319,15 +350,18 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
       // ---- push phase for this queue: the layer's input x^{l-1}_t replaces the oldest state,
       // whose pop has landed in LDS already
       char *qrow = uniform_ptr((char *)a.ring + (ld.ring_off + ((long long)slots[l] * a.bmax + b) * C) * es);
-      for (int c = tid; c < C; c += NT) WTraits<WT>::store1(qrow, c, vo[XO + c]);
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r)
+        if (r < nrows)
+          for (int c = tid; c < C; c += NT) WTraits<WT>::store1(qrow, r * C + c, vo[r * K + XO + c]);
       if (more && L == 1) {
         __syncthreads();
         fetch(nl, nslot);
       }
       // ---- dilated convolution of width w: [v_0 .. v_{w-2} x] . [W_0 ; .. ; W_{w-1}]
-      conv.run(pconv, rl, 0, rl, o_cb, vo, partA);
+      conv.template run<ROWS>(pconv, rl, 0, rl, o_cb, vo, partA, K);
       if constexpr (GATED) {
-        Flight<WT, NT> res, skip;
+        Flight<WT, NT, U> res, skip;
         res.head(pres, rl, o_res, rl, o_rb);
         skip.head(pskip, rl, o_skip, rl, o_sb);
         __syncthreads();
@@ -361,12 +395,14 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
           conv.head(pconv, rl, 0, rl, o_cb);
         }
         __syncthreads();
-        for (int c = tid; c < C; c += NT) {
-          const float pre = part_sum<NT>(partA, Co, c);
-          const float v = (kind == 1 ? xf[c] : 0.f) + fmaxf(pre, 0.f);
-          xf[c] = v;
-          xn[c] = WTraits<WT>::opnd(v);
-        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+          for (int c = tid; c < C; c += NT) {
+            const float pre = part_sum<NT>(partA + r * valu_part_cols(Co, NT), Co, c);
+            const float v = (kind == 1 ? xf[r * C + c] : 0.f) + fmaxf(pre, 0.f);
+            xf[r * C + c] = v;
+            xn[r * K + c] = WTraits<WT>::opnd(v);
+          }
       }
       if (more) land(par ^ 1);
       __syncthreads();
@@ -374,7 +410,7 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     }
 
     // ---- output head (the top layer's output sits where layer 0's next input will)
-    Flight<WT, NT> top;
+    Flight<WT, NT, U> top;
     const float *x = vbuf(par) + XO;
     const Rsrc ro = rsrc(a.out, (uint32_t)Ktop * Q * es), rob = rsrc(a.out_b, Q * 4);
     if constexpr (GATED) {
@@ -391,24 +427,29 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     } else {
       top.head(pout, ro, 0, rob, 0);
     }
-    top.run(pout, ro, 0, rob, 0, x, partA);
+    top.template run<ROWS>(pout, ro, 0, rob, 0, x, partA, K);
     __syncthreads();
-    if (tid < Q) lg[tid] = part_sum<NT>(partA, Q, tid);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+      if (tid < Q) lg[r * Q + tid] = part_sum<NT>(partA + r * valu_part_cols(Q, NT), Q, tid);
     __syncthreads();
 
     if (a.mode != MODE_GENERATE) {
-      if (a.logits && tid < Q) a.logits[((long long)b * a.n_steps + s) * Q + tid] = lg[tid];
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r)
+        if (a.logits && r < nrows && tid < Q) a.logits[((long long)(b + r) * a.n_steps + s) * Q + tid] = lg[r * Q + tid];
       // the next input: the following element of the forced sequence (teacher forcing), or this
       // step's observed sample (online prediction)
       const int nx = s + forced_shift(a.mode);
-      if (tid == 0 && nx < a.n_steps) ins[0] = a.inputs[(long long)b * a.n_steps + nx];
-    } else if (tid < 64) {
-      // ---- sample and feed back
-      const float u = a.uniforms[(long long)b * a.n_steps + s];
-      const int k = sample_row_256(lg, u);
-      if (tid == 0) {
-        a.samples[(long long)b * a.n_steps + s] = k;
-        ins[0] = k;
+      if (owner && nx < a.n_steps) ins[own] = a.inputs[(long long)(b + own) * a.n_steps + nx];
+    } else if (tid < 64 * nrows) {
+      // ---- sample and feed back: one wavefront per stream
+      const int r = ROWS == 1 ? 0 : tid / 64;
+      const float u = a.uniforms[(long long)(b + r) * a.n_steps + s];
+      const int k = sample_row_256(lg + r * Q, u);
+      if (ROWS == 1 ? tid == 0 : tid == 64 * r) {
+        a.samples[(long long)(b + r) * a.n_steps + s] = k;
+        ins[r] = k;
       }
     }
     // ---- advance every queue's slot
@@ -418,28 +459,33 @@ __global__ void __launch_bounds__(NT, 2) valu_step_kernel(StepArgs a) {
     }
     __syncthreads();
   }
-  if (a.mode != MODE_TEACHER && tid == 0) a.last[b] = ins[0];
+  if (a.mode != MODE_TEACHER && owner) a.last[b + own] = ins[own];
 }
 
 typedef void (*ValuKernel)(StepArgs);
-template <typename WT, int NT>
+template <typename WT, int NT, bool MANY>
 static ValuKernel valu_kernel_of(int kind, int w) {
-  if (kind == 2) return w == 2 ? valu_step_kernel<WT, NT, true, true> : valu_step_kernel<WT, NT, true, false>;
-  return w == 2 ? valu_step_kernel<WT, NT, false, true> : valu_step_kernel<WT, NT, false, false>;
+  if (kind == 2) return w == 2 ? valu_step_kernel<WT, NT, true, true, MANY, 1> : valu_step_kernel<WT, NT, true, false, MANY, 1>;
+  return w == 2 ? valu_step_kernel<WT, NT, false, true, MANY, 1> : valu_step_kernel<WT, NT, false, false, MANY, 1>;
 }
-static ValuKernel valu_kernel_of(int dtype, int threads, int kind, int w) {
-  if (dtype == 1) return threads == 512 ? valu_kernel_of<uint16_t, 512>(kind, w) : valu_kernel_of<uint16_t, 256>(kind, w);
-  return threads == 512 ? valu_kernel_of<float, 512>(kind, w) : valu_kernel_of<float, 256>(kind, w);
+template <typename WT>
+static ValuKernel valu_kernel_of(const ValuVariant &v, int kind, int w) {
+  if (v.rows == 2) return w == 2 ? valu_step_kernel<WT, 256, false, true, true, 2> : valu_step_kernel<WT, 256, false, false, true, 2>;
+  if (v.many) return valu_kernel_of<WT, 256, true>(kind, w);
+  return v.threads == 512 ? valu_kernel_of<WT, 512, false>(kind, w) : valu_kernel_of<WT, 256, false>(kind, w);
+}
+static ValuKernel valu_kernel_of(const ValuVariant &v, int dtype, int kind, int w) {
+  return dtype == 1 ? valu_kernel_of<uint16_t>(v, kind, w) : valu_kernel_of<float>(v, kind, w);
 }
 
-hipError_t launch_valu_step(const StepArgs &a, int threads, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL(valu_kernel_of(a.dtype, threads, a.kind, a.w), dim3(a.batch), dim3(threads), lds, s, a);
+hipError_t launch_valu_step(const StepArgs &a, const ValuVariant &v, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL(valu_kernel_of(v, a.dtype, a.kind, a.w), dim3((a.batch + v.rows - 1) / v.rows), dim3(v.threads), lds, s, a);
   return hipGetLastError();
 }
 
-hipError_t set_valu_lds_limit(int dtype, int threads, int kind, int w, size_t bytes) {
-  return hipFuncSetAttribute((const void *)valu_kernel_of(dtype, threads, kind, w),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+hipError_t set_valu_lds_limit(const ValuVariant &v, int dtype, int kind, int w, size_t bytes) {
+  return hipFuncSetAttribute((const void *)valu_kernel_of(v, dtype, kind, w), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
 }
 
 // ---------------------------------------------------------------------------

@@ -26,33 +26,40 @@ struct ValuLds {
 constexpr int kValuPrefPops = 8;   // popped elements per thread and layer held in registers
 __host__ __device__ inline int valu_part_cols(int N, int threads) { return N >= threads ? N : threads; }
 __host__ __device__ inline ValuLds valu_lds_layout(int kind, int C, int S, int H, int Q, int L, int w,
-                                                   int threads) {
+                                                   int threads, int rows) {
   ValuLds o;
   int p = 0;
   auto take = [&](int n) { int at = p; p += (n + 3) & ~3; return at; };
   const int Co = kind == 2 ? 2 * C : C;
-  o.xf = take(C);
-  o.vx = take(w * C);
-  o.vx2 = take(w * C);
+  o.xf = take(rows * C);
+  o.vx = take(rows * w * C);
+  o.vx2 = take(rows * w * C);
   o.zo = take(kind == 2 ? C : 0);
   o.so = take(kind == 2 ? S : 0);
   o.h2 = take(kind == 2 ? H : 0);
-  o.lg = take(Q);
+  o.lg = take(rows * Q);
   int partN = valu_part_cols(Co, threads);
   if (kind == 2) {
     partN = partN > valu_part_cols(S, threads) ? partN : valu_part_cols(S, threads);
     partN = partN > valu_part_cols(H, threads) ? partN : valu_part_cols(H, threads);
   }
-  o.partA = take(partN);
+  o.partA = take(rows * partN);
   o.partB = take(kind == 2 ? valu_part_cols(C, threads) : 0);
   o.ltab = take(8 * L);  // per layer: weight block address, queue offset, dilation, depth (ValuLayer)
   o.slots = take(L);   // int
-  o.ins = take(1);     // int
+  o.ins = take(rows);  // int
   o.total_floats = p;
   return o;
 }
 
-hipError_t launch_valu_step(const StepArgs &a, int threads, size_t lds_bytes, hipStream_t s);
-hipError_t set_valu_lds_limit(int dtype, int threads, int kind, int w, size_t bytes);
+// The general step kernel's variant: threads per block; whether up to four blocks share a compute unit (256
+// threads, half the registers); streams per block (2: `many`, ReLU stacks).
+struct ValuVariant {
+  int threads;
+  bool many;
+  int rows;
+};
+hipError_t launch_valu_step(const StepArgs &a, const ValuVariant &v, size_t lds_bytes, hipStream_t s);
+hipError_t set_valu_lds_limit(const ValuVariant &v, int dtype, int kind, int w, size_t bytes);
 
 }  // namespace fwg

@@ -224,13 +224,25 @@ GENERAL = {
     "relu_f32_c256_l1": (W.ModelConfig(W.RELU, W.F32, 256, (3,)), 1),
     "relures_f32_c128_w5": (W.ModelConfig(W.RELU_RESIDUAL, W.F32, 128, (1, 2, 1), filter_width=5), 2),
     "gated_f32_r64_b300": (W.ModelConfig(W.GATED, W.F32, 64, (1, 2), 64, 64), 300),
+    # past 512 streams: four blocks per compute unit, and two streams per block from 100 KB of weights per layer
+    # on (an odd batch leaves the last block one stream)
+    "gated_f32_r32_b600": (W.ModelConfig(W.GATED, W.F32, 32, (1, 2, 5), 64, 64), 600),
+    "gated_f32_r32_w3_b513": (W.ModelConfig(W.GATED, W.F32, 32, (1, 2), 64, 64, filter_width=3), 513),
+    "gated_bf16_r64_b600": (W.ModelConfig(W.GATED, W.BF16, 64, (1, 2), 64, 64), 600),
+    "relu_bf16_c64_w3_b700": (W.ModelConfig(W.RELU, W.BF16, 64, (1, 3), filter_width=3), 700),
+    "relures_f32_c128_b513": (W.ModelConfig(W.RELU_RESIDUAL, W.F32, 128, (1, 2, 3)), 513),
+    "relu_f32_c128_l1_b514": (W.ModelConfig(W.RELU, W.F32, 128, (2,)), 514),
+    "relures_bf16_c320_w3_b515": (W.ModelConfig(W.RELU_RESIDUAL, W.BF16, 320, (1, 2), filter_width=3), 515),
+    "relu_f32_c1024_b513": (W.ModelConfig(W.RELU, W.F32, 1024, (1,)), 513),
 }
 
 
 @pytest.mark.parametrize("name", list(GENERAL))
 def test_general_kernel_shapes(name):
     """Teacher forcing through the step kernel against the oracle (sampled streams), and the state
-    carried across calls: online prediction in two pieces equals one, bit by bit."""
+    carried across calls: online prediction in two pieces equals one, bit by bit.  Generation on a
+    handle for more streams than 512 equals that of one for 300 (256 threads and one stream per block: the
+    same sums, bit by bit)."""
     cfg, B = GENERAL[name]
     w = W.make_weights(cfg, 80, bias_scale=0.1)
     fw = model(cfg, w, B)
@@ -245,6 +257,14 @@ def test_general_kernel_shapes(name):
     a = fw.step_forced(dev(x[:, :11])).cpu().numpy()
     b = fw.step_forced(dev(x[:, 11:])).cpu().numpy()
     assert np.array_equal(np.concatenate([a, b], axis=1), one)
+    if B > 512:
+        u = W.uniforms(82, B, 20)
+        fw.reset()
+        g = fw.generate(dev(u)).cpu().numpy()
+        alone = model(cfg, w, 300, FWG_REGIME="valu")
+        for i in sel:
+            alone.reset()
+            assert np.array_equal(alone.generate(dev(u[i:i + 1])).cpu().numpy()[0], g[i])
 
 
 @pytest.mark.parametrize("B", [1, 6])
