@@ -119,18 +119,20 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
 
   // z rows: thread -> row tid / 8 (+ 64), 16-byte piece tid % 8 of a k-tile (= one layer)
   constexpr int NZ = BM / 64;
-  uint32_t zo[NZ];  // byte offsets (a chunk's z rows take at most 512 MB)
+  // byte offsets from the block's first row (a chunk of many streams x layers may hold more than 4 GB of z rows)
+  const char *const zb = (const char *)g.z + (size_t)m0 * (size_t)(g.ldz * E);
+  uint32_t zo[NZ];
 #pragma unroll
   for (int i = 0; i < NZ; ++i) {
-    const int m = min(m0 + (tid >> 3) + 64 * i, g.M - 1);  // rows past the end repeat the last one
-    zo[i] = (uint32_t)m * (uint32_t)(g.ldz * E) + 16 * (tid & 7);
+    const int r = min((tid >> 3) + 64 * i, g.M - 1 - m0);  // rows past the end repeat the last one
+    zo[i] = (uint32_t)r * (uint32_t)(g.ldz * E) + 16 * (tid & 7);
   }
   u32x4 zr[NZ];
   f32x4 acc[NC][NM];
   u32x4 wf[2][NC];
   load_tile(wf, ws, 0, lane);
 #pragma unroll
-  for (int i = 0; i < NZ; ++i) zr[i] = *(const u32x4 *)((const char *)g.z + zo[i]);
+  for (int i = 0; i < NZ; ++i) zr[i] = *(const u32x4 *)(zb + zo[i]);
   zero(acc);
 #pragma unroll
   for (int i = 0; i < NZ; ++i) *(u32x4 *)(sm + ((tid >> 3) + 64 * i) * PZ + 16 * (tid & 7)) = zr[i];
@@ -138,7 +140,7 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
   for (int kt = 0; kt < L; ++kt) {
     const int nx = kt + 1 < L ? kt + 1 : kt;
 #pragma unroll
-    for (int i = 0; i < NZ; ++i) zr[i] = *(const u32x4 *)((const char *)g.z + (zo[i] + (uint32_t)nx * ZB));
+    for (int i = 0; i < NZ; ++i) zr[i] = *(const u32x4 *)(zb + (zo[i] + (uint32_t)nx * ZB));
     tile<OT>(acc, wf, sm + (kt & 1) * BM * PZ, PZ, ws, nx, lane);
     unsigned char *dst = sm + ((kt + 1) & 1) * BM * PZ;
 #pragma unroll

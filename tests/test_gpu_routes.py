@@ -167,6 +167,18 @@ def test_parallel_head_large_blocks():
         assert row_rel_err(got[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[dtype]
 
 
+def test_parallel_head_beyond_4gb_of_rows():
+    """A chunk whose z rows take more than 4 GB (65,664 streams x 512 layers: one step per chunk is the
+    least): streams with the same input have the same logits, bit by bit, on both sides of 4 GB."""
+    B = 65664
+    cfg = W.ModelConfig(W.GATED, W.F32, 32, (1,) * 512, 256, 256)
+    fw = model(cfg, W.make_weights(cfg, 76, bias_scale=0.1), B, FWG_PAR_HEAD="1")
+    x = (torch.arange(B, dtype=torch.int32, device="cuda") % 251).view(B, 1).contiguous()
+    lg = fw.teacher_forced_parallel(x)[:, 0]
+    assert torch.isfinite(lg).all() and not torch.equal(lg[0], lg[1])
+    assert torch.equal(lg[251:], lg[:-251])
+
+
 @pytest.mark.parametrize("B,T", [(5, 1000), (4, 2047)])
 def test_parallel_f32_tiles(B, T):
     """float32 products of 512 channels over 5,000 rows (small tiles: 3 rounds of a quarter against 1 of
