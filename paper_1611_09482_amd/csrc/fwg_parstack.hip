@@ -50,8 +50,8 @@ static_assert(NF / NW == 5 && LB == NF * 1024 + NB * 4 && NF % NW == 0 && NR == 
 struct Lds {
   uint16_t x[2][NR * PX];           // layer inputs, by running layer parity
   __attribute__((aligned(16))) unsigned char w[2][LB];  // weights and biases, by running layer parity
-  // followed by the per-layer tables: queue offset in 16-byte pieces [L], dilation [L], slot of the
-  // first row [L], slot of the first row that is kept [L]
+  // followed by the per-layer tables: queue offset in rows of R values (32 bits of them reach 512 GB) [L],
+  // dilation [L], slot of the first row [L], slot of the first row that is kept [L]
 };
 
 // Queue rows and z rows go through raw buffer accesses whose offset is put past the end where a lane
@@ -87,14 +87,14 @@ __global__ void __launch_bounds__(NT) stack_kernel(ParStack g) {
   uint32_t *roff = (uint32_t *)((char *)lds_raw + sizeof(Lds));
   int *dil = (int *)(roff + L), *first = dil + L, *keep = first + L;
   for (int l = tid; l < L; l += NT) {
-    roff[l] = (uint32_t)(g.layers[l].ring_off / 8);
+    roff[l] = (uint32_t)(g.layers[l].ring_off / R);
     dil[l] = g.layers[l].dil;
     first[l] = (int)(g.t0 % (long long)g.layers[l].dil);
   }
   const uint32_t slotb = (uint32_t)g.brows * (R * 2), rowb = (uint32_t)b * (R * 2);  // bytes
   auto queue = [&](int l) {
     const uint32_t off = __builtin_amdgcn_readfirstlane(roff[l]), d = __builtin_amdgcn_readfirstlane(dil[l]);
-    return rsrc((const char *)g.ring + (size_t)off * 16, d * slotb);
+    return rsrc((const char *)g.ring + (size_t)off * (R * 2), d * slotb);
   };
   // the first layer's weights
   {

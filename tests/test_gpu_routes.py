@@ -179,6 +179,25 @@ def test_parallel_head_beyond_4gb_of_rows():
     assert torch.equal(lg[251:], lg[:-251])
 
 
+def test_parallel_stack_queue_beyond_64gb():
+    """A queue more than 64 GB into the queue region (33 layers of 2 GB each before it): priming through
+    the whole-stack kernel leaves its states where the step kernels read them."""
+    if torch.cuda.mem_get_info()[0] < 160e9:
+        pytest.skip("needs 160 GB of free device memory")
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, (2 ** 20 - 1,) * 33 + (64,), 512, 512)
+    w = W.make_weights(cfg, 77, bias_scale=0.1)
+    w.conv[33][:, :, 0] *= 4  # the last layer's recurrent tap counts
+    fw = model(cfg, w, 1, FWG_PAR_STACK="1")
+    x = dev(W.sequences(78, 1, 212))
+    want = fw.step_forced(x).cpu().numpy()[:, 200:]
+    fw.reset()
+    fw.prime(x[:, :200].contiguous())
+    got = fw.step_forced(x[:, 200:].contiguous()).cpu().numpy()
+    del fw
+    torch.cuda.empty_cache()
+    assert row_rel_err(got, want) <= TOL[W.BF16]
+
+
 @pytest.mark.parametrize("B,T", [(5, 1000), (4, 2047)])
 def test_parallel_f32_tiles(B, T):
     """float32 products of 512 channels over 5,000 rows (small tiles: 3 rounds of a quarter against 1 of
