@@ -55,6 +55,9 @@ template <> struct Op<float> {
   __device__ static __forceinline__ void put4(unsigned char *p, const f32x4 &v) { stf4((float *)p, v); }
 };
 
+// Four logits at an address that is a float's (the caller's array may start anywhere).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // One product over k-tiles of 128 bytes: NC channel tiles x NM row tiles per wave.  src: the wave's
 // fragment stream (k-tile, k-step, channel tile); the first k-tile's fragments are in w already.
 template <int NC>
@@ -181,7 +184,7 @@ __global__ void __launch_bounds__(NT, BM == 64 ? 4 : 2) head_kernel(ParHead g) {
     const int b = row / g.Tcur, j = row - b * g.Tcur;
     float *dst = g.logits + ((long long)b * g.n_steps + g.s0 + j) * Q + 32 * w + 4 * q;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) *(float4 *)(dst + 16 * c) = make_float4(lg[c][m][0], lg[c][m][1], lg[c][m][2], lg[c][m][3]);
+    for (int c = 0; c < 2; ++c) *(f32x4_any *)(dst + 16 * c) = lg[c][m];
   }
 }
 
@@ -193,9 +196,12 @@ __global__ void pack_kernel(const unsigned char *src, uint4 *dst, int row, int n
   const int e = blockIdx.x * blockDim.x + threadIdx.x, kts = row / ZB;
   if (e >= NW * kts * 2 * nc * 64) return;
   const int i = e % 64, f = e / 64, c = f % nc, ks = f / nc % 2, kt = f / (2 * nc) % kts, w = f / (2 * nc * kts);
-  const unsigned int *p =
-      (const unsigned int *)(src + (long long)(16 * (nc * w + c) + i % 16) * row + ZB * kt + 64 * ks + 16 * (i / 16));
-  dst[((((size_t)w * nkt + kt0 + kt) * 2 + ks) * nc + c) * 64 + i] = make_uint4(p[0], p[1], p[2], p[3]);
+  // 16 bits at a time: the caller's bf16 arrays may start at any element
+  const uint16_t *p = (const uint16_t *)(src + (long long)(16 * (nc * w + c) + i % 16) * row + ZB * kt + 64 * ks + 16 * (i / 16));
+  uint32_t v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = p[2 * j] | ((uint32_t)p[2 * j + 1] << 16);
+  dst[((((size_t)w * nkt + kt0 + kt) * 2 + ks) * nc + c) * 64 + i] = make_uint4(v[0], v[1], v[2], v[3]);
 }
 
 static void pack(const void *src, void *dst, int row, int nc, int nkt, int kt0, hipStream_t s) {

@@ -167,6 +167,34 @@ def test_parallel_head_large_blocks():
         assert row_rel_err(got[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,R,S", [(W.BF16, 64, 512), (W.F32, 32, 256)])
+def test_parallel_head_element_aligned_arrays(dtype, R, S):
+    """Weights and logits at addresses that are only a multiple of their element's size (views into flat
+    buffers): the same logits, bit by bit, as with arrays of their own."""
+    cfg = W.ModelConfig(W.GATED, dtype, R, (1, 2), S, S)
+    w = W.make_weights(cfg, 79, bias_scale=0.1)
+    x = dev(W.sequences(79, 3, 30))
+    want = model(cfg, w, 3, FWG_PAR_HEAD="1").teacher_forced_parallel(x)
+
+    def off(t):  # a copy one element past an aligned address
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.reshape(-1)
+        return flat[1:].view(t.shape)
+
+    dw = binding.upload_weights(w, dtype)
+    for name in ("embed", "head", "out"):
+        setattr(dw, name, off(getattr(dw, name)))
+    for name in ("conv", "res", "skip"):
+        setattr(dw, name, [off(t) for t in getattr(dw, name)])
+    os.environ["FWG_PAR_HEAD"] = "1"
+    try:
+        fw = binding.FastWavenet(cfg.kind, dtype, R, cfg.dilations, 3, dw, skip_channels=S, head_channels=S)
+    finally:
+        os.environ.pop("FWG_PAR_HEAD")
+    out = off(torch.zeros((3, 30, 256), device="cuda"))
+    assert torch.equal(fw.teacher_forced_parallel(x, out=out), want)
+
+
 def test_parallel_head_beyond_4gb_of_rows():
     """A chunk whose z rows take more than 4 GB (65,664 streams x 512 layers: one step per chunk is the
     least): streams with the same input have the same logits, bit by bit, on both sides of 4 GB."""
