@@ -162,13 +162,12 @@ int fwg_generate(fwg_handle *h, int32_t batch, int32_t n_steps, const float *uni
  * the words they exchange in a static device array of 4 MiB (one per device,
  * set up by fwg_create and held until the process ends) instead of the
  * workspace; a batch whose words do not fit (split family: more than 4 MiB /
- * (8 x (512 L + 8544)) groups of 16 streams, about 21 groups at L = 30, for
- * width 2 and L a multiple of 6 from 12 on -- other layer counts and width 3
- * then keep them in the workspace; wide
+ * (8 x (512 L + 8544)) groups of 16 streams, about 21 groups at L = 30; wide
  * family: 256 + 8 x (16,384 L + 17,664) bytes whatever the batch, so L <= 30;
  * gated chain pair family: 256 + 8 x (736 + 32 L) bytes per stream, 381
  * streams at L = 20) returns FWG_ENOSPACE before anything is enqueued.  The
- * other kernel families use no per-launch scratch and run exactly as
+ * other kernel families ("mfma_bf16_r64_s512" among them, also where its blocks
+ * exchange words: those stay in the handle's workspace) run exactly as
  * fwg_generate.  The array is cleared by a fill kernel at the start of every
  * launch, but every call on a device shares it: calls of this entry point that
  * overlap on one device (other streams, other handles, other threads) race and

@@ -1135,18 +1135,19 @@ int generate_impl(fwg_handle *h, int32_t batch, int32_t n_steps, const float *un
   if (h->bound_batch >= 0 && h->bound_batch != batch)
     return fail(FWG_ESTATE, "batch %d differs from %d used since the last reset", batch, h->bound_batch);
   void *comm = nullptr;
-  if (noalloc && (p.regime == REGIME_SPLIT || p.regime == REGIME_WIDE || p.regime == REGIME_CHAIN_PAIR)) {
+  // The layer counts and widths that the split kernels took over from the single-block kernel, which shares
+  // nothing, keep their words in the workspace, so that calls on other handles may overlap.
+  const bool static_words = (p.regime == REGIME_SPLIT && !split_taken_over(p)) || p.regime == REGIME_WIDE ||
+                            p.regime == REGIME_CHAIN_PAIR;
+  if (noalloc && static_words) {
     const size_t need = p.regime == REGIME_SPLIT ? split_comm_bytes(p.L, (batch + kMfRows - 1) / kMfRows)
                         : p.regime == REGIME_WIDE ? p.wide_comm
                                                   : chain_pair_comm_bytes(p.L, batch);
-    // The layer counts and widths that the split kernels took over from the single-block kernel, which
-    // has no exchange words, keep running at every batch: their words then stay in the workspace.
-    const bool taken_over = p.regime == REGIME_SPLIT && split_taken_over(p);
-    if (need > kStaticScratchBytes && !taken_over)
+    if (need > kStaticScratchBytes)
       return fail(FWG_ENOSPACE, "the exchange words of %d streams x %d layers need %zu bytes; the static scratch "
                   "array holds %zu", batch, p.L, need, kStaticScratchBytes);
     if (!h->static_scratch) return fail(FWG_ESTATE, "no static scratch address was set up for this handle");
-    if (need <= kStaticScratchBytes) comm = h->static_scratch;
+    comm = h->static_scratch;
   }
   if (n_steps == 0) return FWG_OK;
   if (!uniforms || !samples) return fail(FWG_EINVAL, "uniforms and samples are required");

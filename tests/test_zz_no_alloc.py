@@ -109,6 +109,37 @@ def test_noalloc_matches_generate_chain_pair():
     na.device_status()
 
 
+@pytest.mark.parametrize("dil,width,B", [((1, 2, 4, 8, 16, 32, 64), 2, 21), ((1, 2, 4, 8, 16) * 4, 2, 21),
+                                         ((1, 3, 9, 27, 2) * 2, 3, 5)])
+def test_noalloc_matches_generate_other_split_layer_counts(dil, width, B):
+    """Layer counts other than multiples of 6 from 12 on, and width 3, also run on blocks that exchange
+    words, but in the workspace: the samples of fwg_generate, and after equal calls on equal workspaces
+    every word of the two workspaces is the same but the blocks' XCD ids (words that had gone to the
+    static array, which calls on other handles share, would be missing)."""
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, dil, 512, 512, filter_width=width)
+    w = W.make_weights(cfg, 31, bias_scale=0.1)
+    u = W.uniforms(49, B, 60)
+    ws, out = [], []
+    for noalloc in (False, True):
+        n = binding.workspace_size(binding.make_desc(cfg.kind, cfg.dtype, 64, dil, B, 512, 512, filter_width=width))
+        buf = torch.zeros(n // 8 * 8 + 8, dtype=torch.uint8, device="cuda")
+        fw = binding.from_model(cfg, w, max_batch=B, workspace=buf)
+        assert fw.lib.fwg_waits(fw.handle) == 1
+        parts = []
+        for a, b in ((0, 20), (20, 60)):
+            ui = _dev(u[:, a:b])
+            if noalloc:
+                parts.append(fw.generate_noalloc(ui, torch.empty((B, b - a), dtype=torch.int32, device="cuda")))
+            else:
+                parts.append(fw.generate(ui))
+        fw.device_status()
+        out.append(torch.cat(parts, dim=1))
+        ws.append(buf.view(torch.int64).clone())
+    assert torch.equal(out[0], out[1])
+    # layer tables hold device addresses (a few words per layer); words of one group: 512 per layer and more
+    assert int((ws[0] != ws[1]).sum()) < 16 * len(dil) + 20 * (B // 16 + 1)
+
+
 def test_noalloc_other_family_and_errors():
     """Kernel families without per-launch scratch run exactly as fwg_generate; host-side errors
     (batch binding, range) come before anything is enqueued."""
