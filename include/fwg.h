@@ -249,12 +249,18 @@ const char *fwg_last_error(void);
 
 /* Short name of the kernel family a handle uses (for logs and profiles).
  * "mfma_bf16_r64_s512" covers both layouts of the MFMA kernels: one block per
- * 16 streams, and, for layer counts other than multiples of 6 from 12 on and
- * for width 3, the split over cooperating blocks (fwg_waits tells them apart). */
+ * 16 streams, and, from 6 layers on, for layer counts other than multiples of 6
+ * from 12 on and for width 3, the split over cooperating blocks (fwg_waits tells
+ * them apart) whose groups fall back to one block when they find no room. */
 const char *fwg_regime(const fwg_handle *h);
 
-/* 1 when the blocks of the handle's launches wait for each other, so that
- * fwg_device_status can report a launch without valid results; else 0. */
+/* 1 when the blocks of the handle's launches wait for each other (they exchange
+ * words), else 0.  The regimes "mfma_split_bf16_r64_s512", "wide_f32_c512" and
+ * "chain_pair_f32_r32" then need every block resident at once, and
+ * fwg_device_status reports launches that were not.  "mfma_bf16_r64_s512" does
+ * not: a group of blocks that is not resident together within some 20 ms gives
+ * up before it has touched any state, and a second launch on the same stream
+ * runs its 16 streams on one block. */
 int fwg_waits(const fwg_handle *h);
 
 /* Wait for every call enqueued on the handle's stream, then report whether a
@@ -262,9 +268,9 @@ int fwg_waits(const fwg_handle *h);
  * when a bounded wait between the cooperating blocks of a split-family launch
  * ran out (its blocks were not all resident on the device at once; that launch
  * then completes quickly with invalid outputs instead of hanging), FWG_EHIP on
- * a HIP error, else FWG_OK.  Kernel families without cross-block waits always
- * return FWG_OK after the synchronisation.  The mark is cleared by
- * fwg_reset_queues. */
+ * a HIP error, else FWG_OK.  Kernel families without cross-block waits, and
+ * those whose blocks need not be resident together (see fwg_waits), return
+ * FWG_OK after the synchronisation.  The mark is cleared by fwg_reset_queues. */
 int fwg_device_status(fwg_handle *h);
 
 #ifdef __cplusplus

@@ -164,9 +164,9 @@ class FastWavenet:
         _check(self.lib.fwg_create(ctypes.byref(self.desc), ctypes.byref(fw), self.workspace.data_ptr(),
                                    self.ws_bytes, self.stream.cuda_stream, ctypes.byref(h)))
         self.handle = h
-        # kernel families whose launches wait on each other's blocks: a wait that ran out leaves
-        # invalid outputs and a sticky device mark, which the calls below check by default
-        self._waits = bool(self.lib.fwg_waits(self.handle))
+        # kernel families whose launches need all their blocks resident at once: a wait that ran out
+        # leaves invalid outputs and a sticky device mark, which the calls below check by default
+        self._waits = self.regime.startswith(("mfma_split", "wide", "chain_pair"))
 
     def _after(self, check: bool):
         if check and self._waits:

@@ -50,7 +50,7 @@ struct Plan {
   int w;                  // filter width: taps per dilated product
   int regime;
   int brows;              // queue rows per slot (max_batch, padded to whole blocks for the MFMA family)
-  size_t off_frags, off_embT, off_bias, off_ptrtab;
+  size_t off_frags, off_frags1, off_embT, off_bias, off_ptrtab;  // (frags1: the single-block MFMA kernel's)
   size_t off_comm, off_sticky;  // split MFMA family: exchange words and the sticky abort word
   long long queue_elems;  // sum(d_l) * bmax * C
   size_t off_layers, off_embed, off_embed_b, off_head, off_head_b, off_out, off_out_b;
@@ -164,6 +164,9 @@ void naive_tables(Plan *p, const int32_t *dil) {
       for (int o : P[l]) p->nv_host.push_back(index_of(o - (w - 1 - k) * dil[l - 1]));
   }
 }
+
+// The layer counts and width that the split kernels took over from the single-block MFMA kernel.
+bool split_taken_over(const Plan &p) { return p.w == 3 || p.L % 6 != 0 || p.L < 12; }
 
 bool kblock_ok(int K, int N, int kb_elems) {
   if (K % kb_elems) return false;
@@ -310,10 +313,17 @@ int make_plan(const fwg_desc *d, Plan *p) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes); return at; };
   p->off_layers = take(sizeof(LayerDev) * p->L);
-  p->off_frags = p->off_embT = p->off_bias = p->off_ptrtab = p->off_comm = p->off_sticky = 0;
+  p->off_frags = p->off_frags1 = p->off_embT = p->off_bias = p->off_ptrtab = p->off_comm = p->off_sticky = 0;
   if (mf_family) {
-    // either family's fragment streams fit (create may fall back from the split family)
-    p->off_frags = take(std::max(mfma_all_frag_bytes(p->L, w), split_shape ? split_frag_bytes(p->L, w) : size_t(0)));
+    if (split_shape && split_taken_over(*p)) {
+      // both kernels' fragment streams: the single-block kernel runs the groups that give up
+      p->off_frags = take(split_frag_bytes(p->L, w));
+      p->off_frags1 = take(mfma_all_frag_bytes(p->L, w));
+    } else {
+      // either family's fragment streams fit (create may fall back from the split family)
+      p->off_frags = take(std::max(mfma_all_frag_bytes(p->L, w), split_shape ? split_frag_bytes(p->L, w) : size_t(0)));
+      p->off_frags1 = p->off_frags;
+    }
     p->off_embT = take((size_t)p->Q * p->C * 2);
     p->off_bias = take(sizeof(float) * mfma_bias_floats(p->L));
     p->off_ptrtab = take(sizeof(void *) * 3 * p->L);
@@ -450,9 +460,6 @@ int make_plan(const fwg_desc *d, Plan *p) {
   return FWG_OK;
 }
 
-// The layer counts and width that the split kernels took over from the single-block MFMA kernel.
-bool split_taken_over(const Plan &p) { return p.w == 3 || p.L % 6 != 0 || p.L < 12; }
-
 }  // namespace
 
 struct fwg_handle {
@@ -469,6 +476,7 @@ struct fwg_handle {
   // the region was last zeroed is at most this), and whether the region has been zeroed since create
   uint32_t sp_tag = 0;
   bool sp_comm_zeroed = false;
+  int sp_polls = kSpPolls;  // split family, taken-over shapes: polls before a group gives up
   // the highest tag of a launch recorded into a graph: a replay clears the words and writes its tags
   // again at any time, so every other launch's tags lie above it
   uint32_t sp_graph_tag = 0;
@@ -505,7 +513,7 @@ StepArgs base_args(const fwg_handle *h) {
   a.last = (int32_t *)(h->ws + p.off_last);
   a.bmax = p.brows;
   if (p.regime == REGIME_MFMA || p.regime == REGIME_SPLIT) {
-    a.mf_frags = h->ws + p.off_frags;
+    a.mf_frags = h->ws + (p.regime == REGIME_SPLIT ? p.off_frags : p.off_frags1);
     a.mf_embT = h->ws + p.off_embT;
     a.mf_bias = (const float *)(h->ws + p.off_bias);
   }
@@ -661,6 +669,10 @@ hipError_t launch_step(fwg_handle *h, const StepArgs &a, void *comm = nullptr) {
       const hipError_t e = exchange_words(h, &b, comm != nullptr, split_comm_bytes(p.L, b.sp_nb),
                                           split_comm_bytes(p.L, p.brows / kMfRows));
       if (e != hipSuccess) return e;
+      if (split_taken_over(p)) {
+        b.sp_polls = h->sp_polls;
+        b.mf_frags1 = h->ws + p.off_frags1;
+      }
       return launch_split_step(b, h->stream);
     }
     case REGIME_WIDE: {
@@ -1088,8 +1100,10 @@ int fwg_create(const fwg_desc *desc, const fwg_weights *w, void *workspace, size
     for (int l = 0; l < p.L; ++l)
       TRY_OR_FREE(launch_split_repack_layer(w->conv[l], w->res[l], w->skip[l], l, p.L, p.w, frags, s));
     TRY_OR_FREE(launch_split_repack_head(w->head, w->out, p.L, p.w, frags, s));
-  } else if (h->plan.regime == REGIME_MFMA) {
-    char *frags = ws + p.off_frags;
+    if (const char *sp = getenv("FWG_SPLIT_POLLS")) h->sp_polls = atoi(sp) != 0 ? atoi(sp) : kSpPolls;  // test hook
+  }
+  if (h->plan.regime == REGIME_MFMA || (h->plan.regime == REGIME_SPLIT && split_taken_over(p))) {
+    char *frags = ws + p.off_frags1;
     // layers first: a layer also writes fragments into the previous stage and the last head stage
     for (int l = 0; l < p.L; ++l)
       TRY_OR_FREE(launch_mfma_repack_layer(w->conv[l], w->res[l], w->skip[l], l, p.L, p.w, frags, s));

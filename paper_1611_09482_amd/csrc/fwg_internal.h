@@ -58,6 +58,16 @@ struct StepArgs {
                            // stream groups (ceil(batch / 4))
   uint32_t sp_tag0;        // families with exchange words: tag base of this launch, above every tag written to sp_comm
                            // since it was last zeroed (handshake and abort mark + 1, step s + 2 + s)
+  // split family, layer counts and width taken over from the single-block kernel: a group whose blocks do not all
+  // report within this many polls gives up before it has touched any state, and the single-block kernel, launched
+  // next, runs its streams (0: no second launch; negative: every group gives up, a test's setting)
+  int sp_polls;
+  const void *mf_frags1;   // the single-block kernel's fragments for that launch
+  // the single-block kernel as that second launch: run block b only if mode word b (mf_mode_stride apart) is
+  // (mf_mode_tag, kSpGaveUp); NULL: run every block
+  const unsigned long long *mf_mode;
+  size_t mf_mode_stride;
+  uint32_t mf_mode_tag;
 };
 
 // What drives the input of each step.
@@ -96,6 +106,10 @@ __host__ __device__ inline size_t mfma_bias_floats(int L) { return (size_t)L * 3
 // H / kSpHelpers hidden channels, and one class block (output 1x1 and sampling).
 // Fragments per layer of chain waves A and (per popped tap) B, and per layer and helper wave.
 constexpr int kSpHelpers = 8;
+constexpr uint32_t kSpGaveUp = 2;  // mode word of a group: 1 all blocks on one XCD, 0 not, 2 gave up
+// Polls of the launch handshake before such a group gives up (~1 us each: the blocks of an idle device report
+// within ~10 us, and the single-block kernel takes twice the split kernels' time per step).
+constexpr int kSpPolls = 1 << 14;
 constexpr int kSpFA = 6, kSpFB = 4, kSpFS = 8;
 inline bool split_layers_ok(int L) { return L >= 6; }
 size_t split_frag_bytes(int L, int w);

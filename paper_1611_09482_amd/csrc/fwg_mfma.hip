@@ -608,6 +608,9 @@ __device__ __forceinline__ void b_role(const Ctx &c, long long total) {
 // TP = recurrent taps per dilated product (filter width - 1): 1 or 2.
 template <int TP>
 __global__ void __launch_bounds__(NT) mfma_step_kernel(StepArgs a) {
+  // as the split launch's second one: only for groups that gave up
+  if (a.mf_mode && a.mf_mode[blockIdx.x * a.mf_mode_stride] != (((unsigned long long)a.mf_mode_tag << 32) | kSpGaveUp))
+    return;
   extern __shared__ float4 lds_raw[];
   Lds &s = *(Lds *)lds_raw;
   const int tid = threadIdx.x;

@@ -86,6 +86,7 @@ static_assert(ZST <= PH && ZST % 4 == 0, "a wave's staged z^l rows fit its parti
 static_assert(SL == 64 && FS == 8 && HL == 64 && QL == 32 && NHLP == NW,
               "helper slices of 4 skip and 4 hidden tiles; 2 class tiles per class-block wave");
 
+constexpr int NOT_HERE = -1;
 template <int TP>
 struct ChainLds {
   uint16_t vbuf[3][TP][ROWS * PX]; // popped queue rows per tap (0: the newest), by running layer count mod 3
@@ -94,7 +95,8 @@ struct ChainLds {
   float pbuf[2][4][2][ROWS * PP];  // W_r v + b of a layer: [layer parity][tile][tanh / sigmoid]
   uint16_t embT[Q * R];            // embedding table, [class][channel]
   int in[ROWS][KCH];               // forced inputs (forced modes)
-  int ins[ROWS + NHLP + 1];        // next inputs, then (at launch) the helpers' and the class block's XCD ids
+  int ins[ROWS + NHLP + 2];        // next inputs, then (at launch) the helpers' and the class block's XCD ids
+                                   // (NOT_HERE: not reported) and the group's mode
   // followed by the per-layer tables: slot[L], depth[L], rbase[L], qoff[TP][2][L] (32-bit), then the
   // fp32 bias block
 };
@@ -425,7 +427,31 @@ __device__ __forceinline__ void set_mode(Ctx<TP> &c) {
   bool local = true;
   for (int h = 0; h < NHLP + 1; ++h) local = local && (uint32_t)c.s->ins[ROWS + h] == xcd_id();
   c.local = local;
-  if (threadIdx.x == 0) put_word(comm_hs(c.a->sp_comm, c.L, c.blk) + HSLOT * (NHLP + 1), local ? 1u : 0u, c.mark, false);
+  if (threadIdx.x == 0) {
+    u64 *word = comm_hs(c.a->sp_comm, c.L, c.blk) + HSLOT * (NHLP + 1);
+    if (c.a->sp_polls == 0) {
+      put_word(word, local ? 1u : 0u, c.mark, false);
+    } else {
+      bool here = true;
+      for (int h = 0; h < NHLP + 1; ++h) here = here && c.s->ins[ROWS + h] != NOT_HERE;
+      c.s->ins[ROWS + NHLP + 1] = (int)decide_word(word, !here ? kSpGaveUp : local ? 1u : 0u, c.mark);
+    }
+  }
+}
+// After the next barrier: whether the group runs (launches whose groups may give up only).
+template <int TP>
+__device__ __forceinline__ bool group_runs(Ctx<TP> &c) {
+  if (c.a->sp_polls == 0) return true;
+  const uint32_t mode = (uint32_t)c.s->ins[ROWS + NHLP + 1];
+  c.local = mode == 1u;
+  return mode != kSpGaveUp;
+}
+// The group's mode as its helpers and class block learn it (one thread).
+__device__ __forceinline__ uint32_t group_mode(const StepArgs &a, u64 *word, uint32_t mark, uint32_t *abort_word) {
+  uint32_t v[1];
+  if (a.sp_polls == 0) wait_words<1>(word, mark, v, abort_word, a.sp_sticky, mark);
+  else if (!poll_word(word, mark, a.sp_polls, v[0])) v[0] = decide_word(word, kSpGaveUp, mark);
+  return v[0];
 }
 
 // Any layer count from 6 on and both widths run on these kernels (before, layer counts other than
@@ -447,7 +473,7 @@ __device__ __forceinline__ void rotate_ring(u32x4 (&W)[D]) {
 }
 
 template <int TP, int REM>
-__device__ __forceinline__ void a_role(Ctx<TP> &c) {
+__device__ __forceinline__ bool a_role(Ctx<TP> &c) {
   const int L = c.L;
   c.fw = (const char *)c.a->mf_frags + base_a(L, c.p) * 1024;
   c.fend = c.fw + (size_t)len_a(L) * 1024;
@@ -460,12 +486,15 @@ __device__ __forceinline__ void a_role(Ctx<TP> &c) {
   const int tid = threadIdx.x;
   if (tid < NHLP + 1) {
     uint32_t v[1];
-    wait_words<1>(comm_hs(c.a->sp_comm, L, c.blk) + HSLOT * tid, c.mark, v, c.abort_word, c.sticky, c.mark);
+    const u64 *word = comm_hs(c.a->sp_comm, L, c.blk) + HSLOT * tid;
+    if (c.a->sp_polls == 0) wait_words<1>(word, c.mark, v, c.abort_word, c.sticky, c.mark);
+    else if (!poll_word(word, c.mark, c.a->sp_polls, v[0])) v[0] = (uint32_t)NOT_HERE;
     c.s->ins[ROWS + tid] = (int)v[0];
   }
   __syncthreads();  // the popped rows of layers 0..2 and the XCD ids are in LDS
   set_mode(c);
   __syncthreads();  // W_r v + b of layer 0 is in LDS
+  if (!group_runs(c)) return false;
   int par = 0;
   for (long long step = 0; step < c.a->n_steps; ++step) {
     int l = 0;
@@ -490,10 +519,11 @@ __device__ __forceinline__ void a_role(Ctx<TP> &c) {
     if constexpr (REM % 3 != 0) rotate_ring<(REM % 3) * FA>(W);
     if constexpr (REM % 2 != 0) par ^= 1;
   }
+  return true;
 }
 
 template <int TP, int REM, int AH>
-__device__ __forceinline__ void b_role(Ctx<TP> &c) {
+__device__ __forceinline__ bool b_role(Ctx<TP> &c) {
   constexpr int FB = frags_b(TP);
   constexpr int NB = DB / FB;  // layers the weight ring holds
   const int L = c.L;
@@ -517,6 +547,7 @@ __device__ __forceinline__ void b_role(Ctx<TP> &c) {
   for (int f = 0; f < DB; ++f) W[f] = frag_at(c, f);
   c.nxt = c.fw + DB * 1024;
   __syncthreads();
+  if (!group_runs(c)) return false;
   int par = 0, v3 = 0;  // the running layer count mod 2 and mod 3 at layer 0 of the step
   for (long long step = 0; step < c.a->n_steps; ++step) {
     const uint32_t tag = step_tag(*c.a, step);
@@ -546,6 +577,7 @@ __device__ __forceinline__ void b_role(Ctx<TP> &c) {
     if constexpr (REM % 3 == 1) v3 = v4;
     if constexpr (REM % 3 == 2) v3 = v5;
   }
+  return true;
 }
 
 template <int TP, int REM, int AH>
@@ -645,9 +677,8 @@ __device__ __forceinline__ void chain_block(const StepArgs &a, char *lds_raw, in
   // The launch handshake (the helpers' and the class block's XCD ids, then the group's mode) runs
   // inside the roles' first loads: wave A polls the ids while its weight loads and wave B's first
   // pops are in flight.
-  if (c.w < 4) a_role<TP, REM>(c);
-  else b_role<TP, REM, AH>(c);
-  if (a.mode != MODE_TEACHER && tid < c.nrows) a.last[c.b0 + tid] = s.ins[tid];
+  const bool ran = c.w < 4 ? a_role<TP, REM>(c) : b_role<TP, REM, AH>(c);
+  if (ran && a.mode != MODE_TEACHER && tid < c.nrows) a.last[c.b0 + tid] = s.ins[tid];
 }
 
 // ---------------------------------------------------------------------------
@@ -831,12 +862,9 @@ __device__ __forceinline__ void helper_block(const StepArgs &a, char *lds_raw, i
     for (int i = 0; i < 8; ++i) hw1[i] = w1[((w & 3) * (S / 32) + 8 * (w >> 2) + i) * 64 + lane];
   }
   // launch handshake, second half: learn whether the whole group shares one XCD
-  if (tid == 0) {
-    uint32_t v[1];
-    wait_words<1>(hs + HSLOT * (NHLP + 1), mark, v, abort_word, a.sp_sticky, mark);
-    s.local = (int)v[0];
-  }
+  if (tid == 0) s.local = (int)group_mode(a, hs + HSLOT * (NHLP + 1), mark, abort_word);
   __syncthreads();
+  if ((uint32_t)s.local == kSpGaveUp) return;
   HelperCtx c;
   c.a = &a;
   c.s = &s;
@@ -890,12 +918,9 @@ __device__ __forceinline__ void class_block(const StepArgs &a, char *lds_raw, in
       for (int ks = 0; ks < H / 32; ++ks) wo[j][ks] = src[(j * (H / 32) + ks) * 64 + lane];
   }
   // launch handshake, second half: learn whether the whole group shares one XCD
-  if (tid == 0) {
-    uint32_t v[1];
-    wait_words<1>(hs + HSLOT * (NHLP + 1), mark, v, abort_word, a.sp_sticky, mark);
-    s.local = (int)v[0];
-  }
+  if (tid == 0) s.local = (int)group_mode(a, hs + HSLOT * (NHLP + 1), mark, abort_word);
   __syncthreads();
+  if ((uint32_t)s.local == kSpGaveUp) return;
   const bool local = s.local != 0;
   for (long long step = 0; step < a.n_steps; ++step) {
     const uint32_t tag = step_tag(a, step);
@@ -1124,7 +1149,14 @@ size_t split_lds_bytes(int L, int w) {
 hipError_t launch_split_step(const StepArgs &a, hipStream_t s) {
   const dim3 grid(sp::grid_blocks(a.sp_nb)), block(kMfThreads);
   hipLaunchKernelGGL(sp::kernel_of(a.L, a.w), grid, block, split_lds_bytes(a.L, a.w), s, a);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.sp_polls == 0) return e;
+  StepArgs b = a;
+  b.mf_frags = a.mf_frags1;
+  b.mf_mode = sp::comm_hs(a.sp_comm, a.L, 0) + sp::HSLOT * (kSpHelpers + 1);
+  b.mf_mode_stride = sp::group_words(a.L);
+  b.mf_mode_tag = a.sp_tag0 + 1u;
+  return launch_mfma_step(b, s);
 }
 
 hipError_t split_setup(int L, int w, int nb, int *coresident_ok) {

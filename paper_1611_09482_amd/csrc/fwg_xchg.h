@@ -81,5 +81,28 @@ __device__ __forceinline__ void wait_words(const u64 *p, uint32_t tag, uint32_t 
   for (int e = 0; e < N; ++e) out[e] = (uint32_t)v[e];
 }
 
+// Poll one word for `tag`, at most `polls` times; whether it came.
+__device__ __forceinline__ bool poll_word(const u64 *p, uint32_t tag, int polls, uint32_t &out) {
+  for (int it = 0; it < polls; ++it) {
+    const u64 v = get_word(p);
+    if ((uint32_t)(v >> 32) == tag) {
+      out = (uint32_t)v;
+      return true;
+    }
+  }
+  return false;
+}
+// Set a word that several blocks may set for `tag`: the first one's payload stands and is returned (a word
+// that fails the exchange holds that payload already, or an older word its load had not shown yet).
+__device__ __forceinline__ uint32_t decide_word(u64 *p, uint32_t payload, uint32_t tag) {
+  u64 cur = get_word(p);
+  while ((uint32_t)(cur >> 32) != tag) {
+    const u64 want = ((u64)tag << 32) | payload;
+    if (__hip_atomic_compare_exchange_strong(p, &cur, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return payload;
+  }
+  return (uint32_t)cur;
+}
+
 }  // namespace xg
 }  // namespace fwg

@@ -113,6 +113,98 @@ def test_split_graph_replays(n_layers, B):
         fw.device_status()
 
 
+SPLIT_OTHER = [(2, 7, 37), (2, 20, 100), (3, 14, 20)]  # width, layers, streams: not "mfma_split" by name
+
+
+def split_other(width, n_layers, B, **env):
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, tuple((1, 3, 2, 7, 1, 5)[i % 6] for i in range(n_layers)), 512, 512,
+                        filter_width=width)
+    w = W.make_weights(cfg, 45, bias_scale=0.1)
+    return cfg, w, model(cfg, w, B, **env)
+
+
+@pytest.mark.parametrize("width,n_layers,B", SPLIT_OTHER)
+@pytest.mark.parametrize("polls", ["-1", "1", "3"])
+def test_split_groups_that_give_up(width, n_layers, B, polls):
+    """Groups that give up (all of them; those whose blocks do not report within one or three polls, so that
+    some do and some do not) run on the single-block kernel: teacher forcing, online prediction and
+    generation over several launches whose groups may change sides, against the oracle and (all of them)
+    the single-block kernel's bits."""
+    cfg, w, fw = split_other(width, n_layers, B, FWG_SPLIT_POLLS=polls)
+    one = model(cfg, w, B, FWG_REGIME="mfma")
+    assert fw.lib.fwg_waits(fw.handle) == 1 and one.lib.fwg_waits(one.handle) == 0
+    x = W.sequences(46, B, 50)
+    want = one.teacher_forced(dev(x))
+    sel = [0, B // 2, B - 1]
+    assert row_rel_err(want.cpu().numpy()[sel], oracle.Oracle(w).teacher_forced(x[sel])) <= TOL[W.BF16]
+    for _ in range(3):
+        got = fw.teacher_forced(dev(x))
+        assert row_rel_err(got.cpu().numpy(), want.cpu().numpy()) <= TOL[W.BF16]
+        assert polls != "-1" or torch.equal(got, want)
+    steps, ref = [], one.step_forced(dev(x))
+    for a, b in ((0, 1), (1, 2), (2, 17), (17, 50)):
+        steps.append(fw.step_forced(dev(x[:, a:b])))
+    assert row_rel_err(torch.cat(steps, 1).cpu().numpy(), ref.cpu().numpy()) <= TOL[W.BF16]
+    u = dev(W.uniforms(47, B, 30))
+    g = fw.generate(u)
+    fw.device_status()
+    assert int(g.min()) >= 0 and int(g.max()) <= 255
+    assert polls != "-1" or torch.equal(g, one.generate(u))
+
+
+@pytest.mark.parametrize("width,n_layers,B", [(2, 7, 400), (3, 14, 384)])
+def test_split_launches_that_share_the_device(width, n_layers, B):
+    """Two handles whose launches would each fill the device, on two streams at once, with default
+    arguments: valid logits and samples on both, whichever groups find room."""
+    cfg, w, ref = split_other(width, n_layers, B)
+    x, u = dev(W.sequences(48, B, 120)), dev(W.uniforms(49, B, 120))
+    want = ref.teacher_forced(x).cpu().numpy()
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    fws = []
+    for s in streams:
+        with torch.cuda.stream(s):
+            fws.append(binding.from_model(cfg, w, max_batch=B))
+    got = []
+    for _ in range(4):
+        for s, fw in zip(streams, fws):
+            with torch.cuda.stream(s):
+                got.append((fw.teacher_forced(x), fw.generate(u)))
+    torch.cuda.synchronize()
+    for fw in fws:
+        fw.device_status()
+    for lg, g in got:
+        assert row_rel_err(lg.cpu().numpy(), want) <= TOL[W.BF16]
+        assert int(g.min()) >= 0 and int(g.max()) <= 255
+
+
+@pytest.mark.parametrize("width,n_layers,B", SPLIT_OTHER)
+def test_split_other_layer_counts_return_after_the_enqueue(width, n_layers, B):
+    """With default arguments the calls of these shapes do not synchronise: they can be recorded into a graph,
+    whose replays give the eager results, with eager calls in between."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        cfg, w, fw = split_other(width, n_layers, B)
+        x, u = dev(W.sequences(43, B, 20)), dev(W.uniforms(44, B, 20))
+        lg, g = torch.empty((B, 20, 256), device="cuda"), torch.empty((B, 20), dtype=torch.int32, device="cuda")
+        fw.step_forced(x, out=lg)
+        fw.generate(u, out=g)
+        want = lg.clone(), g.clone()
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            fw.reset()
+            fw.step_forced(x, out=lg)
+            fw.generate(u, out=g)
+        for _ in range(3):
+            lg.zero_()
+            g.zero_()
+            graph.replay()
+            s.synchronize()
+            assert torch.equal(lg, want[0]) and torch.equal(g, want[1])
+            fw.teacher_forced(x)
+
+
 @pytest.mark.parametrize("n_layers,B,T,rows", [(2, 1, 40, None), (9, 3, 700, None), (12, 5, 257, None), (10, 17, 300, 64),
                                                (30, 2, 1100, None), (7, 33, 31, 96)])
 def test_parallel_stack(n_layers, B, T, rows):
