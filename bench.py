@@ -254,7 +254,7 @@ def bench_online(args, wl, name, fw, weights, stream, K, Wu):
         "dtype": dtype,
         "data": "synthetic",
         "config": {"workload": name, "description": wl.description, "batch": B, "seq_len": K,
-                   "mode": "online", "regime": fw.regime},
+                   "mode": "online", "regime": fw.regime, "waits": bool(fw.lib.fwg_waits(fw.handle))},
         "roofline": {"bound": "mfma" if mfma else "alu", "achieved": achieved, "peak": peak,
                      "unit": "TFLOP/s", "frac": achieved / peak, "traffic": None,
                      "algorithmic_flops_per_launch": flops, "launch_ms": ms},
@@ -512,6 +512,9 @@ def main():
             "batch": B,
             "steps_per_launch": K,
             "regime": fw.regime,
+            # whether the step kernel's blocks exchange words (of the regime "mfma_bf16_r64_s512": the
+            # split kernels, not the single-block one)
+            "waits": bool(fw.lib.fwg_waits(fw.handle)),
         },
         "roofline": {
             "bound": bound,

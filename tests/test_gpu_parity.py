@@ -129,7 +129,9 @@ FAMILIES = {
     "gated_r64_bf16": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32, 64, 128), 512, 512),
     "gated_r64_bf16_valu": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32, 64, 128), 512, 512),
     "gated_r64_bf16_odd": W.ModelConfig(W.GATED, W.BF16, 64, (1, 3, 1, 7, 2), 512, 512),
-    # 12 layers: the split MFMA kernels (chain block + skip helper blocks; L a multiple of 6, >= 12)
+    # the single-block MFMA kernel at a layer count the split kernels take (FWG_REGIME=mfma)
+    "gated_r64_bf16_one": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32, 64, 128), 512, 512),
+    # 12 layers: the split MFMA kernels' first layer count without a tail after the six-layer loop
     "gated_r64_bf16_split": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32) * 2, 512, 512),
     # 36 layers: more than four layers per helper wave, so the helpers stream their skip fragments
     # (at most 32 layers they keep them in registers)
@@ -148,9 +150,10 @@ FAMILIES = {
     "gated_r32_w3_f32_valu": W.ModelConfig(W.GATED, W.F32, 32, (1, 3, 9, 27, 1, 3, 9), 256, 256, filter_width=3),
     "gated_r32_w3_f32_one": W.ModelConfig(W.GATED, W.F32, 32, (1, 3, 9, 27, 1, 3, 9), 256, 256, filter_width=3),
     "gated_r64_w3_bf16": W.ModelConfig(W.GATED, W.BF16, 64, (1, 3, 9, 27, 2), 512, 512, filter_width=3),
-    # width 3 on the MFMA kernel with a layer count the split kernels would take at width 2, and
-    # one layer (the oldest tap's fragments of the next step's layer 0 reloaded every step)
+    # width 3 on the split kernels and, forced, on the single-block MFMA kernel, and one layer (the
+    # single-block kernel; the oldest tap's fragments of the next step's layer 0 reloaded every step)
     "gated_r64_w3_bf16_l12": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32) * 2, 512, 512, filter_width=3),
+    "gated_r64_w3_bf16_l12_one": W.ModelConfig(W.GATED, W.BF16, 64, (1, 2, 4, 8, 16, 32) * 2, 512, 512, filter_width=3),
     "gated_r64_w3_bf16_l1": W.ModelConfig(W.GATED, W.BF16, 64, (3,), 512, 512, filter_width=3),
     "gated_r64_w3_bf16_valu": W.ModelConfig(W.GATED, W.BF16, 64, (1, 3, 9, 27, 2), 512, 512, filter_width=3),
     "relures_c64_w4_bf16": W.ModelConfig(W.RELU_RESIDUAL, W.BF16, 64, (1, 4, 16, 2), filter_width=4),
@@ -177,6 +180,8 @@ WIDE_FAMILIES = {"relures_c512_f32", "relures_c512_f32_q255"}
 # wide one
 FORCE_VALU = {"gated_r64_bf16_valu", "relu_c32_f32_valu", "relures_c512_f32_valu", "gated_r32_f32_valu",
               "gated_r32_w3_f32_valu", "gated_r64_w3_bf16_valu"}
+# families whose test forces the single-block MFMA kernel instead of the split ones
+FORCE_MFMA = {"gated_r64_bf16_one", "gated_r64_w3_bf16_l12_one"}
 # families whose test forces the wave-per-stream family instead of the chain one
 FORCE_WAVE = {"relu_c32_f32_wave"}
 
@@ -189,21 +194,25 @@ def tf(fw, x, path):
     return out
 
 
-def build_pair(cfg, seed, max_batch, bias_scale=0.1, fam=None, par_rows=None, valu_stage=None):
-    """par_rows: rows per chunk of the time-parallel path (small values force many chunks);
-    valu_stage: "0" keeps the general step kernels from staging weights in LDS."""
+def split_kernel(fw):
+    """Whether a handle of the MFMA shape runs the split kernels (their blocks wait for each other)."""
+    return fw.lib.fwg_waits(fw.handle) == 1
+
+
+def build_pair(cfg, seed, max_batch, bias_scale=0.1, fam=None, par_rows=None):
+    """par_rows: rows per chunk of the time-parallel path (small values force many chunks)."""
     w = W.make_weights(cfg, seed, bias_scale=bias_scale)
     env = {}
     if fam in FORCE_VALU:
         env["FWG_REGIME"] = "valu"
+    if fam in FORCE_MFMA:
+        env["FWG_REGIME"] = "mfma"
     if fam in FORCE_WAVE:
         env["FWG_REGIME"] = "wave"
     if fam in FORCE_CHAIN1:
         env["FWG_REGIME"] = "chain1"
     if par_rows is not None:
         env["FWG_PAR_ROWS"] = str(par_rows)
-    if valu_stage is not None:
-        env["FWG_VALU_STAGE"] = valu_stage
     os.environ.update(env)
     try:
         fw = binding.from_model(cfg, w, max_batch=max_batch)
@@ -216,9 +225,11 @@ def build_pair(cfg, seed, max_batch, bias_scale=0.1, fam=None, par_rows=None, va
         if fam in FORCE_VALU:
             assert fw.regime == "valu", (fam, fw.regime)
         elif mfma_shape:
-            # the split kernels take width 2 and layer counts that are multiples of 6, at least 12
-            split = cfg.filter_width == 2 and cfg.n_layers % 6 == 0 and cfg.n_layers >= 12
-            assert fw.regime == ("mfma_split_bf16_r64_s512" if split else "mfma_bf16_r64_s512"), (fam, fw.regime)
+            # the split kernels take both widths from 6 layers on; the regime names width 2 and multiples of
+            # 6 from 12 on apart (those launches need every block resident at once)
+            assert split_kernel(fw) == (cfg.n_layers >= 6 and fam not in FORCE_MFMA), fam
+            named = split_kernel(fw) and cfg.filter_width == 2 and cfg.n_layers % 6 == 0 and cfg.n_layers >= 12
+            assert fw.regime == ("mfma_split_bf16_r64_s512" if named else "mfma_bf16_r64_s512"), (fam, fw.regime)
         else:
             assert fw.regime in ("valu", "wave", "chain_f32_c32", "chain_gated_f32_r32", "chain_pair_f32_r32",
                                  "wide_f32_c512"), (fam, fw.regime)
@@ -375,19 +386,18 @@ def test_prime_then_generate(fam):
 
 
 @pytest.mark.parametrize("fam", ["relu_c32_f32_valu", "gated_r32_f32", "gated_r64_bf16_valu", "gated_r64_w3_bf16_valu"])
-def test_valu_unstaged_variant(fam):
-    """The general step kernels without LDS weight staging (the variant taken at one stream per
-    block or for wide layers), at a batch that would otherwise stage: teacher-forced logits and
-    generation against the oracle."""
+def test_step_kernels_past_their_queues(fam):
+    """The general step kernels (and the gated chain pair) at 11 streams past every queue's wrap, with
+    another seed than the parity tests: teacher-forced logits and generation against the oracle."""
     cfg = FAMILIES[fam]
     B = 11
-    w, fw, orc = build_pair(cfg, 106, B, fam=fam, valu_stage="0")
+    w, fw, orc = build_pair(cfg, 106, B, fam=fam)
     T = cfg.queue_total + 45
     x = W.sequences(20, B, T)
     err = row_rel_err(fw.teacher_forced(dev(x)).cpu().numpy(), orc.teacher_forced(x))
-    log(f"{fam} [{fw.regime}, unstaged]: TF max row rel err {err.max():.3e}")
+    log(f"{fam} [{fw.regime}]: TF max row rel err {err.max():.3e}")
     assert err.max() <= tol(cfg)
-    check_generation(cfg, fw, orc, W.uniforms(21, B, T), B, fam + " unstaged")
+    check_generation(cfg, fw, orc, W.uniforms(21, B, T), B, fam)
 
 
 @pytest.mark.parametrize("fam", list(FAMILIES))
@@ -508,6 +518,7 @@ def test_delay_line_closed_form_gpu(fwidth, dil, path):
 
 
 @pytest.mark.parametrize("fam,B,regime", [("gated_r64_bf16", 16, "mfma_bf16_r64_s512"),
+                                          ("gated_r64_bf16_one", 16, "mfma_bf16_r64_s512"),
                                           ("gated_r64_bf16_split", 13, "mfma_split_bf16_r64_s512"),
                                           ("gated_r32_f32", 5, "chain_pair_f32_r32"),
                                           ("gated_r32_f32_one", 3, "chain_gated_f32_r32"),
@@ -522,6 +533,8 @@ def test_uniform_logits_sampler_gpu(fam, B, regime):
     n = 400
     if fam in FORCE_CHAIN1:
         os.environ["FWG_REGIME"] = "chain1"
+    if fam in FORCE_MFMA:
+        os.environ["FWG_REGIME"] = "mfma"
     try:
         fw = binding.from_model(cfg, w, max_batch=B)
     finally:
@@ -557,11 +570,9 @@ def test_continuation_reset_and_determinism_gpu(fam):
 
 @pytest.mark.parametrize("B", [1, 37])
 def test_split_multi_group_ragged(B):
-    """The split kernels over three groups with a ragged last one (37 streams = 16 + 16 + 5): the
-    helpers and class blocks of groups 1 and 2 sit on other XCDs than their chain blocks, so those
-    groups exchange words with device-scope stores while group 0 uses workgroup-scope ones; and one
-    stream (a single group with 15 padded rows).  Teacher forcing through the step kernels and
-    generation against the oracle, across several 64-step input chunks."""
+    """The split kernels over three groups with a ragged last one (37 streams = 16 + 16 + 5), each group
+    on an XCD of its own; and one stream (a single group with 15 padded rows).  Teacher forcing through
+    the step kernels and generation against the oracle, across several 64-step input chunks."""
     cfg = FAMILIES["gated_r64_bf16_split"]
     n = 200
     w, fw, orc = build_pair(cfg, 102, B, fam="gated_r64_bf16_split")
@@ -592,6 +603,49 @@ def test_split_largest_resident_batch_and_fallback(B, regime):
     err = row_rel_err(lg[sel], oracle.Oracle(w).teacher_forced(x[sel]))
     log(f"B={B} [{fw.regime}]: TF streams {sel} max row rel err {err.max():.3e}")
     assert err.max() <= tol(cfg)
+
+
+@pytest.mark.parametrize("width,n_layers,B", [(2, 12, 397), (2, 13, 400), (2, 7, 385), (3, 14, 390), (3, 9, 400)])
+def test_split_groups_across_xcds(width, n_layers, B):
+    """25 groups: no XCD has room for a fourth row of whole groups, so most groups' blocks sit on several
+    XCDs and their words go through device-scope stores.  Generation in two launches and online prediction
+    after it give the bits of handles of up to 200 streams (every group on one XCD); the logits on the
+    samples against the oracle on two streams."""
+    dil = tuple((1, 3, 2, 7, 1, 5)[i % 6] for i in range(n_layers))
+    cfg = W.ModelConfig(W.GATED, W.BF16, 64, dil, 512, 512, filter_width=width)
+    w = W.make_weights(cfg, 114, bias_scale=0.1)
+    fw, part = binding.from_model(cfg, w, max_batch=B), binding.from_model(cfg, w, max_batch=200)
+    assert split_kernel(fw) and split_kernel(part)
+    u, x = dev(W.uniforms(115, B, 70)), dev(W.sequences(116, B, 9))
+    g = torch.cat([fw.generate(u[:, :33].contiguous()), fw.generate(u[:, 33:].contiguous())], 1)
+    lg = fw.step_forced(x)
+    fw.device_status()
+    for a, b in ((0, 200), (200, B)):
+        part.reset()
+        assert torch.equal(part.generate(u[a:b].contiguous()), g[a:b])
+        assert torch.equal(part.step_forced(x[a:b].contiguous()), lg[a:b])
+    sel = [17, B - 1]
+    seq = torch.cat([g, x], 1)[sel].cpu().numpy()
+    st = oracle.Oracle(w).state(2)
+    assert row_rel_err(lg.cpu().numpy()[sel], st.step_forced(seq)[:, 70:]).max() <= tol(cfg)
+
+
+def test_split_fallback_width_3():
+    """512 streams of a width-3 model: the split kernels' blocks do not fit at once, and fwg_create takes
+    the single-block kernel.  Teacher forcing and generation, the oracle on sampled streams."""
+    cfg = FAMILIES["gated_r64_w3_bf16_l12"]
+    w = W.make_weights(cfg, 117, bias_scale=0.1)
+    fw = binding.from_model(cfg, w, max_batch=512)
+    assert not split_kernel(fw)
+    orc, sel = oracle.Oracle(w), [0, 200, 511]
+    x = W.sequences(118, 512, 80)
+    assert row_rel_err(fw.teacher_forced(dev(x)).cpu().numpy()[sel], orc.teacher_forced(x[sel])).max() <= tol(cfg)
+    u = W.uniforms(119, 512, 40)
+    g = fw.generate(dev(u)).cpu().numpy()
+    seq = np.concatenate([np.full((512, 1), cfg.seed_input, np.int32), g[:, :-1]], axis=1)
+    glg = fw.teacher_forced(dev(seq)).cpu().numpy()
+    assert row_rel_err(glg[sel], orc.teacher_forced(seq[sel])).max() <= tol(cfg)
+    check_samples_exact(g[sel], glg[sel], u[sel], "512 streams, width 3")
 
 
 @pytest.mark.parametrize("fam,B,regime", [("gated_r32_f32", 128, "chain_pair_f32_r32"),
@@ -835,11 +889,17 @@ def test_full_gated_w3():
     _check_streams_on_gpu_sequence(wl, fw, orc, u, g, [0, 63], wl.n_steps)
 
 
-def test_full_gated_w3_bf16():
+@pytest.mark.parametrize("split", [True, False])
+def test_full_gated_w3_bf16(split):
     """Width 3 on the benchmark's layer shape at full size (256 streams x 8,000 steps, queues up to
-    1,458 deep) on the MFMA step kernel: sampled streams checked by the oracle over every step."""
-    wl, w, fw, orc = _full("gated_r64_s512_w3_l14_b256_bf16")
-    assert fw.regime == "mfma_bf16_r64_s512"
+    1,458 deep) on the split and the single-block kernel: sampled streams checked by the oracle over every
+    step."""
+    os.environ.update({} if split else {"FWG_REGIME": "mfma"})
+    try:
+        wl, w, fw, orc = _full("gated_r64_s512_w3_l14_b256_bf16")
+    finally:
+        os.environ.pop("FWG_REGIME", None)
+    assert fw.regime == "mfma_bf16_r64_s512" and split_kernel(fw) == split
     u = W.uniforms(wl.uniform_seed, wl.batch, wl.n_steps)
     t0 = time.time()
     g = fw.generate(dev(u)).cpu().numpy()
