@@ -18,7 +18,7 @@ generation time per sample of the cached method (fwg_generate) and of the naive
 tree recomputation (fwg_generate_naive), each averaged over --repeats calls of
 --naive-samples samples.
 
-Prints one JSON line (see the design doc for the field definitions).
+Prints one JSON line.
 """
 from __future__ import annotations
 

@@ -308,9 +308,13 @@ static hipError_t launch_em_t(const ParGemm &g, int em, dim3 grid, hipStream_t s
 
 // 128-wide tiles for outputs at least 128 wide over at least 4096 rows, else 64-wide tiles.  float32
 // products are bound by the matrix cores at either size (64-wide tiles stage twice the bytes per product
-// but their products are 4x slower than bf16 ones), so they take the tiles whose count fills the compute
-// units more evenly: 10,656 x 512 outputs are 336 large tiles (2 rounds of 256) or 1,336 small ones (6
-// rounds of a quarter), K = 1024: 161 us against 122.
+// but their products are 4x slower than bf16 ones), so they take the tiles whose count needs fewer rounds of
+// the compute units, a small tile counted as a quarter: 10,656 x 512 outputs are 336 large tiles (2 rounds of
+// 256) or 1,336 small ones (6 rounds of a quarter).  Measured, us large / small, K = 1024, N = 512: 4,096 rows
+// 92 / 52, 9,600 154 / 102, 10,656 156 / 121, 20,800 291 / 213 (small taken), 16,384 162 / 162, 32,768 319 / 301
+// (large taken).  The count is too kind to the large tiles where it takes them just past a round of the small
+// ones (6,400 rows 99 / 81, 24,576 305 / 232; N = K / 2 = 256: 16,384 rows 64 / 48): no row count was found where
+// they are the faster, but they are what these chunks took before the rule.
 template <typename OT, int AM>
 static hipError_t launch_em(const ParGemm &g, int em, hipStream_t s) {
   bool wide = g.N >= 128 && g.M >= 4096;

@@ -36,6 +36,14 @@
 // word lets the host report it); every wave keeps executing its straight-line program, so the grid
 // always drains.
 //
+// The layer counts and width that came to these kernels from the single-block kernel (a.sp_polls != 0) keep
+// its independence of what else runs on the device: a group's mode word is set once, by compare-and-exchange,
+// either by its chain block once all ten blocks have reported (run) or by whichever block ran out of polls
+// first (give up).  Nothing but loads has happened by then, so the single-block kernel, launched right after
+// on the same stream, runs the groups that gave up from the same state and exits at once for the others (the
+// second launch costs ~4 us; a group that runs has all its blocks resident, so none of its later waits
+// depends on other launches).
+//
 // Chain block: 8 waves, A = waves 0..3 and B = waves 4..7, A and B of pair p share SIMD p.
 //  - wave A (p): the current-input half of the dilated product (W_e x) for tanh tile p and
 //    sigmoid tile p, plus W_r v + b from LDS, the gate, the residual 1x1 for channel tile p;
