@@ -186,8 +186,9 @@ class FastWavenet:
 
     def generate(self, uniforms, out=None, check: bool = True):
         """uniforms: float32 CUDA tensor [batch][n_steps] -> int32 samples [batch][n_steps].
-        check: for kernel families with cross-block waits, synchronise and raise FwgError (EDEVICE)
-        if the launch ended without valid results (False: return right after the enqueue)."""
+        check: for kernel families whose launches need all their blocks resident at once, synchronise
+        and raise FwgError (EDEVICE) if the launch ended without valid results (False, and every other
+        family: return right after the enqueue)."""
         torch = self._torch
         assert uniforms.dtype == torch.float32 and uniforms.is_cuda and uniforms.is_contiguous()
         B, n = uniforms.shape
